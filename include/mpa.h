@@ -323,7 +323,10 @@ typedef struct {
   int32_t num_prefill_seqs;  /* sequences with q_len > 1 */
   int32_t split_tokens;      /* nominal KV tokens per decode split: a row of L keys is cut into
                                 ceil(L / split_tokens) parts of equal size, rounded up to whole
-                                blocks (the last part ends at L) */
+                                blocks (the last part ends at L).  On a device that the batch's
+                                rows fill for long, the rows laid end to end, block by block, are
+                                cut into ranges of split_tokens instead, and a row's parts are
+                                its intersections with them */
   int32_t num_decode_items;  /* (sequence, split) work items */
   int32_t num_prefill_tiles; /* (sequence, query tile, KV split, KV head) work items */
   int32_t decode_launches;   /* decode kernel launches (sequence chunks) */

@@ -25,8 +25,7 @@ constexpr int kMaskWords = 8;  // CU-mask words: devices of up to 256 CUs
 
 struct Batch {
   std::vector<int> decode;   // sequence ids with q_len == 1
-  std::vector<int> prefill;  // sequence ids with q_len > 1
-  long decode_tokens = 0;    // sum of KV lengths of decode rows
+  std::vector<int> prefill;  // sequence ids with q_len > 1, in launch order
 };
 
 int check_shape(const mpa_shape* sh) {
@@ -76,9 +75,9 @@ bool prefill_whole(const mpa_shape* sh, const std::vector<int>& prefill, const i
   return units >= 2L * mpa::kPrefillSplitTarget || most == 1;
 }
 
-// Validates the host metadata and classifies the sequences.
+// Validates the host metadata.
 int check_batch(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl, const int32_t* bt_host,
-                bool append_only, Batch* b) {
+                bool append_only) {
   int rc = check_shape(sh);
   if (rc != MPA_OK) return rc;
   const int S = sh->num_seqs;
@@ -100,21 +99,26 @@ int check_batch(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl
         if (id < 0 || id >= sh->num_blocks) return MPA_ERR_INVALID;
       }
     }
-    if (ql == 1) {
-      b->decode.push_back(s);
-      b->decode_tokens += L;
-    } else {
-      b->prefill.push_back(s);
-    }
+  }
+  return MPA_OK;
+}
+
+// The sequences of a valid batch by kind.
+Batch classify(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl) {
+  Batch b;
+  for (int s = 0; s < sh->num_seqs; ++s) {
+    const int ql = qsl[s + 1] - qsl[s];
+    if (ql == 1) b.decode.push_back(s);
+    if (ql > 1) b.prefill.push_back(s);
   }
   // The MFMA prefill kernel dispatches its work units from the plan's last
   // chunk backwards, each chunk from its longest query tile (the one that
   // sees all L keys).  With whole chunks ordered by L, the longest units go
   // first and the short ones fill the end of the launch.  A split chunk's
   // units are not ordered by length, so split batches keep batch order.
-  if (sh->dtype != MPA_F32 && b->prefill.size() > 1 && prefill_whole(sh, b->prefill, seq_lens, qsl))
-    std::stable_sort(b->prefill.begin(), b->prefill.end(), [&](int x, int y) { return seq_lens[x] < seq_lens[y]; });
-  return MPA_OK;
+  if (sh->dtype != MPA_F32 && b.prefill.size() > 1 && prefill_whole(sh, b.prefill, seq_lens, qsl))
+    std::stable_sort(b.prefill.begin(), b.prefill.end(), [&](int x, int y) { return seq_lens[x] < seq_lens[y]; });
+  return b;
 }
 
 // How a decode row of L keys is split at nominal split size S: into
@@ -143,13 +147,13 @@ RowSplit row_split(int L, int S) {
 // splits fill the last round of waves; fewer, larger ones cut start-up and
 // merge work).  MPA_SPLIT_TOKENS (a multiple of 16, at most 1024) overrides
 // it for tuning sweeps.
-int choose_split_uncached(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens) {
+int choose_split(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens) {
   if (const char* env = getenv("MPA_SPLIT_TOKENS")) {
     const int v = atoi(env);
     if (v >= kBlock && v <= 1024 && v % kBlock == 0) return v;
   }
   if (b.decode.empty()) return 1024;
-  const long slots = mpa::decode_wave_slots(sh->dtype, sh->head_dim);
+  const long slots = mpa::decode_wave_slots(sh->dtype, sh->head_dim, false);
   const long overhead = 64;
   long best_cost = -1;
   int best = 1024;
@@ -166,58 +170,74 @@ int choose_split_uncached(const mpa_shape* sh, const Batch& b, const int32_t* se
   return best;
 }
 
-// Per-thread memo of the last batch's two plan choices (the decode split
-// and the prefill split count).  One step plans its batch several times --
-// workspace sizing, the append, each attention half, the step model -- and
-// the searches behind the choices cost more host time than the rest of the
-// plan.  The key is everything the choices depend on: the shape's heads,
-// head_dim and dtype, the exact seq_lens and query_start_loc, the device
-// (its wave capacity) and the tuning overrides in the environment.
-struct PlanMemo {
-  int32_t key[7] = {-1, -1, -1, -1, -1, -1, -1};
-  std::vector<int32_t> seq_lens, qsl;
-  int split = 0;  // 0: not chosen yet
-  int want = 0;
+int row_blocks(int L) { return (int)(((long)L + kBlock - 1) / kBlock); }
+
+// The fewest blocks per wave at which a launch's rows are dealt to the waves
+// as ranges of equal size (the streaming decode kernel) instead of each row
+// being split on its own.  Below it the waves' few blocks do not pay for the
+// wider launch and the rows cut at odd places; measured on 8 to 192 rows of
+// 512-8,192 and 2,048-16,384 tokens (blocks per wave: time of row splits ->
+// of ranges, decode and merge), the two meet at
+//   bf16, d 128: 12 blocks 58.6 -> 61.4 us, 24 100.6 -> 99.4, 42 169.7 ->
+//                165.8, 102 417 -> 385;
+//   bf16, d 64:  6 blocks 28.3 -> 29.1 us, 10 38.8 -> 37.3, 26 82.9 -> 77.7;
+//   fp8,  d 128: 51 blocks 113.5 -> 115.3 us (row splits fill one round of
+//                waves), 61 152.8 -> 143.7 (two rounds), 139 322 -> 284;
+//   fp8,  d 64:  12 blocks 22.6 -> 22.5 us, 22 33.5 -> 30.9, 139 158 -> 140;
+//   f32:         21 blocks 121.8 -> 123.3 us, 26 146.6 -> 144.5, 51 376 -> 354.
+int range_min_blocks(int dtype, int head_dim) {
+  if (dtype == MPA_F32) return 24;
+  if (dtype == MPA_FP8) return head_dim == 128 ? 60 : 12;
+  return head_dim == 128 ? 24 : 10;
+}
+
+// One decode launch: rows [c0, c1) of Batch::decode.
+struct DecodeLaunch {
+  size_t c0 = 0, c1 = 0;
+  int range_blocks = 0;  // DecodePlan::range_blocks
+  long items = 0;        // parts of its rows
+  bool split = false;    // some row has several parts
 };
 
-int env_int(const char* name) {
-  const char* e = getenv(name);
-  return e ? atoi(e) : -1;
-}
+// A row's parts when its nb blocks begin at block `at` of the launch's.
+long range_parts(long at, long nb, int range) { return (at + nb - 1) / range - at / range + 1; }
 
-PlanMemo& plan_memo(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl) {
-  thread_local PlanMemo m;
-  // an empty batch may come without metadata (check_batch accepts null
-  // arrays when num_seqs is 0): its query_start_loc is {0}
-  static const int32_t kEmptyQsl[1] = {0};
-  if (sh->num_seqs == 0 && !qsl) qsl = kEmptyQsl;
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-  const int32_t key[7] = {sh->num_q_heads, sh->num_kv_heads, sh->head_dim, (int32_t)sh->dtype, dev,
-                          env_int("MPA_SPLIT_TOKENS"), env_int("MPA_PREFILL_SPLITS")};
-  const size_t n = (size_t)sh->num_seqs;
-  if (memcmp(key, m.key, sizeof key) != 0 || m.seq_lens.size() != n || m.qsl.size() != n + 1 ||
-      (n && memcmp(m.seq_lens.data(), seq_lens, n * sizeof(int32_t)) != 0) ||
-      memcmp(m.qsl.data(), qsl, (n + 1) * sizeof(int32_t)) != 0) {
-    memcpy(m.key, key, sizeof key);
-    m.seq_lens.assign(seq_lens, seq_lens + n);
-    m.qsl.assign(qsl, qsl + n + 1);
-    m.split = m.want = 0;
+// The decode launches, with ranges where they pay (`ranges`) or all rows
+// split on their own.  MPA_DECODE_RANGE (blocks; 0: none) overrides the
+// choice of ranges for tuning sweeps and tests; MPA_SPLIT_TOKENS asks for row
+// splits.
+std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, int split,
+                                        bool ranges) {
+  std::vector<DecodeLaunch> out;
+  const char* env = getenv("MPA_DECODE_RANGE");
+  const int forced = env ? atoi(env) : getenv("MPA_SPLIT_TOKENS") ? 0 : -1;
+  const long slots = ranges && forced != 0 ? mpa::decode_wave_slots(sh->dtype, sh->head_dim, true) : 0;
+  for (size_t c0 = 0; c0 < b.decode.size(); c0 += mpa::kMaxPlanSeqs) {
+    DecodeLaunch d;
+    d.c0 = c0;
+    d.c1 = std::min(b.decode.size(), c0 + mpa::kMaxPlanSeqs);
+    long blocks = 0;
+    for (size_t k = d.c0; k < d.c1; ++k) blocks += row_blocks(seq_lens[b.decode[k]]);
+    if (ranges && blocks < (1L << 30)) {  // block counts are 32 bits in the plan
+      const long per_head = std::max(1L, slots / sh->num_kv_heads);
+      const long range = (blocks + per_head - 1) / per_head;
+      if (forced > 0)
+        d.range_blocks = forced;
+      else if (slots > 0 && range >= range_min_blocks(sh->dtype, sh->head_dim))
+        d.range_blocks = (int)range;
+    }
+    long at = 0;
+    for (size_t k = d.c0; k < d.c1; ++k) {
+      const int L = seq_lens[b.decode[k]];
+      const long parts =
+          d.range_blocks ? range_parts(at, row_blocks(L), d.range_blocks) : (long)row_split(L, split).parts;
+      at += row_blocks(L);
+      d.items += parts;
+      d.split |= parts > 1;
+    }
+    out.push_back(d);
   }
-  return m;
-}
-
-int choose_split(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, const int32_t* qsl) {
-  PlanMemo& m = plan_memo(sh, seq_lens, qsl);
-  if (m.split == 0) m.split = choose_split_uncached(sh, b, seq_lens);
-  return m.split;
-}
-
-long decode_items(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, int split) {
-  (void)sh;
-  long n = 0;
-  for (int s : b.decode) n += row_split(seq_lens[s], split).parts;
-  return n;
+  return out;
 }
 
 // Query tokens per prefill tile: 256 (token, head) rows for the MFMA kernel
@@ -340,19 +360,17 @@ std::vector<PrefillSplit> prefill_splits(const mpa_shape* sh, const Batch& b, co
   long units;
   int most;  // the most splits any chunk can take
   prefill_units(sh, b.prefill, seq_lens, qsl, &units, &most);
-  PlanMemo& m = plan_memo(sh, seq_lens, qsl);
-  if (m.want == 0) {
-    double best_t = -1.0;
-    for (int want = 1; want <= most && (want == 1 || units * want <= 8L * mpa::kPrefillSplitTarget); ++want) {
-      const double t = prefill_time(sh, b, seq_lens, qsl, split_layout(b, seq_lens, qsl, want, 0), kPlanWgUs,
-                                    kPlanTileUs, mpa::kPrefillSplitTarget, kPlanMergeUs, kPlanMergeRowUs);
-      if (best_t < 0 || t < best_t * (1.0 - 1e-9)) {
-        best_t = t;
-        m.want = want;
-      }
+  double best_t = -1.0;
+  int best = 1;
+  for (int want = 1; want <= most && (want == 1 || units * want <= 8L * mpa::kPrefillSplitTarget); ++want) {
+    const double t = prefill_time(sh, b, seq_lens, qsl, split_layout(b, seq_lens, qsl, want, 0), kPlanWgUs,
+                                  kPlanTileUs, mpa::kPrefillSplitTarget, kPlanMergeUs, kPlanMergeRowUs);
+    if (best_t < 0 || t < best_t * (1.0 - 1e-9)) {
+      best_t = t;
+      best = want;
     }
   }
-  return split_layout(b, seq_lens, qsl, m.want, first_item);
+  return split_layout(b, seq_lens, qsl, best, first_item);
 }
 
 long prefill_items(const std::vector<PrefillSplit>& sp, const Batch& b, const int32_t* qsl) {
@@ -360,6 +378,95 @@ long prefill_items(const std::vector<PrefillSplit>& sp, const Batch& b, const in
   for (size_t k = 0; k < sp.size(); ++k)
     if (sp[k].nsplit > 1) n += (long)sp[k].nsplit * (qsl[b.prefill[k] + 1] - qsl[b.prefill[k]]);
   return n;
+}
+
+// Everything a step's launches follow from.  The partial results of split
+// decode rows come first in the workspace, those of split chunks after them.
+struct StepPlan {
+  Batch batch;
+  int split = 0;  // nominal tokens per part of rows split on their own
+  std::vector<DecodeLaunch> decode;
+  std::vector<PrefillSplit> prefill;  // of batch.prefill
+  long items = 0;                     // workspace slots
+  bool decode_split = false, prefill_split = false;  // some row / chunk has several parts
+};
+
+StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl) {
+  StepPlan p;
+  p.batch = classify(sh, seq_lens, qsl);
+  auto total = [](const std::vector<DecodeLaunch>& v) {
+    long n = 0;
+    for (const auto& d : v) n += d.items;
+    return n;
+  };
+  p.decode = decode_layout(sh, p.batch, seq_lens, 1024, true);
+  bool all_ranges = true;
+  for (const auto& d : p.decode) all_ranges &= d.range_blocks > 0;
+  if (!all_ranges) {
+    p.split = choose_split(sh, p.batch, seq_lens);
+    p.decode = decode_layout(sh, p.batch, seq_lens, p.split, true);
+  }
+  long ditems = total(p.decode);
+  p.prefill = prefill_splits(sh, p.batch, seq_lens, qsl, ditems);
+  p.items = ditems + prefill_items(p.prefill, p.batch, qsl);
+  if (workspace_bytes(sh, p.items) > MPA_SCRATCH_BYTES && !getenv("MPA_DECODE_RANGE")) {
+    // Ranges cut every row, also short ones, so their partial results can
+    // take more room than those of row splits.  A step past the fixed array
+    // of mpa_append_attention_noalloc takes the smaller of the two.
+    const int split = choose_split(sh, p.batch, seq_lens);
+    const std::vector<DecodeLaunch> rows = decode_layout(sh, p.batch, seq_lens, split, false);
+    if (total(rows) < ditems) {
+      p.split = split;
+      p.decode = rows;
+      ditems = total(rows);
+      p.prefill = prefill_splits(sh, p.batch, seq_lens, qsl, ditems);
+      p.items = ditems + prefill_items(p.prefill, p.batch, qsl);
+    }
+  }
+  if (p.split == 0 && !p.decode.empty()) p.split = p.decode[0].range_blocks * kBlock;
+  if (p.split == 0) p.split = 1024;
+  for (const auto& d : p.decode) p.decode_split |= d.split;
+  for (const auto& c : p.prefill) p.prefill_split |= c.nsplit > 1;
+  return p;
+}
+
+int env_int(const char* name) {
+  const char* e = getenv(name);
+  return e ? atoi(e) : -1;
+}
+
+// The plan of a valid batch, from a per-thread memo of the last one: one step
+// asks for its plan several times (workspace sizing, the append, each
+// attention half, the step model).  The key is everything the plan depends
+// on: the shape's heads, head_dim and dtype, the exact seq_lens and
+// query_start_loc, the device (its wave capacity) and the tuning overrides
+// in the environment.  The reference holds until the thread's next call.
+const StepPlan& step_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl) {
+  struct Memo {
+    int32_t key[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
+    std::vector<int32_t> seq_lens, qsl;
+    StepPlan plan;
+  };
+  thread_local Memo m;
+  // an empty batch may come without metadata (check_batch accepts null
+  // arrays when num_seqs is 0): its query_start_loc is {0}
+  static const int32_t kEmptyQsl[1] = {0};
+  if (sh->num_seqs == 0 && !qsl) qsl = kEmptyQsl;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+  const int32_t key[8] = {sh->num_q_heads, sh->num_kv_heads, sh->head_dim, (int32_t)sh->dtype, dev,
+                          env_int("MPA_SPLIT_TOKENS"), env_int("MPA_PREFILL_SPLITS"), env_int("MPA_DECODE_RANGE")};
+  const size_t n = (size_t)sh->num_seqs;
+  if (memcmp(key, m.key, sizeof key) != 0 || m.seq_lens.size() != n || m.qsl.size() != n + 1 ||
+      (n && memcmp(m.seq_lens.data(), seq_lens, n * sizeof(int32_t)) != 0) ||
+      memcmp(m.qsl.data(), qsl, (n + 1) * sizeof(int32_t)) != 0) {
+    m.key[0] = -1;  // no plan while it is made
+    m.seq_lens.assign(seq_lens, seq_lens + n);
+    m.qsl.assign(qsl, qsl + n + 1);
+    m.plan = make_plan(sh, seq_lens, qsl);
+    memcpy(m.key, key, sizeof key);
+  }
+  return m.plan;
 }
 
 // MPA_DEBUG=1 (read per call): before an append, the cache slots it writes
@@ -398,8 +505,7 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
                const int32_t* block_tables, const int32_t* seq_lens, const int32_t* query_start_loc,
                const int32_t* seq_lens_host, const int32_t* query_start_loc_host, const int32_t* block_tables_host,
                const mpa::RopeArgs* rope, void* stream, bool multi_only = false) {
-  Batch b;
-  int rc = check_batch(shape, seq_lens_host, query_start_loc_host, block_tables_host, true, &b);
+  int rc = check_batch(shape, seq_lens_host, query_start_loc_host, block_tables_host, true);
   if (rc != MPA_OK) return rc;
   if (shape->total_q_tokens == 0) return MPA_OK;
   if (debug_checks()) {
@@ -421,6 +527,7 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
   a.inv_v_scale = shape->dtype == MPA_FP8 ? 1.f / shape->v_scale : 1.f;
   (void)seq_lens;
   (void)query_start_loc;
+  const Batch b = classify(shape, seq_lens_host, query_start_loc_host);
   // single-token sequences one wave per token; with the rotary embedding
   // (which also rotates q, token by token) every sequence
   std::vector<int> seqs(b.decode);
@@ -479,9 +586,19 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
 
 namespace {
 
+// The rate of a decode launch whose rows are dealt as ranges, over that of
+// row splits (mpa_rates::decode_gbs): 6,420-6,710 GB/s on the agentic, lent,
+// budget and longctx steps against the 5,880 fitted to row splits.
+constexpr double kRangeSpeed = 1.105;
+// A launch of ranges has one workgroup for every CU.  On three quarters of
+// the CUs a second round runs the last quarter of them by themselves (the
+// 4,096-token budget steps took 1,408-1,421 us in this mode).
+constexpr double kRangeSpeedQ3 = 0.8;
+
 // The step-time model (mpa_predict_step), shared with the mode planner.
-mpa_step_time model_step(const mpa_shape* shape, const Batch& b, const int32_t* seq_lens_host,
+mpa_step_time model_step(const mpa_shape* shape, const StepPlan& plan, const int32_t* seq_lens_host,
                          const int32_t* qsl_host, const mpa_rates& r) {
+  const Batch& b = plan.batch;
   const double elem = 2.0;  // bf16
   const double row_bytes = (double)shape->num_kv_heads * shape->head_dim * elem;  // one token's K (or V)
   mpa_step_time t = {0.0, 0.0, 0.0, 0.0};
@@ -500,27 +617,23 @@ mpa_step_time model_step(const mpa_shape* shape, const Batch& b, const int32_t* 
   }
 
   // decode, launch by launch as run_attention issues them
-  const int split = choose_split(shape, b, seq_lens_host, qsl_host);
   const double head_bytes = 2.0 * shape->head_dim * elem;  // K + V of one token and KV head
-  for (size_t c0 = 0; c0 < b.decode.size(); c0 += mpa::kMaxPlanSeqs) {
-    const size_t c1 = std::min(b.decode.size(), c0 + mpa::kMaxPlanSeqs);
+  for (const DecodeLaunch& d : plan.decode) {
     double bytes = 0.0, wave = 0.0;
-    bool split_any = false;
-    for (size_t k = c0; k < c1; ++k) {
+    for (size_t k = d.c0; k < d.c1; ++k) {
       const int L = seq_lens_host[b.decode[k]];
       bytes += (double)L * head_bytes * shape->num_kv_heads;
-      wave = std::max(wave, (double)std::min(L, row_split(L, split).tokens) * head_bytes);
-      split_any |= row_split(L, split).parts > 1;
+      if (!d.range_blocks) wave = std::max(wave, (double)std::min(L, row_split(L, plan.split).tokens) * head_bytes);
     }
-    t.decode_us += r.decode_fixed_us + std::max(bytes / (r.decode_gbs * 1e3), wave / (r.decode_wave_gbs * 1e3));
-    if (split_any) t.decode_us += r.merge_us;
+    if (d.range_blocks) wave = (double)d.range_blocks * kBlock * head_bytes;
+    const double gbs = r.decode_gbs * (d.range_blocks ? kRangeSpeed : 1.0);
+    t.decode_us += r.decode_fixed_us + std::max(bytes / (gbs * 1e3), wave / (r.decode_wave_gbs * 1e3));
+    if (d.split) t.decode_us += r.merge_us;
   }
 
   // prefill: each launch's workgroups, in launch order (longest query tiles
   // first), on prefill_slots slots that take the next workgroup when free
-  const std::vector<PrefillSplit> psplit =
-      prefill_splits(shape, b, seq_lens_host, qsl_host, decode_items(shape, b, seq_lens_host, split));
-  t.prefill_us = prefill_time(shape, b, seq_lens_host, qsl_host, psplit, r.prefill_wg_us, r.prefill_tile_us,
+  t.prefill_us = prefill_time(shape, b, seq_lens_host, qsl_host, plan.prefill, r.prefill_wg_us, r.prefill_tile_us,
                               r.prefill_slots, r.prefill_merge_us, r.prefill_merge_row_us);
   bool few = false;
   for (int s : b.prefill) few |= seq_lens_host[s] - (qsl_host[s + 1] - qsl_host[s]) < mpa::kFewKeys;
@@ -530,8 +643,8 @@ mpa_step_time model_step(const mpa_shape* shape, const Batch& b, const int32_t* 
 }
 
 int check_model_inputs(const mpa_shape* shape, const int32_t* seq_lens_host, const int32_t* qsl_host,
-                       const mpa_rates& r, Batch* b) {
-  int rc = check_batch(shape, seq_lens_host, qsl_host, nullptr, false, b);
+                       const mpa_rates& r) {
+  int rc = check_batch(shape, seq_lens_host, qsl_host, nullptr, false);
   if (rc != MPA_OK) return rc;
   if (shape->dtype != MPA_BF16) return MPA_ERR_UNSUPPORTED;
   if (!(r.append_gbs > 0) || !(r.append_block_gbs > 0) || !(r.decode_gbs > 0) || !(r.decode_wave_gbs > 0) ||
@@ -559,18 +672,20 @@ const char* mpa_status_string(int status) {
 int mpa_get_plan_info(const mpa_shape* shape, const int32_t* seq_lens_host, const int32_t* qsl_host,
                       mpa_plan_info* info) {
   if (!info) return MPA_ERR_INVALID;
-  Batch b;
-  int rc = check_batch(shape, seq_lens_host, qsl_host, nullptr, false, &b);
+  int rc = check_batch(shape, seq_lens_host, qsl_host, nullptr, false);
   if (rc != MPA_OK) return rc;
-  const int split = choose_split(shape, b, seq_lens_host, qsl_host);
+  const StepPlan& plan = step_plan(shape, seq_lens_host, qsl_host);
+  const Batch& b = plan.batch;
   info->num_decode_seqs = (int32_t)b.decode.size();
   info->num_prefill_seqs = (int32_t)b.prefill.size();
-  info->split_tokens = split;
-  info->num_decode_items = (int32_t)decode_items(shape, b, seq_lens_host, split);
+  // the nominal part size: that of the first launch's ranges, if it has them
+  const bool ranged = !plan.decode.empty() && plan.decode[0].range_blocks > 0;
+  info->split_tokens = ranged ? plan.decode[0].range_blocks * kBlock : plan.split;
+  info->num_decode_items = 0;
+  for (const auto& d : plan.decode) info->num_decode_items += (int32_t)d.items;
   long tiles = 0;
   const int qt = q_tile(shape);
-  const std::vector<PrefillSplit> ps =
-      prefill_splits(shape, b, seq_lens_host, qsl_host, decode_items(shape, b, seq_lens_host, split));
+  const std::vector<PrefillSplit>& ps = plan.prefill;
   int max_split = b.prefill.empty() ? 0 : 1;
   for (size_t k = 0; k < b.prefill.size(); ++k) {
     const int s = b.prefill[k];
@@ -579,7 +694,7 @@ int mpa_get_plan_info(const mpa_shape* shape, const int32_t* seq_lens_host, cons
   }
   info->num_prefill_tiles = (int32_t)(tiles * shape->num_kv_heads);
   info->prefill_max_splits = max_split;
-  info->decode_launches = (int32_t)((b.decode.size() + mpa::kMaxPlanSeqs - 1) / mpa::kMaxPlanSeqs);
+  info->decode_launches = (int32_t)plan.decode.size();
   return MPA_OK;
 }
 
@@ -645,10 +760,9 @@ int mpa_predict_step(const mpa_shape* shape, const int32_t* seq_lens_host, const
   mpa_rates def;
   mpa_default_rates(&def);
   const mpa_rates& r = rates ? *rates : def;
-  Batch b;
-  int rc = check_model_inputs(shape, seq_lens_host, qsl_host, r, &b);
+  int rc = check_model_inputs(shape, seq_lens_host, qsl_host, r);
   if (rc != MPA_OK) return rc;
-  *out = model_step(shape, b, seq_lens_host, qsl_host, r);
+  *out = model_step(shape, step_plan(shape, seq_lens_host, qsl_host), seq_lens_host, qsl_host, r);
   return MPA_OK;
 }
 
@@ -658,16 +772,19 @@ int mpa_plan_coexec(const mpa_shape* shape, const int32_t* seq_lens_host, const 
   mpa_rates def;
   mpa_default_rates(&def);
   const mpa_rates& r = rates ? *rates : def;
-  Batch b;
-  int rc = check_model_inputs(shape, seq_lens_host, qsl_host, r, &b);
+  int rc = check_model_inputs(shape, seq_lens_host, qsl_host, r);
   if (rc != MPA_OK) return rc;
-  const double dfrac[4] = {1.0, r.coexec_decode_q1, r.coexec_decode_q2, r.coexec_decode_q3};
+  double dfrac[4] = {1.0, r.coexec_decode_q1, r.coexec_decode_q2, r.coexec_decode_q3};
   const double pfrac[4] = {1.0, r.coexec_prefill_q3, r.coexec_prefill_q2, r.coexec_prefill_q1};
   if (!(r.coexec_slowdown >= 1.0)) return MPA_ERR_INVALID;
   for (int k = 1; k <= 3; ++k)
     if (!(dfrac[k] > 0) || !(pfrac[k] > 0)) return MPA_ERR_INVALID;
   if (!(r.coexec_fixed_us >= 0.0)) return MPA_ERR_INVALID;
-  const mpa_step_time serial = model_step(shape, b, seq_lens_host, qsl_host, r);
+  const StepPlan& plan = step_plan(shape, seq_lens_host, qsl_host);
+  const Batch& b = plan.batch;
+  for (const auto& d : plan.decode)
+    if (d.range_blocks) dfrac[3] = r.coexec_decode_q3 * kRangeSpeedQ3;
+  const mpa_step_time serial = model_step(shape, plan, seq_lens_host, qsl_host, r);
   double t[4];
   t[0] = serial.decode_us + serial.prefill_us;
   // The prefill half on the (4 - k) / 4 of the CUs: its workgroups' makespan
@@ -675,7 +792,7 @@ int mpa_plan_coexec(const mpa_shape* shape, const int32_t* seq_lens_host, const 
   // batch has few workgroups), times the per-CU speed measured on that share
   // (pfrac against the share itself), and never faster than alone on the
   // whole device.
-  const std::vector<PrefillSplit> ps = prefill_splits(shape, b, seq_lens_host, qsl_host, 0);
+  const std::vector<PrefillSplit>& ps = plan.prefill;
   const double all_slots = prefill_time(shape, b, seq_lens_host, qsl_host, ps, r.prefill_wg_us, r.prefill_tile_us,
                                         r.prefill_slots, 0.0, 0.0);
   for (int k = 1; k <= 3; ++k) {
@@ -733,15 +850,9 @@ int mpa_partition_streams(int32_t mode, void** decode_stream, void** prefill_str
 }
 
 size_t mpa_workspace_size(const mpa_shape* shape, const int32_t* seq_lens_host, const int32_t* qsl_host) {
-  Batch b;
-  if (check_batch(shape, seq_lens_host, qsl_host, nullptr, false, &b) != MPA_OK) return 0;
-  const int split = choose_split(shape, b, seq_lens_host, qsl_host);
-  bool any_split = false;
-  for (int s : b.decode) any_split |= row_split(seq_lens_host[s], split).parts > 1;
-  const long ditems = decode_items(shape, b, seq_lens_host, split);
-  const long pitems = prefill_items(prefill_splits(shape, b, seq_lens_host, qsl_host, ditems), b, qsl_host);
-  if (!any_split && pitems == 0) return 0;
-  return workspace_bytes(shape, ditems + pitems);
+  if (check_batch(shape, seq_lens_host, qsl_host, nullptr, false) != MPA_OK) return 0;
+  const StepPlan& plan = step_plan(shape, seq_lens_host, qsl_host);
+  return plan.decode_split || plan.prefill_split ? workspace_bytes(shape, plan.items) : 0;
 }
 
 int mpa_kv_append(const mpa_shape* shape, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
@@ -785,29 +896,19 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
                   const int32_t* block_tables_host, void* out, float* lse, void* workspace,
                   size_t workspace_bytes_given, void* stream, const void* k_new = nullptr,
                   const void* v_new = nullptr, bool validate_only = false) {
-  Batch b;
-  int rc = check_batch(shape, seq_lens_host, query_start_loc_host, block_tables_host, false, &b);
+  int rc = check_batch(shape, seq_lens_host, query_start_loc_host, block_tables_host, false);
   if (rc != MPA_OK) return rc;
-  if (!(phases & kDecode)) b.decode.clear();
-  if (!(phases & kPrefill)) b.prefill.clear();
-  if (b.decode.empty() && b.prefill.empty()) return MPA_OK;
+  // The plan is the whole batch's, whichever phase runs: the two halves
+  // together equal the mixed call exactly, and their partial results lie in
+  // disjoint parts of the workspace, so they can run concurrently.
+  const StepPlan& plan = step_plan(shape, seq_lens_host, query_start_loc_host);
+  const bool decode = (phases & kDecode) && !plan.batch.decode.empty();
+  const bool prefill = (phases & kPrefill) && !plan.batch.prefill.empty();
+  if (!decode && !prefill) return MPA_OK;
   if (!q || !k_cache || !v_cache || !block_tables || !seq_lens || !query_start_loc || !out)
     return MPA_ERR_INVALID;
-  // The split size depends on every decode row of the batch, whichever
-  // phase runs, so that the phases together equal the mixed call exactly.
-  // The workspace layout (decode partials, then prefill partials) is also
-  // the whole batch's, so the two halves can run concurrently.
-  Batch all;
-  check_batch(shape, seq_lens_host, query_start_loc_host, nullptr, false, &all);
-  const int split = choose_split(shape, all, seq_lens_host, query_start_loc_host);
-  const long ditems = decode_items(shape, all, seq_lens_host, split);
-  const std::vector<PrefillSplit> psplit =
-      prefill_splits(shape, all, seq_lens_host, query_start_loc_host, ditems);
-  const long items = ditems + prefill_items(psplit, all, query_start_loc_host);
-  bool any_split = false;
-  for (int s : b.decode) any_split |= row_split(seq_lens_host[s], split).parts > 1;
-  if (!b.prefill.empty())
-    for (const auto& ps : psplit) any_split |= ps.nsplit > 1;
+  const long items = plan.items;
+  const bool any_split = (decode && plan.decode_split) || (prefill && plan.prefill_split);
   if (any_split) {
     const size_t need = workspace_bytes(shape, items);
     if (!workspace || workspace_bytes_given < need || ((uintptr_t)workspace & 15) != 0) return MPA_ERR_WORKSPACE;
@@ -840,54 +941,53 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
   hipStream_t st = (hipStream_t)stream;
   clear_stale_hip_error();
 
-  // Decode rows, in launches of up to kMaxPlanSeqs sequences.
-  std::vector<mpa::DecodePlan> dplans;
-  {
-    long base = 0;
-    for (size_t c0 = 0; c0 < b.decode.size(); c0 += mpa::kMaxPlanSeqs) {
-      mpa::DecodePlan p;
-      memset(&p, 0, sizeof(p));
-      const size_t c1 = std::min(b.decode.size(), c0 + mpa::kMaxPlanSeqs);
-      p.n_seqs = (int32_t)(c1 - c0);
-      p.item_base = (int32_t)base;
-      int acc = 0;
-      for (size_t k = c0; k < c1; ++k) {
-        const int s = b.decode[k];
-        const RowSplit rs = row_split(seq_lens_host[s], split);
-        p.seq[k - c0] = s;
-        p.split_tokens[k - c0] = rs.tokens;
-        p.item_start[k - c0] = acc;
+  // Decode rows, in launches of up to kMaxPlanSeqs sequences; split rows are
+  // merged after their launch.
+  long base = 0;
+  for (const DecodeLaunch& d : plan.decode) {
+    if (!decode) break;
+    mpa::DecodePlan p;
+    p.n_seqs = (int32_t)(d.c1 - d.c0);
+    p.item_base = (int32_t)base;
+    p.range_blocks = d.range_blocks;
+    int acc = 0, at = 0;
+    for (int k = 0; k < p.n_seqs; ++k) {
+      const int s = plan.batch.decode[d.c0 + k];
+      const int L = seq_lens_host[s];
+      p.seq[k] = s;
+      p.item_start[k] = acc;
+      if (d.range_blocks) {
+        p.part[k] = at;
+        acc += (int)range_parts(at, row_blocks(L), d.range_blocks);
+        at += row_blocks(L);
+      } else {
+        const RowSplit rs = row_split(L, plan.split);
+        p.part[k] = rs.tokens;
         acc += rs.parts;
       }
-      p.item_start[c1 - c0] = acc;
-      base += acc;
-      dplans.push_back(p);
     }
-  }
-  for (const auto& p : dplans) {
-    hipError_t e = mpa::launch_decode(a, p, p.item_start[p.n_seqs], shape->dtype, shape->head_dim, st);
+    p.part[p.n_seqs] = at;
+    p.item_start[p.n_seqs] = acc;
+    base += acc;
+    hipError_t e = mpa::launch_decode(a, p, acc, shape->dtype, shape->head_dim, st);
+    if (e == hipSuccess && d.split) e = mpa::launch_merge(a, p, shape->dtype, shape->head_dim, st);
     if (e != hipSuccess) return MPA_ERR_HIP;
   }
-  if (any_split) {
-    for (const auto& p : dplans) {
-      hipError_t e = mpa::launch_merge(a, p, shape->dtype, shape->head_dim, st);
-      if (e != hipSuccess) return MPA_ERR_HIP;
-    }
-  }
-  // Prefill chunks (b.prefill is all.prefill or empty), in launches of up to
-  // kMaxPrefillSeqs; KV-split chunks are merged after their launch.
+  // Prefill chunks, in launches of up to kMaxPrefillSeqs; KV-split chunks are
+  // merged after their launch.
   const int qt = q_tile(shape);
-  for (size_t c0 = 0; c0 < b.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
+  const std::vector<int>& chunks = plan.batch.prefill;
+  for (size_t c0 = 0; prefill && c0 < chunks.size(); c0 += mpa::kMaxPrefillSeqs) {
     mpa::PrefillPlan p;
     memset(&p, 0, sizeof(p));
-    const size_t c1 = std::min(b.prefill.size(), c0 + mpa::kMaxPrefillSeqs);
+    const size_t c1 = std::min(chunks.size(), c0 + mpa::kMaxPrefillSeqs);
     p.n_seqs = (int32_t)(c1 - c0);
     p.q_tile = qt;
     int acc = 0, rows = 0;
     for (size_t k = c0; k < c1; ++k) {
-      const int s = b.prefill[k];
+      const int s = chunks[k];
       const int C = query_start_loc_host[s + 1] - query_start_loc_host[s];
-      const PrefillSplit& ps = psplit[k];
+      const PrefillSplit& ps = plan.prefill[k];
       p.seq[k - c0] = s;
       p.tile_start[k - c0] = acc;
       p.nsplit[k - c0] = ps.nsplit;

@@ -41,17 +41,21 @@ struct AttnArgs {
   float inv_k_scale, inv_v_scale;  // fp8 caches: 1 / scale, rounded to f32 (1 otherwise)
 };
 
-// Decode work for up to kMaxPlanSeqs sequences: item k of this launch is
-// split x = k - item_start[j] of sequence seq[j], where item_start[j] <= k <
-// item_start[j+1]; it covers keys [x * split_tokens[j], (x + 1) *
-// split_tokens[j]) (a multiple of the block size; the last split ends at the
-// sequence's length).  Its partial results live at workspace slot
-// item_base + k.
+// Decode work for up to kMaxPlanSeqs sequences.  Parts item_start[j] <= k <
+// item_start[j+1] are those of sequence seq[j]; part k's partial results live
+// at workspace slot item_base + k.
+// range_blocks == 0: row j is split on its own, part x covering keys
+// [x * part[j], (x + 1) * part[j]) (a multiple of the block size; the last
+// part ends at the sequence's length), one wave per part and KV head.
+// range_blocks > 0: the rows' cache blocks laid end to end (row j's are
+// part[j] .. part[j+1] - 1) are cut into ranges of range_blocks, one wave per
+// range and KV head; a row's parts are its intersections with the ranges.
 struct DecodePlan {
   int32_t n_seqs;
   int32_t item_base;
+  int32_t range_blocks;
   int32_t seq[kMaxPlanSeqs];
-  int32_t split_tokens[kMaxPlanSeqs];
+  int32_t part[kMaxPlanSeqs + 1];
   int32_t item_start[kMaxPlanSeqs + 1];
 };
 
@@ -129,8 +133,9 @@ hipError_t launch_append_blocks(const AppendArgs& a, const AppendBlockPlan& p, i
                                 hipStream_t stream);
 hipError_t launch_rope_append(const AppendArgs& a, const AppendPlan& p, const RopeArgs& r, int dtype, int head_dim,
                               hipStream_t stream);
-// Decode waves the current device holds at once (2048 without a device).
-int decode_wave_slots(int dtype, int head_dim);
+// Decode waves the current device holds at once, of the kernel that splits
+// each row on its own (2048 without a device) or of the streaming one (0).
+int decode_wave_slots(int dtype, int head_dim, bool stream);
 hipError_t launch_decode(const AttnArgs& a, const DecodePlan& p, int n_items, int dtype, int head_dim,
                          hipStream_t stream);
 hipError_t launch_merge(const AttnArgs& a, const DecodePlan& p, int dtype, int head_dim, hipStream_t stream);

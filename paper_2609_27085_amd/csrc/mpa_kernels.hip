@@ -283,12 +283,15 @@ __device__ inline unsigned f32_to_e4m3(float x) {
 
 // Largest j in [0, n) with starts[j] <= x (starts non-decreasing, starts[0] <= x).
 __device__ inline int upper_index(const int32_t* starts, int n, int x) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (starts[mid] <= x) lo = mid; else hi = mid - 1;
+  // One load per 64 entries and a ballot, instead of a chain of dependent
+  // scalar loads.
+  const int lane = threadIdx.x & 63;
+  int j = 0;
+  for (int c = 0; c < n; c += 64) {
+    const bool in = c + lane < n && starts[min(c + lane, n - 1)] <= x;
+    j += __popcll(__ballot(in));
   }
-  return lo;
+  return j - 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -338,11 +341,13 @@ __device__ inline void load_block(const AttnArgs& a, int blk, int g, BlockFrags<
 // accumulators are rescaled on a few blocks only.  The quotient O / l at the
 // end is the same for any m; the block that sets m has its maximum at
 // exactly 2^0 = 1, so a single key returns its value row unchanged.
-// `edge` (wave-uniform) marks a block with keys past kend or past some row's
-// causal limit; only then are scores masked and V rows of keys >= kend zeroed.
-template <int DT, int D>
+// EDGE: the block may hold keys past kend or past some row's causal limit
+// (its scores are masked and V rows of keys >= kend zeroed), or belong to
+// rows of at most kFewKeys keys.  The plain form has neither, so the loop
+// over a row's whole blocks carries no copies of the accumulators for them.
+template <int DT, int D, bool EDGE>
 __device__ inline void consume_block(const AttnArgs& a, const typename Tr<DT>::Chunk* qf, const BlockFrags<DT, D>& f,
-                                     int kb, int kend, int limit, bool edge, bool few_keys, RowState<DT, D>& st) {
+                                     int kb, int kend, int limit, bool few_keys, RowState<DT, D>& st) {
   using T = Tr<DT>;
   constexpr int R = D / (4 * T::X);
   constexpr int MT = D / 16;
@@ -352,7 +357,7 @@ __device__ inline void consume_block(const AttnArgs& a, const typename Tr<DT>::C
   for (int r = 0; r < R; ++r) s = T::qk(f.k[r], qf[r], s);
   s *= a.scale_log2;
   const int key0 = kb * kBlock + 4 * grp;
-  if (edge) {
+  if constexpr (EDGE) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (!(key0 + i <= limit && key0 + i < kend)) s[i] = -INFINITY;
@@ -375,6 +380,12 @@ __device__ inline void consume_block(const AttnArgs& a, const typename Tr<DT>::C
   for (int i = 0; i < 4; ++i) p[i] = exp2_fast(s[i] - m);
   const auto pf = T::make_p(p);
   st.l = T::psum(p, pf, st.l);
+  if constexpr (!EDGE) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) st.acc[mt] = T::pv(f.v[mt], pf, st.acc[mt]);
+    return;
+  }
+  const int nvalid = kend - key0;
   if constexpr (T::kRoundsP) {
     if (few_keys) {
       // rows of at most kFewKeys keys: few probabilities carry each output,
@@ -382,7 +393,6 @@ __device__ inline void consume_block(const AttnArgs& a, const typename Tr<DT>::C
       // goes through a second PV product
       const auto plo = T::make_p_lo(p, pf);
       st.l = T::psum(p, plo, st.l);
-      const int nvalid = edge ? kend - key0 : kBlock;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const auto v = T::keep_first(f.v[mt], nvalid);
@@ -391,13 +401,59 @@ __device__ inline void consume_block(const AttnArgs& a, const typename Tr<DT>::C
       return;
     }
   }
-  if (edge) {
-    const int nvalid = kend - key0;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) st.acc[mt] = T::pv(T::keep_first(f.v[mt], nvalid), pf, st.acc[mt]);
-  } else {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) st.acc[mt] = T::pv(f.v[mt], pf, st.acc[mt]);
+  for (int mt = 0; mt < MT; ++mt) st.acc[mt] = T::pv(T::keep_first(f.v[mt], nvalid), pf, st.acc[mt]);
+}
+
+// The block ids of a run of cache blocks: 64 consecutive block-table entries
+// per coalesced load, one per lane, broadcast with readlane.  The next 64
+// are loaded when a group is begun, so that the loads of the blocks never
+// wait for their ids.  Blocks are asked for in order (a block at or past
+// kb_end, asked for by a prefetch, is the last one).
+struct BlockIds {
+  const int32_t* bt;
+  int base, last, nb;
+  int cur, nxt;
+  bool poison;  // an id was out of range (block 0 is read in its place)
+  __device__ inline BlockIds(const int32_t* table, int kb_begin, int kb_end, int num_blocks)
+      : bt(table), base(kb_begin), last(kb_end - 1), nb(num_blocks), poison(false) {
+    cur = fetch(base);
+    nxt = fetch(base + 64);
+  }
+  __device__ inline int fetch(int kb) const {
+    const int k = kb + (int)(threadIdx.x & 63);
+    return k <= last ? bt[k] : 0;
+  }
+  __device__ inline int operator()(int kb) {
+    kb = min(kb, last);
+    if (kb - base >= 64) {
+      base += 64;
+      cur = nxt;
+      nxt = fetch(base + 64);
+    }
+    int blk = __builtin_amdgcn_readlane(cur, kb - base);
+    if (blk < 0 || blk >= nb) {
+      poison = true;
+      blk = 0;
+    }
+    return blk;
+  }
+};
+
+// Blocks between two workgroup barriers of a streaming decode workgroup.
+constexpr int kLockstepBlocks = 4;
+
+// Keeps the waves of a streaming decode workgroup within kLockstepBlocks
+// blocks of each other: `step` counts this wave's blocks since its last
+// barrier.  The memory system serves the waves of a SIMD by age, so left
+// alone the oldest finish early and the last ones stream by themselves at a
+// falling rate.  Waves that have ended no longer count at s_barrier, so the
+// waves of a workgroup may have different numbers of blocks.
+__device__ inline void lockstep(int& step, int blocks) {
+  step += blocks;
+  if (step >= kLockstepBlocks) {
+    step = 0;
+    __builtin_amdgcn_s_barrier();
   }
 }
 
@@ -406,40 +462,45 @@ __device__ inline void consume_block(const AttnArgs& a, const typename Tr<DT>::C
 // are requested before the current one is consumed (the request is pinned in
 // place with a scheduling barrier, and is issued unconditionally -- the last
 // block is requested twice -- so consuming a block waits only for its own
-// loads).  One block deep keeps the decode kernel at 3 waves per SIMD; two
-// deep costs a wave per SIMD and measured slower.  Block ids come from a
-// coalesced load of up to 64 consecutive block-table entries, one per lane,
-// broadcast with readlane.
-template <int DT, int D>
+// loads).  The blocks that every row sees whole come first, the others
+// (kb_edge on: the last block, a causal diagonal, rows of few keys) last.
+template <int DT, int D, bool STREAM>
 __device__ inline void attend_blocks(const AttnArgs& a, const typename Tr<DT>::Chunk* qf,
                                      const int32_t* bt, int g, int kb_begin, int kb_end, int kend,
-                                     int limit, int min_limit, RowState<DT, D>& st, bool& poison) {
-  const int lane = threadIdx.x & 63;
+                                     int limit, int min_limit, RowState<DT, D>& st, bool& poison, int& step) {
   const bool few_keys = kend <= kFewKeys;  // every row sees at most kFewKeys keys
-  for (int c0 = kb_begin; c0 < kb_end; c0 += 64) {
-    const int c1 = min(kb_end, c0 + 64);
-    const int ids = c0 + lane < c1 ? bt[c0 + lane] : 0;
-    auto block_id = [&](int kb) -> int {
-      int blk = __builtin_amdgcn_readlane(ids, min(kb, c1 - 1) - c0);
-      if (blk < 0 || blk >= a.nb) {
-        poison = true;
-        blk = 0;
-      }
-      return blk;
-    };
-    auto is_edge = [&](int kb) { return kb * kBlock + kBlock > kend || kb * kBlock + kBlock - 1 > min_limit; };
-    BlockFrags<DT, D> fa, fb;
-    load_block<DT, D>(a, block_id(c0), g, fa);
-    for (int kb = c0; kb < c1; kb += 2) {
-      load_block<DT, D>(a, block_id(kb + 1), g, fb);
-      __builtin_amdgcn_sched_barrier(0);
-      consume_block<DT, D>(a, qf, fa, kb, kend, limit, is_edge(kb), few_keys, st);
-      if (kb + 1 >= c1) break;
-      load_block<DT, D>(a, block_id(kb + 2), g, fa);
-      __builtin_amdgcn_sched_barrier(0);
-      consume_block<DT, D>(a, qf, fb, kb + 1, kend, limit, is_edge(kb + 1), few_keys, st);
-    }
+  const int whole = min_limit < kend ? min_limit + 1 : kend;  // keys that every row sees
+  const int kb_edge = few_keys ? kb_begin : max(kb_begin, whole / kBlock);
+  if (kb_begin >= kb_end) return;
+  BlockIds id(bt, kb_begin, kb_end, a.nb);
+  BlockFrags<DT, D> fa, fb;
+  load_block<DT, D>(a, id(kb_begin), g, fa);
+  int kb = kb_begin;
+  for (; kb + 2 <= kb_edge; kb += 2) {
+    load_block<DT, D>(a, id(kb + 1), g, fb);
+    __builtin_amdgcn_sched_barrier(0);
+    consume_block<DT, D, false>(a, qf, fa, kb, kend, limit, false, st);
+    load_block<DT, D>(a, id(kb + 2), g, fa);
+    __builtin_amdgcn_sched_barrier(0);
+    consume_block<DT, D, false>(a, qf, fb, kb + 1, kend, limit, false, st);
+    if constexpr (STREAM) lockstep(step, 2);
   }
+  if (kb < kb_edge) {
+    load_block<DT, D>(a, id(kb + 1), g, fb);
+    __builtin_amdgcn_sched_barrier(0);
+    consume_block<DT, D, false>(a, qf, fa, kb, kend, limit, false, st);
+    if constexpr (STREAM) lockstep(step, 1);
+    fa = fb;
+    ++kb;
+  }
+  for (; kb < kb_end; ++kb) {
+    load_block<DT, D>(a, id(kb + 1), g, fb);
+    __builtin_amdgcn_sched_barrier(0);
+    consume_block<DT, D, true>(a, qf, fa, kb, kend, limit, few_keys, st);
+    if constexpr (STREAM) lockstep(step, 1);
+    fa = fb;
+  }
+  poison |= id.poison;
 }
 
 // attend_blocks for fp8 caches.  A block's K and V granules of one head are
@@ -452,7 +513,8 @@ __device__ inline void attend_blocks(const AttnArgs& a, const typename Tr<DT>::C
 // operand layout (conflict-free: a wave's K read covers 512 contiguous
 // bytes, its V read 256).  `ring` is the wave's 3 * 2 * 16 * D bytes of LDS.
 // The copies are counted in vmcnt only (the compiler does not see them), so
-// the waits are explicit; the loop issues no other vector-memory operation.
+// the waits are explicit; the only other vector-memory operation of the loop
+// is a load of 64 block ids every 64 blocks, which makes the waits stricter.
 template <int D>
 __device__ inline void attend_blocks_fp8_lds(const AttnArgs& a, const bf16x8* qf, const int32_t* bt, int g,
                                              int kb_begin, int kb_end, int kend, int limit, int min_limit,
@@ -467,49 +529,50 @@ __device__ inline void attend_blocks_fp8_lds(const AttnArgs& a, const bf16x8* qf
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, grp = lane >> 4;
   const bool few_keys = kend <= kFewKeys;
-  for (int c0 = kb_begin; c0 < kb_end; c0 += 64) {
-    const int c1 = min(kb_end, c0 + 64);
-    const int ids = c0 + lane < c1 ? bt[c0 + lane] : 0;
-    auto block_id = [&](int kb) -> int {
-      int blk = __builtin_amdgcn_readlane(ids, min(kb, c1 - 1) - c0);
-      if (blk < 0 || blk >= a.nb) {
-        poison = true;
-        blk = 0;
-      }
-      return blk;
-    };
-    auto copy = [&](int kb, int slot) {
-      const size_t gran = ((size_t)block_id(kb) * a.hkv + g) * GB;
-      const uint8_t* kp = reinterpret_cast<const uint8_t*>(a.k_cache) + gran;
-      const uint8_t* vp = reinterpret_cast<const uint8_t*>(a.v_cache) + gran;
+  const int whole = min_limit < kend ? min_limit + 1 : kend;
+  const int kb_edge = few_keys ? kb_begin : max(kb_begin, whole / kBlock);
+  if (kb_begin >= kb_end) return;
+  BlockIds id(bt, kb_begin, kb_end, a.nb);
+  auto copy = [&](int kb, int slot) {
+    const size_t gran = ((size_t)id(kb) * a.hkv + g) * GB;
+    const uint8_t* kp = reinterpret_cast<const uint8_t*>(a.k_cache) + gran;
+    const uint8_t* vp = reinterpret_cast<const uint8_t*>(a.v_cache) + gran;
 #pragma unroll
-      for (int u = 0; u < NI; ++u) {
-        global_to_lds16_nt(kp, (unsigned)(u * 1024 + lane * 16), ring + slot * SLOT + u * 1024);
-        global_to_lds16_nt(vp, (unsigned)(u * 1024 + lane * 16), ring + slot * SLOT + GB + u * 1024);
-      }
-    };
-    copy(c0, 0);
-    copy(c0 + 1, 1);  // past the chunk's last block: that block again (unused)
-    int slot = 0;
-    for (int kb = c0; kb < c1; ++kb) {
-      copy(kb + 2, slot == 0 ? 2 : slot - 1);
-      MPA_WAIT_VMCNT(4 * NI);  // the copies of blocks kb+1 and kb+2 may still be in flight
-      const uint8_t* sp = ring + slot * SLOT;
-      BlockFrags<2, D> f;
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-        f.k[r] = T::k_from_codes(*reinterpret_cast<const u32x2*>(sp + ((4 * r + grp) * kBlock + n) * T::X));
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        f.v[mt] = T::v_from_codes(*reinterpret_cast<const unsigned*>(sp + GB + (16 * mt + n) * kBlock + 4 * grp));
-      const bool edge = kb * kBlock + kBlock > kend || kb * kBlock + kBlock - 1 > min_limit;
-      consume_block<2, D>(a, qf, f, kb, kend, limit, edge, few_keys, st);
-      slot = slot == 2 ? 0 : slot + 1;
+    for (int u = 0; u < NI; ++u) {
+      global_to_lds16_nt(kp, (unsigned)(u * 1024 + lane * 16), ring + slot * SLOT + u * 1024);
+      global_to_lds16_nt(vp, (unsigned)(u * 1024 + lane * 16), ring + slot * SLOT + GB + u * 1024);
     }
-    // The ring is reused by the next group of blocks (and the wave's LDS is
-    // released when it ends): no copy may still be writing it.
-    MPA_WAIT_VMCNT(0);
+  };
+  int slot = 0;
+  BlockFrags<2, D> f;
+  // requests block kb + 2, waits for block kb and reads it
+  auto next = [&](int kb) {
+    copy(kb + 2, slot == 0 ? 2 : slot - 1);
+    MPA_WAIT_VMCNT(4 * NI);  // the copies of blocks kb+1 and kb+2 may still be in flight
+    const uint8_t* sp = ring + slot * SLOT;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      f.k[r] = T::k_from_codes(*reinterpret_cast<const u32x2*>(sp + ((4 * r + grp) * kBlock + n) * T::X));
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      f.v[mt] = T::v_from_codes(*reinterpret_cast<const unsigned*>(sp + GB + (16 * mt + n) * kBlock + 4 * grp));
+    slot = slot == 2 ? 0 : slot + 1;
+  };
+  copy(kb_begin, 0);
+  copy(kb_begin + 1, 1);  // past the last block: that block again (unused)
+  int kb = kb_begin;
+  for (; kb < kb_edge; ++kb) {
+    next(kb);
+    consume_block<2, D, false>(a, qf, f, kb, kend, limit, false, st);
   }
+  for (; kb < kb_end; ++kb) {
+    next(kb);
+    consume_block<2, D, true>(a, qf, f, kb, kend, limit, few_keys, st);
+  }
+  // The ring is reused by the next run of blocks (and the wave's LDS is
+  // released when it ends): no copy may still be writing it.
+  MPA_WAIT_VMCNT(0);
+  poison |= id.poison;
 }
 
 template <int D>
@@ -522,11 +585,10 @@ __device__ inline void store_fp8_chunk(const AppendArgs& a, size_t head, int c, 
 // then waits for its stores before it loads any block.  A bad block id
 // writes nothing (the row comes out NaN).
 template <int DT, int D>
-__device__ inline void append_decode_token(const AttnArgs& a, int s, int pos, int t, int g) {
+__device__ inline void append_decode_token(const AttnArgs& a, int s, int pos, int t, int g, int lane) {
   using T = Tr<DT>;
   using E = typename T::Elem;
   constexpr int X = T::X;
-  const int lane = threadIdx.x & 63;
   const int blk = a.block_tables[(size_t)s * a.mb + pos / kBlock];
   if (blk < 0 || blk >= a.nb) return;
   const int slot = pos % kBlock;
@@ -561,10 +623,24 @@ __device__ inline void append_decode_token(const AttnArgs& a, int s, int pos, in
 }
 
 // ---------------------------------------------------------------------------
-// Decode: one wave per (sequence, split, KV head); the G query heads of the
-// group are the 16 MFMA columns (columns >= G carry zero queries).
-template <int DT, int D>
-__global__ __launch_bounds__(256) void decode_kernel(AttnArgs a, DecodePlan p) {
+// Decode; the G query heads of the group are the 16 MFMA columns (columns
+// >= G carry zero queries).
+// STREAM false: one wave per (sequence, split, KV head).
+// STREAM true: the launch holds one wave per slot of the device, and the
+// wave of a KV head takes a range of p.range_blocks consecutive blocks of
+// all rows laid end to end; it walks the rows its range touches, each a part
+// of that row.  Bound by HBM: a wave that starts costs the latency of its
+// plan, its block ids and its first block with nothing in flight (about 5
+// us), and splits of at most 1,024 tokens start 2 to 6 waves per slot on
+// large batches.  Decode and merge, random contexts, before -> after: 7.9
+// GB (256 rows) 1,375 -> 1,205 us, 10.8 GB (32 rows) 1,767 -> 1,554 us (6.97
+// TB/s; a contiguous read of 2 GiB takes 7.08), fp8 1.46 GB 265 -> 237 us,
+// 64-wide heads 1.6 GB 271 -> 247 us.
+// Decode waves a SIMD holds at the kernels' register use.
+constexpr int decode_waves_per_simd(int dt, int d) { return d == 128 ? (dt == 1 ? 2 : 3) : 4; }
+
+template <int DT, int D, int WPG, bool STREAM>
+__global__ __launch_bounds__(64 * WPG, decode_waves_per_simd(DT, D)) void decode_kernel(AttnArgs a, DecodePlan p) {
   using T = Tr<DT>;
   using QE = typename T::QElem;
   constexpr int X = T::X;
@@ -572,64 +648,88 @@ __global__ __launch_bounds__(256) void decode_kernel(AttnArgs a, DecodePlan p) {
   constexpr int MT = D / 16;
   const int lane = threadIdx.x & 63;
   const int wave = wave_uniform(threadIdx.x >> 6);
-  const int unit = blockIdx.x * kWavesPerGroup + wave;
+  const int unit = blockIdx.x * WPG + wave;
   const int item = unit / a.hkv;
-  if (item >= p.item_start[p.n_seqs]) return;
   const int g = unit - item * a.hkv;
-  const int j = upper_index(p.item_start, p.n_seqs, item);
-  const int s = p.seq[j];
-  const int split = item - p.item_start[j];
-  const int nsplit = p.item_start[j + 1] - p.item_start[j];
-  const int L = a.seq_lens[s];
-  const int k0 = split * p.split_tokens[j];
-  const int k1 = min(L, k0 + p.split_tokens[j]);
-  const int trow = a.qsl[s];
   const int G = a.hq / a.hkv;
-  const int n = lane & 15, grp = lane >> 4;
-  const bool head_ok = n < G;
-  const int h = g * G + (head_ok ? n : 0);
-  if (a.k_new != nullptr && split == nsplit - 1) append_decode_token<DT, D>(a, s, L - 1, trow, g);
-
-  const QE* q = reinterpret_cast<const QE*>(a.q) + ((size_t)trow * a.hq + h) * D;
-  typename T::Chunk qf[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) qf[r] = head_ok ? T::load_q(q + (4 * r + grp) * X) : T::zero_chunk();
-
-  RowState<DT, D> st;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) st.acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  st.m = -INFINITY;
-  st.l = 0.f;
-  bool poison = false;
-  if constexpr (DT == 2) {
-    __shared__ __attribute__((aligned(16))) uint8_t ring[kWavesPerGroup][3 * 2 * kBlock * D];
-    attend_blocks_fp8_lds<D>(a, qf, a.block_tables + (size_t)s * a.mb, g, k0 / kBlock, (k1 + kBlock - 1) / kBlock,
-                             k1, INT32_MAX, INT32_MAX, st, poison, ring[wave]);
+  int j, blk = 0, blk_end = 0;
+  if constexpr (STREAM) {
+    blk = item * p.range_blocks;
+    blk_end = min(blk + p.range_blocks, p.part[p.n_seqs]);
+    if (blk >= blk_end) return;
+    j = upper_index(p.part, p.n_seqs, blk);
   } else {
-    attend_blocks<DT, D>(a, qf, a.block_tables + (size_t)s * a.mb, g, k0 / kBlock, (k1 + kBlock - 1) / kBlock, k1,
-                         INT32_MAX, INT32_MAX, st, poison);
+    if (item >= p.item_start[p.n_seqs]) return;
+    j = upper_index(p.item_start, p.n_seqs, item);
   }
-
-  float l = st.l + __shfl_xor(st.l, 16);
-  l += __shfl_xor(l, 32);
-  if (!head_ok) return;
-  if (nsplit == 1) {
-    const float inv = poison ? NAN : a.v_scale / l;
-    QE* o = reinterpret_cast<QE*>(a.out) + ((size_t)trow * a.hq + h) * D;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) T::store4(o + 16 * mt + 4 * grp, st.acc[mt] * inv);
-    if (a.lse && grp == 0) a.lse[(size_t)trow * a.hq + h] = poison ? NAN : (st.m + log2f(l)) * kLn2;
-  } else {
-    const size_t slot = (size_t)(p.item_base + item) * a.hq + h;
-    float* wo = a.ws_o + slot * D;
-    const float bad = poison ? NAN : 1.f;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      *reinterpret_cast<f32x4*>(wo + 16 * mt + 4 * grp) = st.acc[mt] * (bad * a.v_scale);
-    if (grp == 0) {
-      a.ws_ml[slot * 2] = st.m;
-      a.ws_ml[slot * 2 + 1] = l * bad;
+  int step = 0;
+  for (;; ++j) {
+    int ln = lane;
+    if constexpr (STREAM) asm volatile("" : "+v"(ln));
+    const int n = ln & 15, grp = ln >> 4;
+    const bool head_ok = n < G;
+    const int h = g * G + (head_ok ? n : 0);
+    const int s = p.seq[j];
+    const int nsplit = p.item_start[j + 1] - p.item_start[j];
+    const int L = a.seq_lens[s];
+    int k0, k1, split;
+    if constexpr (STREAM) {
+      const int row0 = p.part[j];
+      split = item - row0 / p.range_blocks;
+      k0 = (blk - row0) * kBlock;
+      blk = min(blk_end, p.part[j + 1]);
+      k1 = min(L, (blk - row0) * kBlock);
+    } else {
+      split = item - p.item_start[j];
+      k0 = split * p.part[j];
+      k1 = min(L, k0 + p.part[j]);
     }
+    const int trow = a.qsl[s];
+    if (a.k_new != nullptr && split == nsplit - 1) append_decode_token<DT, D>(a, s, L - 1, trow, g, ln);
+
+    const QE* q = reinterpret_cast<const QE*>(a.q) + ((size_t)trow * a.hq + h) * D;
+    typename T::Chunk qf[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) qf[r] = head_ok ? T::load_q(q + (4 * r + grp) * X) : T::zero_chunk();
+
+    RowState<DT, D> st;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) st.acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    st.m = -INFINITY;
+    st.l = 0.f;
+    bool poison = false;
+    if constexpr (DT == 2) {
+      __shared__ __attribute__((aligned(16))) uint8_t ring[WPG][3 * 2 * kBlock * D];
+      attend_blocks_fp8_lds<D>(a, qf, a.block_tables + (size_t)s * a.mb, g, k0 / kBlock, (k1 + kBlock - 1) / kBlock,
+                               k1, INT32_MAX, INT32_MAX, st, poison, ring[wave]);
+    } else {
+      attend_blocks<DT, D, STREAM>(a, qf, a.block_tables + (size_t)s * a.mb, g, k0 / kBlock,
+                                   (k1 + kBlock - 1) / kBlock, k1, INT32_MAX, INT32_MAX, st, poison, step);
+    }
+
+    float l = st.l + __shfl_xor(st.l, 16);
+    l += __shfl_xor(l, 32);
+    if (head_ok) {
+      if (nsplit == 1) {
+        const float inv = poison ? NAN : a.v_scale / l;
+        QE* o = reinterpret_cast<QE*>(a.out) + ((size_t)trow * a.hq + h) * D;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) T::store4(o + 16 * mt + 4 * grp, st.acc[mt] * inv);
+        if (a.lse && grp == 0) a.lse[(size_t)trow * a.hq + h] = poison ? NAN : (st.m + log2f(l)) * kLn2;
+      } else {
+        const size_t slot = (size_t)(p.item_base + p.item_start[j] + split) * a.hq + h;
+        float* wo = a.ws_o + slot * D;
+        const float bad = poison ? NAN : 1.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          *reinterpret_cast<f32x4*>(wo + 16 * mt + 4 * grp) = st.acc[mt] * (bad * a.v_scale);
+        if (grp == 0) {
+          a.ws_ml[slot * 2] = st.m;
+          a.ws_ml[slot * 2 + 1] = l * bad;
+        }
+      }
+    }
+    if (!STREAM || blk >= blk_end) return;
   }
 }
 
@@ -638,13 +738,14 @@ __global__ __launch_bounds__(256) void decode_kernel(AttnArgs a, DecodePlan p) {
 // output is sum_k acc_k 2^(m_k - M) divided by that denominator.
 //
 // One output row from n partial results, by one wave.  Splits are taken 64
-// at a time: lane k loads split k's (m, l) pair, the group's maximum and
-// weighted sum come from wave reductions, and the partial rows are then
-// loaded four at a time (all four issued before any is used), each weight
-// broadcast from its lane.  Only the n real splits are read.  ml points at
-// split 0's (m, l) pair (8-byte aligned), acc at split 0's element `lane` of
-// the row; consecutive splits are ml_stride and acc_stride floats apart.
-// Lane l writes elements l, l + 64, ... of out; lane 0 writes lse.
+// at a time: lane k loads split k's (m, l) pair and the group's maximum and
+// weighted sum come from wave reductions.  A partial row is D / 4 lanes of
+// 16 bytes, so the wave reads 256 / D rows per instruction, kMergeUnroll of
+// them in flight; each lane adds its 4 elements of every (256 / D)-th split,
+// and the lanes' sums are combined at the end.  Only the n real splits are
+// read.  ml points at split 0's (m, l) pair (8-byte aligned), acc at split
+// 0's row (16-byte aligned); consecutive splits are ml_stride and acc_stride
+// floats apart.
 __device__ inline float wave_max64(float x) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
@@ -655,21 +756,24 @@ __device__ inline float wave_sum64(float x) {
   for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
   return x;
 }
-__device__ inline float lane_value(float x, int k) {  // k wave-uniform
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
-}
+constexpr int kMergeUnroll = 4;
 
-template <int DT, int D>
-__device__ inline void merge_splits(const float* ml, size_t ml_stride, const float* acc, size_t acc_stride, int n,
-                                    typename Tr<DT>::QElem* out, float* lse) {
-  using T = Tr<DT>;
-  constexpr int PER = D / 64;
-  constexpr int U = 4;
+// Running result over some splits of a row: maximum, weighted sum and (in
+// every lane, elements 4 * (lane % (D / 4)) .. + 3) weighted rows.
+struct MergeState {
+  float M, lsum;
+  f32x4 o;
+};
+
+template <int D>
+__device__ inline MergeState merge_range(const float* ml, size_t ml_stride, const float* acc, size_t acc_stride,
+                                         int n) {
+  constexpr int LPR = D / 4;     // lanes per partial row
+  constexpr int RPI = 64 / LPR;  // rows per load instruction
   const int lane = threadIdx.x & 63;
-  float M = -INFINITY, lsum = 0.f;
-  float o[PER];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) o[e] = 0.f;
+  const int sub = lane / LPR;
+  acc += 4 * (lane % LPR);
+  MergeState r = {-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
   for (int c0 = 0; c0 < n; c0 += 64) {
     const int cnt = min(64, n - c0);
     float mk = -INFINITY, lk = 0.f;
@@ -678,38 +782,41 @@ __device__ inline void merge_splits(const float* ml, size_t ml_stride, const flo
       mk = v.x;
       lk = v.y;
     }
-    const float gm = fmaxf(M, wave_max64(mk));      // every split holds a key: finite
+    const float gm = fmaxf(r.M, wave_max64(mk));  // every split holds a key: finite
     const float wk = lane < cnt ? exp2_fast(mk - gm) : 0.f;
-    const float rescale = exp2_fast(M - gm);        // M = -inf on the first group: 0
-    lsum = lsum * rescale + wave_sum64(wk * lk);
+    const float rescale = exp2_fast(r.M - gm);    // M = -inf on the first group: 0
+    r.lsum = r.lsum * rescale + wave_sum64(wk * lk);
+    r.o *= rescale;
+    for (int k = 0; k < cnt; k += RPI * kMergeUnroll) {
+      f32x4 v[kMergeUnroll];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) o[e] *= rescale;
-    const float* a0 = acc + (size_t)c0 * acc_stride;
-    int k = 0;
-    for (; k + U <= cnt; k += U) {
-      float v[U][PER];
+      for (int u = 0; u < kMergeUnroll; ++u) {
+        const int i = min(k + u * RPI + sub, cnt - 1);
+        v[u] = *reinterpret_cast<const f32x4*>(acc + (size_t)(c0 + i) * acc_stride);
+      }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < PER; ++e) v[u][e] = a0[(size_t)(k + u) * acc_stride + 64 * e];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const float w = lane_value(wk, k + u);
-#pragma unroll
-        for (int e = 0; e < PER; ++e) o[e] += w * v[u][e];
+      for (int u = 0; u < kMergeUnroll; ++u) {
+        const int i = k + u * RPI + sub;
+        const float w = __shfl(wk, min(i, cnt - 1));
+        if (i < cnt) r.o += v[u] * w;
       }
     }
-    for (; k < cnt; ++k) {
-      const float w = lane_value(wk, k);
-#pragma unroll
-      for (int e = 0; e < PER; ++e) o[e] += w * a0[(size_t)k * acc_stride + 64 * e];
-    }
-    M = gm;
+    r.M = gm;
   }
-  const float inv = 1.f / lsum;
 #pragma unroll
-  for (int e = 0; e < PER; ++e) T::store1(out + lane + 64 * e, o[e] * inv);
-  if (lse && lane == 0) *lse = (M + log2f(lsum)) * kLn2;
+  for (int off = LPR; off < 64; off <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r.o[e] += __shfl_xor(r.o[e], off);
+  return r;
+}
+
+// Lanes 0 .. D/4 - 1 write the row's elements, lane 0 its lse.
+template <int DT, int D>
+__device__ inline void merge_store(const MergeState& r, typename Tr<DT>::QElem* out, float* lse) {
+  const int lane = threadIdx.x & 63;
+  const float inv = 1.f / r.lsum;
+  if (lane < D / 4) Tr<DT>::store4(out + 4 * lane, r.o * inv);
+  if (lse && lane == 0) *lse = (r.M + log2f(r.lsum)) * kLn2;
 }
 
 // The merge kernels run four waves per workgroup, each wave merging whole
@@ -720,23 +827,51 @@ constexpr int kMergeWaves = 4;
 constexpr int kPrefillMergeHeadsPerWave = 4;
 
 // Decode merge: one workgroup per (split decode sequence, 4 q heads); wave w
-// merges head 4 * blockIdx.y + w.
-template <int DT, int D>
+// merges head 4 * blockIdx.y + w.  WIDE: one workgroup per (sequence, q
+// head), its waves each taking a quarter of the splits.
+template <int DT, int D, bool WIDE>
 __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(AttnArgs a, DecodePlan p) {
   using E = typename Tr<DT>::QElem;
   const int j = blockIdx.x;
-  const int h = blockIdx.y * kMergeWaves + wave_uniform(threadIdx.x >> 6);
+  const int wave = wave_uniform(threadIdx.x >> 6);
+  const int h = WIDE ? blockIdx.y : blockIdx.y * kMergeWaves + wave;
   if (j >= p.n_seqs || h >= a.hq) return;
   const int n = p.item_start[j + 1] - p.item_start[j];
   if (n <= 1) return;
   const int s = p.seq[j];
-  const size_t base = (size_t)p.item_base + p.item_start[j];
   const int t = a.qsl[s];
-  const int lane = threadIdx.x & 63;
-  merge_splits<DT, D>(a.ws_ml + (base * a.hq + h) * 2, (size_t)a.hq * 2,
-                      a.ws_o + (base * a.hq + h) * D + lane, (size_t)a.hq * D, n,
-                      reinterpret_cast<E*>(a.out) + ((size_t)t * a.hq + h) * D,
-                      a.lse ? a.lse + (size_t)t * a.hq + h : nullptr);
+  // this wave's splits [x0, x0 + nx)
+  const int per = WIDE ? (n + kMergeWaves - 1) / kMergeWaves : n;
+  const int x0 = WIDE ? min(wave * per, n) : 0;
+  const int nx = WIDE ? min(per, n - x0) : n;
+  const size_t base = (size_t)p.item_base + p.item_start[j] + x0;
+  MergeState r = merge_range<D>(a.ws_ml + (base * a.hq + h) * 2, (size_t)a.hq * 2, a.ws_o + (base * a.hq + h) * D,
+                                (size_t)a.hq * D, nx);
+  if constexpr (WIDE) {
+    __shared__ float ml[kMergeWaves][2];
+    __shared__ f32x4 rows[kMergeWaves][D / 4];
+    const int lane = threadIdx.x & 63;
+    if (lane == 0) {
+      ml[wave][0] = r.M;
+      ml[wave][1] = r.lsum;
+    }
+    if (lane < D / 4) rows[wave][lane] = r.o;
+    __syncthreads();
+    if (wave != 0) return;
+    float M = ml[0][0];  // wave 0 has splits: finite
+#pragma unroll
+    for (int w = 1; w < kMergeWaves; ++w) M = fmaxf(M, ml[w][0]);
+    MergeState all = {M, 0.f, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int w = 0; w < kMergeWaves; ++w) {
+      const float f = exp2_fast(ml[w][0] - M);  // a wave without splits: 0
+      all.lsum += ml[w][1] * f;
+      all.o += rows[w][lane % (D / 4)] * f;
+    }
+    r = all;
+  }
+  merge_store<DT, D>(r, reinterpret_cast<E*>(a.out) + ((size_t)t * a.hq + h) * D,
+                     a.lse ? a.lse + (size_t)t * a.hq + h : nullptr);
 }
 
 // Prefill merge: one workgroup per (token of a KV-split chunk, 16 q heads);
@@ -753,15 +888,14 @@ __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArg
   const int t0 = a.qsl[s];
   const int C = a.qsl[s + 1] - t0;
   const size_t slot = (size_t)p.item_base[j] + i;
-  const int lane = threadIdx.x & 63;
   const int h0 = blockIdx.y * (kMergeWaves * kPrefillMergeHeadsPerWave) + wave_uniform(threadIdx.x >> 6);
   for (int k = 0; k < kPrefillMergeHeadsPerWave; ++k) {
     const int h = h0 + k * kMergeWaves;
     if (h >= a.hq) break;
-    merge_splits<DT, D>(a.ws_ml + (slot * a.hq + h) * 2, (size_t)C * a.hq * 2,
-                        a.ws_o + (slot * a.hq + h) * D + lane, (size_t)C * a.hq * D, p.nsplit[j],
-                        reinterpret_cast<E*>(a.out) + ((size_t)(t0 + i) * a.hq + h) * D,
-                        a.lse ? a.lse + (size_t)(t0 + i) * a.hq + h : nullptr);
+    const MergeState m = merge_range<D>(a.ws_ml + (slot * a.hq + h) * 2, (size_t)C * a.hq * 2,
+                                        a.ws_o + (slot * a.hq + h) * D, (size_t)C * a.hq * D, p.nsplit[j]);
+    merge_store<DT, D>(m, reinterpret_cast<E*>(a.out) + ((size_t)(t0 + i) * a.hq + h) * D,
+                       a.lse ? a.lse + (size_t)(t0 + i) * a.hq + h : nullptr);
   }
 }
 
@@ -770,7 +904,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArg
 // tile's 64 (token, head) rows are the 16 columns of each of the 4 waves;
 // row r is token r / G of the tile and head r % G of the group.
 template <int DT, int D>
-__global__ __launch_bounds__(256) void prefill_kernel(AttnArgs a, PrefillPlan p) {
+__global__ __launch_bounds__(256, 2) void prefill_kernel(AttnArgs a, PrefillPlan p) {
   using T = Tr<DT>;
   using QE = typename T::QElem;
   constexpr int X = T::X;
@@ -816,8 +950,9 @@ __global__ __launch_bounds__(256) void prefill_kernel(AttnArgs a, PrefillPlan p)
   st.l = 0.f;
   bool poison = false;
   const int min_limit = P + min(first_tok + (wave * 16) / G, C - 1);
-  attend_blocks<DT, D>(a, qf, a.block_tables + (size_t)s * a.mb, g, 0, (kend + kBlock - 1) / kBlock,
-                       kend, P + i, min_limit, st, poison);
+  int step = 0;
+  attend_blocks<DT, D, false>(a, qf, a.block_tables + (size_t)s * a.mb, g, 0, (kend + kBlock - 1) / kBlock,
+                       kend, P + i, min_limit, st, poison, step);
 
   float l = st.l + __shfl_xor(st.l, 16);
   l += __shfl_xor(l, 32);
@@ -1673,14 +1808,44 @@ struct RopeAppendL {
   }
 };
 
+// Waves per streaming workgroup: bf16 and f32 caches, all that a CU holds (2
+// to 4 per SIMD), so that the lockstep covers the CU; fp8 caches, whose waves
+// keep even by themselves (their copies run two blocks ahead; with the
+// lockstep at any distance the same time within 0.5 %), the usual four.
+template <int DT, int D>
+constexpr int kStreamWaves = DT == 2 ? kWavesPerGroup : 4 * decode_waves_per_simd(DT, D);
+
 template <int DT, int D>
 struct DecodeL {
   static hipError_t run(const AttnArgs& a, const DecodePlan& p, int n_items, hipStream_t stream) {
     const long units = (long)n_items * a.hkv;
     if (units == 0) return hipSuccess;
-    hipLaunchKernelGGL((decode_kernel<DT, D>), dim3((unsigned)((units + kWavesPerGroup - 1) / kWavesPerGroup)),
-                       dim3(64 * kWavesPerGroup), 0, stream, a, p);
+    if (p.range_blocks > 0) {
+      constexpr int W = kStreamWaves<DT, D>;
+      const long waves = (long)((p.part[p.n_seqs] + p.range_blocks - 1) / p.range_blocks) * a.hkv;
+      hipLaunchKernelGGL((decode_kernel<DT, D, W, true>), dim3((unsigned)((waves + W - 1) / W)), dim3(64 * W), 0, stream,
+                         a, p);
+      return hipGetLastError();
+    }
+    hipLaunchKernelGGL((decode_kernel<DT, D, kWavesPerGroup, false>),
+                       dim3((unsigned)((units + kWavesPerGroup - 1) / kWavesPerGroup)), dim3(64 * kWavesPerGroup), 0,
+                       stream, a, p);
     return hipGetLastError();
+  }
+};
+
+// Decode waves per CU.
+template <int DT, int D>
+struct DecodeOccupancy {
+  static hipError_t run(bool stream, int* waves) {
+    constexpr int W = kStreamWaves<DT, D>;
+    int groups = 0;
+    const hipError_t e =
+        stream ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&groups, decode_kernel<DT, D, W, true>, 64 * W, 0)
+               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&groups, decode_kernel<DT, D, kWavesPerGroup, false>,
+                                                              64 * kWavesPerGroup, 0);
+    *waves = groups * (stream ? W : kWavesPerGroup);
+    return e;
   }
 };
 
@@ -1688,8 +1853,12 @@ template <int DT, int D>
 struct MergeL {
   static hipError_t run(const AttnArgs& a, const DecodePlan& p, hipStream_t stream) {
     if (p.n_seqs == 0) return hipSuccess;
-    hipLaunchKernelGGL((merge_kernel<DT, D>), dim3(p.n_seqs, (a.hq + kMergeWaves - 1) / kMergeWaves),
-                       dim3(64 * kMergeWaves), 0, stream, a, p);
+    const int parts = p.item_start[p.n_seqs];
+    if (parts >= 16L * p.n_seqs && (long)p.n_seqs * a.hq <= 4096)
+      hipLaunchKernelGGL((merge_kernel<DT, D, true>), dim3(p.n_seqs, a.hq), dim3(64 * kMergeWaves), 0, stream, a, p);
+    else
+      hipLaunchKernelGGL((merge_kernel<DT, D, false>), dim3(p.n_seqs, (a.hq + kMergeWaves - 1) / kMergeWaves),
+                         dim3(64 * kMergeWaves), 0, stream, a, p);
     return hipGetLastError();
   }
 };
@@ -1748,34 +1917,24 @@ hipError_t launch_rope_append(const AppendArgs& a, const AppendPlan& p, const Ro
   return dispatch<RopeAppendL>(dtype, head_dim, a, p, r, stream);
 }
 
-int decode_wave_slots(int dtype, int head_dim) {
+int decode_wave_slots(int dtype, int head_dim, bool stream) {
   // Concurrent decode waves the device can hold: workgroups per CU at this
-  // kernel's register use, times waves per workgroup, times CUs.  Cached per
-  // device; 2048 when there is no device to ask.
-  static std::atomic<int> cache[64][3][2];
+  // kernel's register and LDS use, times waves per workgroup, times CUs.
+  // Cached per device.  Without a device: 2048, and 0 for the streaming kernel
+  // (whose ranges are made for the device that runs them).
+  const int none = stream ? 0 : 2048;
+  static std::atomic<int> cache[64][3][2][2];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 2048;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return none;
   const int di = dtype == 0 ? 0 : dtype == 1 ? 1 : 2, hi = head_dim == 128 ? 0 : 1;
-  const int known = cache[dev][di][hi].load(std::memory_order_relaxed);
+  std::atomic<int>& entry = cache[dev][di][hi][stream ? 1 : 0];
+  const int known = entry.load(std::memory_order_relaxed);
   if (known > 0) return known;
   int cus = 0, per_cu = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 2048;
-  hipError_t e = hipErrorInvalidValue;
-  if (dtype == 0 && head_dim == 128)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<0, 128>, 256, 0);
-  else if (dtype == 0 && head_dim == 64)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<0, 64>, 256, 0);
-  else if (dtype == 1 && head_dim == 128)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<1, 128>, 256, 0);
-  else if (dtype == 1 && head_dim == 64)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<1, 64>, 256, 0);
-  else if (dtype == 2 && head_dim == 128)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<2, 128>, 256, 0);
-  else if (dtype == 2 && head_dim == 64)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<2, 64>, 256, 0);
-  if (e != hipSuccess || per_cu <= 0) return 2048;
-  const int slots = per_cu * kWavesPerGroup * cus;
-  cache[dev][di][hi].store(slots, std::memory_order_relaxed);
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return none;
+  if (dispatch<DecodeOccupancy>(dtype, head_dim, stream, &per_cu) != hipSuccess || per_cu <= 0) return none;
+  const int slots = per_cu * cus;
+  entry.store(slots, std::memory_order_relaxed);
   return slots;
 }
 hipError_t launch_decode(const AttnArgs& a, const DecodePlan& p, int n_items, int dtype, int head_dim,
