@@ -482,7 +482,7 @@ __device__ inline void attend_blocks(const AttnArgs& a, const typename Tr<DT>::C
                                      int limit, int min_limit, RowState<DT, D>& st, bool& poison, int& step) {
   const bool few_keys = kend <= kFewKeys;  // every row sees at most kFewKeys keys
   const int whole = min_limit < kend ? min_limit + 1 : kend;  // keys that every row sees
-  const int kb_edge = few_keys ? kb_begin : max(kb_begin, whole / kBlock);
+  const int kb_edge = few_keys ? kb_begin : max(kb_begin, min(kb_end, whole / kBlock));
   if (kb_begin >= kb_end) return;
   BlockIds id(bt, kb_begin, kb_end, a.nb);
   BlockFrags<DT, D> fa, fb;
@@ -542,7 +542,7 @@ __device__ inline void attend_blocks_fp8_lds(const AttnArgs& a, const bf16x8* qf
   const int n = lane & 15, grp = lane >> 4;
   const bool few_keys = kend <= kFewKeys;
   const int whole = min_limit < kend ? min_limit + 1 : kend;
-  const int kb_edge = few_keys ? kb_begin : max(kb_begin, whole / kBlock);
+  const int kb_edge = few_keys ? kb_begin : max(kb_begin, min(kb_end, whole / kBlock));
   if (kb_begin >= kb_end) return;
   BlockIds id(bt, kb_begin, kb_end, a.nb);
   auto copy = [&](int kb, int slot) {
@@ -933,11 +933,33 @@ __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArg
 }
 
 // ---------------------------------------------------------------------------
-// Prefill chunks: one workgroup per (sequence, query tile, KV head).  The
-// tile's 64 (token, head) rows are the 16 columns of each of the 4 waves;
-// row r is token r / G of the tile and head r % G of the group.
-template <int DT, int D>
-__global__ __launch_bounds__(256, 2) void prefill_kernel(AttnArgs a, PrefillPlan p) {
+// Prefill chunks, f32 caches.  A (sequence, query tile, KV head) has 64
+// (token, head) rows; row r is token r / G of the tile and head r % G of the
+// group.  A wave works on 16 rows (its MFMA columns).
+// KEYS false: one workgroup per tile, each of its 4 waves with rows of its
+// own and all their keys.
+// KEYS true: one workgroup per 16 rows (4 to a tile), whose 8 waves each take
+// an eighth of the key blocks; their results are merged in LDS.  A wave needs
+// 2,048 MFMA cycles per 16 keys whichever form runs, so a tile by itself
+// takes about 1.2 us per block of its longest row with most of the device
+// idle; an eighth of the keys a wave spreads the same products over four
+// times the workgroups and eighths of the time.
+constexpr int kKeyWaves = 8;
+
+// Which form a launch of this many (tile, KV head) pairs takes, measured
+// (us, KEYS false -> true; head_dim 128, tokens on prefix):
+//   64 tiles  (8/2 heads, 500 on 1,000)  112.5 ->  41.4
+//   152       (32/8, 300 on 1,000)        99.6 ->  89.8
+//   250       (8/2, 2,000 on 500)        182.5 -> 152.9
+//   256       (32/8, 500 on 1,000)       115.4 -> 128.1  (one full round of tiles)
+//   352       (32/8, 700 on 1,000)       246.2 -> 202.3
+//   504       (32/8, 1,000 on 0)         134.1 -> 133.0
+//   752       (32/8, 1,500 on 2,000)     710.7 -> 755.6  (K and V read for 16 rows, not 64)
+// A launch that just fills one round, or makes two, keeps whole tiles.
+constexpr bool prefill_by_keys(long tiles) { return tiles <= 224 || (tiles > 256 && tiles < 504); }
+
+template <int DT, int D, bool KEYS>
+__global__ __launch_bounds__(KEYS ? 64 * kKeyWaves : 256, 2) void prefill_kernel(AttnArgs a, PrefillPlan p) {
   using T = Tr<DT>;
   using QE = typename T::QElem;
   constexpr int X = T::X;
@@ -945,9 +967,12 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(AttnArgs a, PrefillPlan
   constexpr int MT = D / 16;
   const int lane = threadIdx.x & 63;
   const int wave = wave_uniform(threadIdx.x >> 6);
-  const int tile = blockIdx.x;
-  const int g = blockIdx.y;
-  if (tile >= p.tile_start[p.n_seqs]) return;
+  const int unit = blockIdx.x / a.hkv;
+  const int g = blockIdx.x - unit * a.hkv;
+  const int n_tiles = p.tile_start[p.n_seqs];
+  const int tile = n_tiles - 1 - (KEYS ? unit >> 2 : unit);  // a chunk's last (longest) tiles first
+  const int sub = KEYS ? unit & 3 : wave;                    // the 16 rows of the tile
+  if (tile < 0) return;
   const int j = upper_index(p.tile_start, p.n_seqs, tile);
   const int s = p.seq[j];
   const int qt = tile - p.tile_start[j];
@@ -957,9 +982,9 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(AttnArgs a, PrefillPlan
   const int P = L - C;
   const int G = a.hq / a.hkv;
   const int first_tok = qt * p.q_tile;
-  if (first_tok + (wave * 16) / G >= C) return;  // this wave has no rows
+  if (first_tok + (sub * 16) / G >= C) return;  // no rows here (the same for the whole workgroup with KEYS)
   const int n = lane & 15, grp = lane >> 4;
-  const int row = wave * 16 + n;
+  const int row = sub * 16 + n;
   // The tile holds q_tile tokens (G * q_tile <= 64 rows): when G does not
   // divide 64, the last rows of the workgroup would fall on the next tile's
   // first token.  They compute a valid token of this tile and store nothing.
@@ -968,8 +993,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(AttnArgs a, PrefillPlan
   const bool row_ok = r_tok < p.q_tile && i_raw < C;
   const int i = min(i_raw, C - 1);
   const int h = g * G + row % G;
-  const int last_tok = min(first_tok + min((wave * 16 + 15) / G, p.q_tile - 1), C - 1);
-  const int kend = P + last_tok + 1;  // keys this wave needs
+  const int last_tok = min(first_tok + min((sub * 16 + 15) / G, p.q_tile - 1), C - 1);
+  const int kend = P + last_tok + 1;  // keys these rows need
 
   const QE* q = reinterpret_cast<const QE*>(a.q) + ((size_t)(t0 + i) * a.hq + h) * D;
   typename T::Chunk qf[R];
@@ -982,16 +1007,56 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(AttnArgs a, PrefillPlan
   st.m = -INFINITY;
   st.l = 0.f;
   bool poison = false;
-  const int min_limit = P + min(first_tok + (wave * 16) / G, C - 1);
+  const int min_limit = P + min(first_tok + (sub * 16) / G, C - 1);
+  const int nb = (kend + kBlock - 1) / kBlock;
+  const int per = KEYS ? (nb + kKeyWaves - 1) / kKeyWaves : nb;
+  const int kb0 = KEYS ? min(wave * per, nb) : 0;
   int step = 0;
-  attend_blocks<DT, D, false>(a, qf, a.block_tables + (size_t)s * a.mb, g, 0, (kend + kBlock - 1) / kBlock,
-                       kend, P + i, min_limit, st, poison, step);
+  attend_blocks<DT, D, false>(a, qf, a.block_tables + (size_t)s * a.mb, g, kb0, min(nb, kb0 + per), kend, P + i,
+                              min_limit, st, poison, step);
 
   float l = st.l + __shfl_xor(st.l, 16);
   l += __shfl_xor(l, 32);
+  QE* o = reinterpret_cast<QE*>(a.out) + ((size_t)(t0 + i) * a.hq + h) * D;
+  if constexpr (KEYS) {
+    // (max, sum) of every wave and row, then the accumulators, half of the
+    // dims at a time; wave w adds up the rows' dims 16 * mt for its mt.  A
+    // wave that saw no key of a row has max -inf and weight 0; wave 0 has key
+    // 0, which every row sees.
+    __shared__ float ml[kKeyWaves][2][16];
+    __shared__ f32x4 part[kKeyWaves][MT / 2][64];
+    if (grp == 0) {
+      ml[wave][0][n] = st.m;
+      ml[wave][1][n] = poison ? NAN : l;
+    }
+    float w[kKeyWaves], M = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half) __syncthreads();
+#pragma unroll
+      for (int mt = 0; mt < MT / 2; ++mt) part[wave][mt][lane] = st.acc[half * (MT / 2) + mt];
+      __syncthreads();
+      if (half == 0) {
+#pragma unroll
+        for (int k = 0; k < kKeyWaves; ++k) M = fmaxf(M, ml[k][0][n]);
+#pragma unroll
+        for (int k = 0; k < kKeyWaves; ++k) {
+          w[k] = exp2_fast(ml[k][0][n] - M);
+          sum += ml[k][1][n] * w[k];
+        }
+      }
+      if (wave < MT / 2 && row_ok) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kKeyWaves; ++k) v += part[k][wave][lane] * w[k];
+        T::store4(o + 16 * (half * (MT / 2) + wave) + 4 * grp, v * (a.v_scale / sum));
+      }
+    }
+    if (a.lse && wave == 0 && grp == 0 && row_ok) a.lse[(size_t)(t0 + i) * a.hq + h] = (M + log2f(sum)) * kLn2;
+    return;
+  }
   if (!row_ok) return;
   const float inv = poison ? NAN : a.v_scale / l;
-  QE* o = reinterpret_cast<QE*>(a.out) + ((size_t)(t0 + i) * a.hq + h) * D;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) T::store4(o + 16 * mt + 4 * grp, st.acc[mt] * inv);
   if (a.lse && grp == 0)
@@ -1928,7 +1993,12 @@ struct PrefillL {
     if constexpr (DT == 0 || DT == 2) {
       return launch_prefill_mfma<DT, D>(a, p, n_tiles, stream);
     } else {
-      hipLaunchKernelGGL((prefill_kernel<DT, D>), dim3(n_tiles, a.hkv), dim3(64 * kWavesPerGroup), 0, stream, a, p);
+      if (prefill_by_keys((long)n_tiles * a.hkv))
+        hipLaunchKernelGGL((prefill_kernel<DT, D, true>), dim3((unsigned)n_tiles * 4 * a.hkv), dim3(64 * kKeyWaves), 0, stream, a,
+                           p);
+      else
+        hipLaunchKernelGGL((prefill_kernel<DT, D, false>), dim3((unsigned)n_tiles * a.hkv), dim3(64 * kWavesPerGroup), 0, stream,
+                           a, p);
       return hipGetLastError();
     }
   }
