@@ -500,7 +500,7 @@ int check_append_slots(const mpa_shape* sh, const int32_t* seq_lens, const int32
 }
 
 // The append launches (plain, or with the rotary embedding when rope is
-// given): one wave per new token, up to kMaxPlanSeqs sequences per launch.
+// given).
 int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                const int32_t* block_tables, const int32_t* seq_lens, const int32_t* query_start_loc,
                const int32_t* seq_lens_host, const int32_t* query_start_loc_host, const int32_t* block_tables_host,
@@ -528,53 +528,41 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
   (void)seq_lens;
   (void)query_start_loc;
   const Batch b = classify(shape, seq_lens_host, query_start_loc_host);
-  // single-token sequences one wave per token; with the rotary embedding
-  // (which also rotates q, token by token) every sequence
-  std::vector<int> seqs(b.decode);
-  if (rope) seqs.insert(seqs.end(), b.prefill.begin(), b.prefill.end());
-  if (multi_only) seqs.clear();  // the decode kernel appends the single-token rows
   clear_stale_hip_error();
   // multi-token sequences one wave per (cache block, KV head)
-  if (!rope) {
-    for (size_t c0 = 0; c0 < b.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
-      mpa::AppendBlockPlan p;
-      memset(&p, 0, sizeof(p));
-      const size_t c1 = std::min(b.prefill.size(), c0 + mpa::kMaxPrefillSeqs);
-      p.n_seqs = (int32_t)(c1 - c0);
-      int acc = 0;
-      for (size_t k = c0; k < c1; ++k) {
-        const int s = b.prefill[k];
-        const int ql = query_start_loc_host[s + 1] - query_start_loc_host[s];
-        const int pos0 = seq_lens_host[s] - ql;
-        p.seq[k - c0] = s;
-        p.row0[k - c0] = query_start_loc_host[s];
-        p.pos0[k - c0] = pos0;
-        p.ntok[k - c0] = ql;
-        p.unit_start[k - c0] = acc;
-        acc += (pos0 + ql - 1) / kBlock - pos0 / kBlock + 1;
-      }
-      p.unit_start[c1 - c0] = acc;
-      if (mpa::launch_append_blocks(a, p, shape->dtype, shape->head_dim, (hipStream_t)stream) != hipSuccess)
-        return MPA_ERR_HIP;
-    }
-  }
-  for (size_t c0 = 0; c0 < seqs.size(); c0 += mpa::kMaxPlanSeqs) {
-    mpa::AppendPlan p;
-    memset(&p, 0, sizeof(p));
-    const size_t c1 = std::min(seqs.size(), c0 + mpa::kMaxPlanSeqs);
-    p.n_seqs = (int32_t)(c1 - c0);
-    int acc = 0;
-    for (size_t k = c0; k < c1; ++k) {
-      const int s = seqs[k];
+  for (size_t c0 = 0; c0 < b.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
+    mpa::AppendBlockPlan p;
+    p.n_seqs = (int32_t)(std::min(b.prefill.size(), c0 + mpa::kMaxPrefillSeqs) - c0);
+    int units = 0, tokens = 0;
+    for (int k = 0; k < p.n_seqs; ++k) {
+      const int s = b.prefill[c0 + k];
       const int ql = query_start_loc_host[s + 1] - query_start_loc_host[s];
-      p.seq[k - c0] = s;
-      p.row0[k - c0] = query_start_loc_host[s];
-      p.pos0[k - c0] = seq_lens_host[s] - ql;
-      p.tok_start[k - c0] = acc;
-      acc += ql;
+      const int pos0 = seq_lens_host[s] - ql;
+      p.seq[k] = s;
+      p.row0[k] = query_start_loc_host[s];
+      p.pos0[k] = pos0;
+      p.ntok[k] = ql;
+      p.unit_start[k] = units;
+      p.tok_start[k] = tokens;
+      units += (pos0 + ql - 1) / kBlock - pos0 / kBlock + 1;
+      tokens += ql;
     }
-    p.tok_start[c1 - c0] = acc;
-    p.unit = acc == (int)(c1 - c0) ? 1 : 0;
+    p.unit_start[p.n_seqs] = units;
+    p.tok_start[p.n_seqs] = tokens;
+    if (mpa::launch_append_blocks(a, p, rope, shape->dtype, shape->head_dim, (hipStream_t)stream) != hipSuccess)
+      return MPA_ERR_HIP;
+  }
+  // single-token sequences one wave per token, unless the decode kernel
+  // appends them
+  for (size_t c0 = 0; !multi_only && c0 < b.decode.size(); c0 += mpa::kMaxPlanSeqs) {
+    mpa::AppendPlan p;
+    p.n_seqs = (int32_t)(std::min(b.decode.size(), c0 + mpa::kMaxPlanSeqs) - c0);
+    for (int k = 0; k < p.n_seqs; ++k) {
+      const int s = b.decode[c0 + k];
+      p.seq[k] = s;
+      p.row[k] = query_start_loc_host[s];
+      p.pos[k] = seq_lens_host[s] - 1;
+    }
     hipError_t e = rope ? mpa::launch_rope_append(a, p, *rope, shape->dtype, shape->head_dim, (hipStream_t)stream)
                         : mpa::launch_append(a, p, shape->dtype, shape->head_dim, (hipStream_t)stream);
     if (e != hipSuccess) return MPA_ERR_HIP;

@@ -98,17 +98,13 @@ struct RopeArgs {
   int32_t hq, half;
 };
 
-// Append work for up to kMaxPlanSeqs sequences: token k of this launch is new
-// token (k - tok_start[j]) of sequence seq[j]; that token is query row
-// row0[j] + (k - tok_start[j]) at position pos0[j] + (k - tok_start[j]).
+// Append work for up to kMaxPlanSeqs sequences that add one token each:
+// sequence seq[k]'s is query row row[k] at position pos[k].
 struct AppendPlan {
   int32_t n_seqs;
-  int32_t unit;  // 1 when every sequence of the plan adds exactly one token
-
   int32_t seq[kMaxPlanSeqs];
-  int32_t row0[kMaxPlanSeqs];
-  int32_t pos0[kMaxPlanSeqs];
-  int32_t tok_start[kMaxPlanSeqs + 1];
+  int32_t row[kMaxPlanSeqs];
+  int32_t pos[kMaxPlanSeqs];
 };
 
 // Append work for up to kMaxPrefillSeqs sequences that add several tokens,
@@ -123,14 +119,16 @@ struct AppendBlockPlan {
   int32_t pos0[kMaxPrefillSeqs];
   int32_t ntok[kMaxPrefillSeqs];
   int32_t unit_start[kMaxPrefillSeqs + 1];
+  int32_t tok_start[kMaxPrefillSeqs + 1];  // new tokens of the sequences before j
 };
 
 // Launchers (mpa_kernels.hip).  dtype: 0 = bf16, 1 = f32, 2 = fp8 cache.  Return the HIP
 // error of the launch.
 hipError_t launch_append(const AppendArgs& a, const AppendPlan& p, int dtype, int head_dim, hipStream_t stream);
-// The same bits for multi-token sequences, one wave per (cache block, KV head).
-hipError_t launch_append_blocks(const AppendArgs& a, const AppendBlockPlan& p, int dtype, int head_dim,
-                                hipStream_t stream);
+// The same bits for multi-token sequences, one wave per (cache block, KV
+// head); with the rotary embedding when rope is given.
+hipError_t launch_append_blocks(const AppendArgs& a, const AppendBlockPlan& p, const RopeArgs* rope, int dtype,
+                                int head_dim, hipStream_t stream);
 hipError_t launch_rope_append(const AppendArgs& a, const AppendPlan& p, const RopeArgs& r, int dtype, int head_dim,
                               hipStream_t stream);
 // Decode waves the current device holds at once, of the kernel that splits

@@ -1616,12 +1616,11 @@ __device__ inline void store_fp8_chunk(const AppendArgs& a, size_t head, int c, 
 }
 
 // ---------------------------------------------------------------------------
-// Append: one wave per new token.  The token's sequence comes from the
-// kernel-argument plan (directly when every sequence of the plan adds one
-// token, else by a scalar binary search), its block id from one scalar load;
-// the wave then copies the token's Hkv*d key elements as 16-byte chunks and
-// its value elements into the V^T rows of the slot, issuing the loads of up
-// to 4 chunks per lane before their stores.
+// Append of the sequences that add one token: one wave per token, whose
+// sequence comes from the kernel-argument plan and its block id from one
+// scalar load; the wave then copies the token's Hkv*d key elements as 16-byte
+// chunks and its value elements into the V^T rows of the slot, issuing the
+// loads of up to 4 chunks per lane before their stores.
 template <int DT, int D>
 __global__ __launch_bounds__(256) void append_kernel(AppendArgs a, AppendPlan p) {
   using T = Tr<DT>;
@@ -1631,12 +1630,10 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a, AppendPlan p)
   constexpr int U = 4;
   const int lane = threadIdx.x & 63;
   const int tok = blockIdx.x * kWavesPerGroup + wave_uniform(threadIdx.x >> 6);
-  if (tok >= p.tok_start[p.n_seqs]) return;
-  const int j = p.unit ? tok : upper_index(p.tok_start, p.n_seqs, tok);
-  const int k = tok - p.tok_start[j];
-  const int s = p.seq[j];
-  const int t = p.row0[j] + k;
-  const int pos = p.pos0[j] + k;
+  if (tok >= p.n_seqs) return;
+  const int s = p.seq[tok];
+  const int t = p.row[tok];
+  const int pos = p.pos[tok];
   const int blk = a.block_tables[(size_t)s * a.mb + pos / kBlock];
   if (blk < 0 || blk >= a.nb) return;
   const int slot = pos % kBlock;
@@ -1679,6 +1676,84 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a, AppendPlan p)
   }
 }
 
+// Rotary embedding of 16-byte chunk c of one head row (rotate-half form):
+// element i < half pairs with i + half; with the position's angle row cs
+// (cos, sin interleaved per pair), y_i = x_i cos - x_{i+half} sin and
+// y_{i+half} = x_{i+half} cos + x_i sin, and elements >= 2*half are copied.
+// half is a multiple of the chunk's element count.  Each product and each
+// sum is rounded to f32 (no fused multiply-add), then the result to the
+// storage type.
+template <int DT>
+__device__ inline u32x4 rope_chunk(const typename Tr<DT>::Elem* row, int c, int half, const float* cs) {
+#pragma clang fp contract(off)
+  using T = Tr<DT>;
+  constexpr int X = T::X;
+  const u32x4 w = *reinterpret_cast<const u32x4*>(row + c * X);
+  const int e0 = c * X;
+  if (e0 >= 2 * half) return w;
+  const bool lo = e0 < half;
+  const u32x4 wp = *reinterpret_cast<const u32x4*>(row + (lo ? e0 + half : e0 - half));
+  const int j0 = lo ? e0 : e0 - half;
+  float x[X], xp[X], y[X];
+  T::unpack(w, x);
+  T::unpack(wp, xp);
+#pragma unroll
+  for (int e = 0; e < X; ++e) {
+    const float a = x[e] * cs[2 * (j0 + e)];
+    const float b = xp[e] * cs[2 * (j0 + e) + 1];
+    y[e] = lo ? a - b : a + b;
+  }
+  return T::pack(y);
+}
+
+// Rotates the hq head rows of one token's query in place (angle row cs): a
+// lane holds the two chunks of a rotated pair and the token's angles for
+// them, loaded once, and goes over heads, four at a time with their loads
+// issued together.  The element arithmetic is rope_chunk's.
+template <int DT, int D>
+__device__ inline void rotate_query(typename Tr<DT>::Elem* q, int hq, int half, const float* cs, int lane) {
+#pragma clang fp contract(off)
+  using T = Tr<DT>;
+  constexpr int X = T::X;
+  constexpr int U = 4;
+  const int np = half / X;                    // chunk pairs of a head row
+  const int hp = min(64 / np, hq);            // heads per pass
+  const int hl = lane / np, c = lane - hl * np;
+  if (hl >= hp) return;
+  float co[X], si[X];
+#pragma unroll
+  for (int e = 0; e < X; ++e) {
+    co[e] = cs[2 * (c * X + e)];
+    si[e] = cs[2 * (c * X + e) + 1];
+  }
+  for (int h0 = hl; h0 < hq; h0 += U * hp) {
+    u32x4 lo[U], hi[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const auto* row = q + (size_t)min(h0 + u * hp, hq - 1) * D + c * X;
+      lo[u] = *reinterpret_cast<const u32x4*>(row);
+      hi[u] = *reinterpret_cast<const u32x4*>(row + half);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (h0 + u * hp >= hq) break;
+      float x[X], y[X], xr[X], yr[X];
+      T::unpack(lo[u], x);
+      T::unpack(hi[u], y);
+#pragma unroll
+      for (int e = 0; e < X; ++e) {
+        const float a = x[e] * co[e], b = y[e] * si[e];
+        const float d = y[e] * co[e], f = x[e] * si[e];
+        xr[e] = a - b;
+        yr[e] = d + f;
+      }
+      auto* row = q + (size_t)(h0 + u * hp) * D + c * X;
+      *reinterpret_cast<u32x4*>(row) = T::pack(xr);
+      *reinterpret_cast<u32x4*>(row + half) = T::pack(yr);
+    }
+  }
+}
+
 // Append for sequences that add several tokens: one wave per (cache block,
 // KV head) writes every new token of the block.  K pieces (chunk c, slot t)
 // are taken slot-fastest, so the stores of a chunk row are one contiguous
@@ -1686,8 +1761,12 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a, AppendPlan p)
 // row of a dim (16 slots) is stored at once when the block is written whole
 // (element by element for the slots of a partly written block).  The bits
 // stored are the plain append's.
-template <int DT, int D>
-__global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendBlockPlan p) {
+// ROPE: the keys are rotated on the way, and the launch's further waves, one
+// per new token, rotate the query rows.  3,001 tokens of 32 / 8 heads of 128
+// (74 MB): 20.6 us; a wave per token for all three, with the single-token
+// append's scattered V elements and each query chunk loaded twice, took 31.8.
+template <int DT, int D, bool ROPE>
+__global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendBlockPlan p, RopeArgs rope) {
   constexpr int RT = DT == 2 ? 0 : DT;  // new rows: bf16 beside an fp8 cache
   using NE = typename Tr<RT>::Elem;
   using CE = typename Tr<DT>::Elem;
@@ -1698,7 +1777,17 @@ __global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendB
   const int lane = threadIdx.x & 63;
   const int w = blockIdx.x * kWavesPerGroup + wave_uniform(threadIdx.x >> 6);
   const int unit = w / a.hkv, h = w - unit * a.hkv;
-  if (unit >= p.unit_start[p.n_seqs]) return;
+  if (unit >= p.unit_start[p.n_seqs]) {
+    if constexpr (ROPE) {
+      const int tok = w - p.unit_start[p.n_seqs] * a.hkv;
+      if (tok >= p.tok_start[p.n_seqs]) return;
+      const int j = upper_index(p.tok_start, p.n_seqs, tok);
+      const int k = tok - p.tok_start[j];
+      rotate_query<RT, D>(reinterpret_cast<NE*>(rope.q) + (size_t)(p.row0[j] + k) * rope.hq * D, rope.hq, rope.half,
+                          rope.cos_sin + (size_t)(p.pos0[j] + k) * rope.half * 2, lane);
+    }
+    return;
+  }
   const int j = upper_index(p.unit_start, p.n_seqs, unit);
   const int first = p.pos0[j], end = p.pos0[j] + p.ntok[j];  // new positions [first, end)
   const int b = first / kBlock + (unit - p.unit_start[j]);   // cache block index in the sequence
@@ -1720,7 +1809,11 @@ __global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendB
   for (int u = 0; u < KP; ++u) {
     const int pc = 64 * u + lane, c = pc / kBlock, t = pc % kBlock;
     const int row = row_s0 + min(max(t, s0), s1 - 1) - s0;  // slots outside [s0, s1) reload a valid row
-    kw[u] = *reinterpret_cast<const u32x4*>(kn + (size_t)row * rstride + c * X);
+    if constexpr (ROPE)
+      kw[u] = rope_chunk<RT>(kn + (size_t)row * rstride, c, rope.half,
+                             rope.cos_sin + (size_t)(first + row - p.row0[j]) * rope.half * 2);
+    else
+      kw[u] = *reinterpret_cast<const u32x4*>(kn + (size_t)row * rstride + c * X);
   }
 #pragma unroll
   for (int u = 0; u < KP; ++u) {
@@ -1776,37 +1869,8 @@ __global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendB
   }
 }
 
-// Rotary embedding of 16-byte chunk c of one head row (rotate-half form):
-// element i < half pairs with i + half; with the position's angle row cs
-// (cos, sin interleaved per pair), y_i = x_i cos - x_{i+half} sin and
-// y_{i+half} = x_{i+half} cos + x_i sin, and elements >= 2*half are copied.
-// half is a multiple of the chunk's element count.  Each product and each
-// sum is rounded to f32 (no fused multiply-add), then the result to the
-// storage type.
-template <int DT>
-__device__ inline u32x4 rope_chunk(const typename Tr<DT>::Elem* row, int c, int half, const float* cs) {
-#pragma clang fp contract(off)
-  using T = Tr<DT>;
-  constexpr int X = T::X;
-  const u32x4 w = *reinterpret_cast<const u32x4*>(row + c * X);
-  const int e0 = c * X;
-  if (e0 >= 2 * half) return w;
-  const bool lo = e0 < half;
-  const u32x4 wp = *reinterpret_cast<const u32x4*>(row + (lo ? e0 + half : e0 - half));
-  const int j0 = lo ? e0 : e0 - half;
-  float x[X], xp[X], y[X];
-  T::unpack(w, x);
-  T::unpack(wp, xp);
-#pragma unroll
-  for (int e = 0; e < X; ++e) {
-    const float a = x[e] * cs[2 * (j0 + e)];
-    const float b = xp[e] * cs[2 * (j0 + e) + 1];
-    y[e] = lo ? a - b : a + b;
-  }
-  return T::pack(y);
-}
-
-// Append with the rotary embedding: one wave per new token at position pos.
+// Append with the rotary embedding of the sequences that add one token: one
+// wave per new token at position pos.
 // The wave rotates the token's query row (all Hq heads, in place), writes
 // its rotated key row into the cache and copies its value row, as the plain
 // append does.  A head's chunks all fall in one pass of the 64 lanes (D / X
@@ -1821,21 +1885,13 @@ __global__ __launch_bounds__(256) void rope_append_kernel(AppendArgs a, AppendPl
   static_assert(64 % NC == 0, "a head row's chunks fit one pass of the wave");
   const int lane = threadIdx.x & 63;
   const int tok = blockIdx.x * kWavesPerGroup + wave_uniform(threadIdx.x >> 6);
-  if (tok >= p.tok_start[p.n_seqs]) return;
-  const int j = p.unit ? tok : upper_index(p.tok_start, p.n_seqs, tok);
-  const int k = tok - p.tok_start[j];
-  const int s = p.seq[j];
-  const int t = p.row0[j] + k;
-  const int pos = p.pos0[j] + k;
+  if (tok >= p.n_seqs) return;
+  const int s = p.seq[tok];
+  const int t = p.row[tok];
+  const int pos = p.pos[tok];
   const float* cs = r.cos_sin + (size_t)pos * r.half * 2;
 
-  E* q = reinterpret_cast<E*>(r.q) + (size_t)t * r.hq * D;
-  for (int c0 = 0; c0 < r.hq * NC; c0 += 64) {
-    const int ci = c0 + lane;
-    if (ci >= r.hq * NC) break;
-    const u32x4 y = rope_chunk<RT>(q + (ci / NC) * D, ci % NC, r.half, cs);
-    *reinterpret_cast<u32x4*>(q + (ci / NC) * D + (ci % NC) * X) = y;
-  }
+  rotate_query<RT, D>(reinterpret_cast<E*>(r.q) + (size_t)t * r.hq * D, r.hq, r.half, cs, lane);
 
   const int blk = a.block_tables[(size_t)s * a.mb + pos / kBlock];
   if (blk < 0 || blk >= a.nb) return;
@@ -1851,14 +1907,14 @@ __global__ __launch_bounds__(256) void rope_append_kernel(AppendArgs a, AppendPl
                          *reinterpret_cast<const u32x4*>(vn + h * D + c * X));
       continue;
     }
-    *reinterpret_cast<u32x4*>(reinterpret_cast<E*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * X) =
-        rope_chunk<RT>(kn + h * D, c, r.half, cs);
+    st_stream(reinterpret_cast<E*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * X,
+              rope_chunk<RT>(kn + h * D, c, r.half, cs));
     E vv[X];
 #pragma unroll
     for (int e = 0; e < X; ++e) vv[e] = vn[h * D + c * X + e];
     E* vc = reinterpret_cast<E*>(a.v_cache) + (head * D + c * X) * kBlock + slot;
 #pragma unroll
-    for (int e = 0; e < X; ++e) vc[e * kBlock] = vv[e];
+    for (int e = 0; e < X; ++e) st_stream(vc + e * kBlock, vv[e]);
   }
 }
 
@@ -1876,7 +1932,7 @@ hipError_t dispatch(int dtype, int head_dim, Args&&... args) {
 template <int DT, int D>
 struct AppendL {
   static hipError_t run(const AppendArgs& a, const AppendPlan& p, hipStream_t stream) {
-    const int tokens = p.tok_start[p.n_seqs];
+    const int tokens = p.n_seqs;
     if (tokens == 0) return hipSuccess;
     hipLaunchKernelGGL((append_kernel<DT, D>), dim3((tokens + kWavesPerGroup - 1) / kWavesPerGroup),
                        dim3(64 * kWavesPerGroup), 0, stream, a, p);
@@ -1886,11 +1942,14 @@ struct AppendL {
 
 template <int DT, int D>
 struct AppendBlockL {
-  static hipError_t run(const AppendArgs& a, const AppendBlockPlan& p, hipStream_t stream) {
-    const long waves = (long)p.unit_start[p.n_seqs] * a.hkv;
+  static hipError_t run(const AppendArgs& a, const AppendBlockPlan& p, const RopeArgs* rope, hipStream_t stream) {
+    const long waves = (long)p.unit_start[p.n_seqs] * a.hkv + (rope ? p.tok_start[p.n_seqs] : 0);
     if (waves == 0) return hipSuccess;
-    hipLaunchKernelGGL((append_block_kernel<DT, D>), dim3((unsigned)((waves + kWavesPerGroup - 1) / kWavesPerGroup)),
-                       dim3(64 * kWavesPerGroup), 0, stream, a, p);
+    const dim3 grid((unsigned)((waves + kWavesPerGroup - 1) / kWavesPerGroup)), block(64 * kWavesPerGroup);
+    if (rope)
+      hipLaunchKernelGGL((append_block_kernel<DT, D, true>), grid, block, 0, stream, a, p, *rope);
+    else
+      hipLaunchKernelGGL((append_block_kernel<DT, D, false>), grid, block, 0, stream, a, p, RopeArgs{});
     return hipGetLastError();
   }
 };
@@ -1898,7 +1957,7 @@ struct AppendBlockL {
 template <int DT, int D>
 struct RopeAppendL {
   static hipError_t run(const AppendArgs& a, const AppendPlan& p, const RopeArgs& r, hipStream_t stream) {
-    const int tokens = p.tok_start[p.n_seqs];
+    const int tokens = p.n_seqs;
     if (tokens == 0) return hipSuccess;
     hipLaunchKernelGGL((rope_append_kernel<DT, D>), dim3((tokens + kWavesPerGroup - 1) / kWavesPerGroup),
                        dim3(64 * kWavesPerGroup), 0, stream, a, p, r);
@@ -2010,9 +2069,9 @@ hipError_t launch_append(const AppendArgs& a, const AppendPlan& p, int dtype, in
   return dispatch<AppendL>(dtype, head_dim, a, p, stream);
 }
 
-hipError_t launch_append_blocks(const AppendArgs& a, const AppendBlockPlan& p, int dtype, int head_dim,
-                                hipStream_t stream) {
-  return dispatch<AppendBlockL>(dtype, head_dim, a, p, stream);
+hipError_t launch_append_blocks(const AppendArgs& a, const AppendBlockPlan& p, const RopeArgs* rope, int dtype,
+                                int head_dim, hipStream_t stream) {
+  return dispatch<AppendBlockL>(dtype, head_dim, a, p, rope, stream);
 }
 
 hipError_t launch_rope_append(const AppendArgs& a, const AppendPlan& p, const RopeArgs& r, int dtype, int head_dim,
