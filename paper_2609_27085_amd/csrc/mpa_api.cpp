@@ -9,9 +9,7 @@
 #include <string.h>
 
 #include <algorithm>
-#include <functional>
 #include <mutex>
-#include <queue>
 #include <unordered_set>
 #include <vector>
 
@@ -157,7 +155,13 @@ int choose_split(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens) {
   const long overhead = 64;
   long best_cost = -1;
   int best = 1024;
+  long tokens = 0;
+  for (int s : b.decode) tokens += seq_lens[s];
   for (int split = 128; split <= 1024; split += kBlock) {
+    // no split makes fewer parts than this many, so most splits are ruled out
+    // without a pass over the rows
+    const long fewest = std::max((long)b.decode.size(), (tokens + split - 1) / split) * sh->num_kv_heads;
+    if (best_cost >= 0 && (fewest + slots - 1) / slots * (split + overhead) >= best_cost) continue;
     long items = 0;
     for (int s : b.decode) items += row_split(seq_lens[s], split).parts;
     const long waves = items * sh->num_kv_heads;
@@ -291,22 +295,52 @@ std::vector<PrefillSplit> split_layout(const Batch& b, const int32_t* seq_lens, 
   return out;
 }
 
+// The makespan of jobs dealt in order, each `copies` times over, to `slots`
+// slots that take the next job when free.  When the copies divide the slots
+// the schedule is that many times the same one, so one is simulated.
+double list_makespan(const std::vector<double>& jobs, int copies, int slots) {
+  if (slots % copies == 0) {
+    slots /= copies;
+    copies = 1;
+  }
+  if ((long)jobs.size() * copies <= slots) return jobs.empty() ? 0.0 : *std::max_element(jobs.begin(), jobs.end());
+  std::vector<double> heap((size_t)slots, 0.0);  // when each slot is free, least first
+  double makespan = 0.0;
+  for (double job : jobs)
+    for (int c = 0; c < copies; ++c) {
+      const double end = heap[0] + job;
+      makespan = std::max(makespan, end);
+      size_t i = 0;
+      for (;;) {  // the first slot is free at `end`: sift it down
+        size_t k = 2 * i + 1;
+        if (k >= heap.size()) break;
+        if (k + 1 < heap.size() && heap[k + 1] < heap[k]) ++k;
+        if (heap[k] >= end) break;
+        heap[i] = heap[k];
+        i = k;
+      }
+      heap[i] = end;
+    }
+  return makespan;
+}
+
 // Predicted device time of the prefill launches for a split layout: per
 // launch (kMaxPrefillSeqs chunks), the makespan of its workgroups -- each
 // wg_us + tile_us per 64-key tile -- dealt in launch order (the longest
 // query tiles first) to `slots` slots that take the next workgroup when
 // free; plus, when a chunk of the launch is split, the merge: merge_us +
-// merge_row_us per partial (token, q head, split) row.
+// merge_row_us per partial (token, q head, split) row.  A launch whose time
+// cannot be below `cutoff` may be given its lower bound instead.
 double prefill_time(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, const int32_t* qsl,
                     const std::vector<PrefillSplit>& sp, double wg_us, double tile_us, int slots, double merge_us,
-                    double merge_row_us) {
+                    double merge_row_us, double cutoff = INFINITY) {
   const int qt = q_tile(sh);
   double total = 0.0;
-  std::vector<int> tiles;
+  std::vector<double> jobs;
   for (size_t c0 = 0; c0 < b.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
     const size_t c1 = std::min(b.prefill.size(), c0 + mpa::kMaxPrefillSeqs);
-    tiles.clear();  // 64-key tiles of each work unit, in unit order
-    double partial_rows = 0.0;
+    jobs.clear();  // the work units' times, in unit order
+    double partial_rows = 0.0, work = 0.0, shortest = INFINITY;
     for (size_t k = c0; k < c1; ++k) {
       const int s = b.prefill[k];
       const int C = qsl[s + 1] - qsl[s];
@@ -315,22 +349,18 @@ double prefill_time(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens
       for (int q = 0; q < (C + qt - 1) / qt; ++q) {
         const int kend = P + std::min(q * qt + qt - 1, C - 1) + 1;
         const int all = (kend + 63) / 64;
-        for (int x = 0; x < sp[k].nsplit; ++x)
-          tiles.push_back(x == sp[k].nsplit - 1 ? all - x * sp[k].tiles : sp[k].tiles);
+        for (int x = 0; x < sp[k].nsplit; ++x) {
+          jobs.push_back(wg_us + tile_us * (x == sp[k].nsplit - 1 ? all - x * sp[k].tiles : sp[k].tiles));
+          work += jobs.back();
+          shortest = std::min(shortest, jobs.back());
+        }
       }
     }
-    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
-    for (int i = 0; i < slots; ++i) free_at.push(0.0);
-    double makespan = 0.0;
-    // blockIdx order: the last unit first, each unit once per KV head
-    for (size_t u = tiles.size(); u-- > 0;)
-      for (int g = 0; g < sh->num_kv_heads; ++g) {
-        const double end = free_at.top() + wg_us + tile_us * tiles[u];
-        free_at.pop();
-        makespan = std::max(makespan, end);
-        free_at.push(end);
-      }
-    total += makespan + (partial_rows > 0 ? merge_us + merge_row_us * partial_rows : 0.0);
+    std::reverse(jobs.begin(), jobs.end());  // blockIdx order: the last unit first, each unit once per KV head
+    const double merge = partial_rows > 0 ? merge_us + merge_row_us * partial_rows : 0.0;
+    const long units = (long)jobs.size() * sh->num_kv_heads;
+    const double bound = std::max(work * sh->num_kv_heads / slots, (units + slots - 1) / slots * shortest);
+    total += (units && bound + merge >= cutoff ? bound : list_makespan(jobs, sh->num_kv_heads, slots)) + merge;
   }
   return total;
 }
@@ -360,12 +390,12 @@ std::vector<PrefillSplit> prefill_splits(const mpa_shape* sh, const Batch& b, co
   long units;
   int most;  // the most splits any chunk can take
   prefill_units(sh, b.prefill, seq_lens, qsl, &units, &most);
-  double best_t = -1.0;
+  double best_t = INFINITY;
   int best = 1;
   for (int want = 1; want <= most && (want == 1 || units * want <= 8L * mpa::kPrefillSplitTarget); ++want) {
     const double t = prefill_time(sh, b, seq_lens, qsl, split_layout(b, seq_lens, qsl, want, 0), kPlanWgUs,
-                                  kPlanTileUs, mpa::kPrefillSplitTarget, kPlanMergeUs, kPlanMergeRowUs);
-    if (best_t < 0 || t < best_t * (1.0 - 1e-9)) {
+                                  kPlanTileUs, mpa::kPrefillSplitTarget, kPlanMergeUs, kPlanMergeRowUs, best_t);
+    if (t < best_t * (1.0 - 1e-9)) {
       best_t = t;
       best = want;
     }
