@@ -23,7 +23,7 @@ constexpr int kMaskWords = 8;  // CU-mask words: devices of up to 256 CUs
 
 struct Batch {
   std::vector<int> decode;   // sequence ids with q_len == 1
-  std::vector<int> prefill;  // sequence ids with q_len > 1, in launch order
+  std::vector<int> prefill;  // sequence ids with q_len > 1
 };
 
 int check_shape(const mpa_shape* sh) {
@@ -56,17 +56,11 @@ void prefill_units(const mpa_shape* sh, const std::vector<int>& prefill, const i
   }
 }
 
-// Whether the planner leaves every prefill chunk of the batch whole (one KV
-// split each): f32 chunks, and MFMA batches with at least two workgroups
-// per CU or no prefix long enough to split, unless MPA_PREFILL_SPLITS
-// overrides the choice.  prefill_splits() takes the same decision.
+// Whether the planner starts from whole chunks (one KV split each): MFMA
+// batches with at least two workgroups per CU or no prefix long enough to
+// split.
 bool prefill_whole(const mpa_shape* sh, const std::vector<int>& prefill, const int32_t* seq_lens,
                    const int32_t* qsl) {
-  if (sh->dtype == MPA_F32 || prefill.empty()) return true;
-  if (const char* env = getenv("MPA_PREFILL_SPLITS")) {
-    const int v = atoi(env);
-    if (v >= 1 && v <= 64) return false;
-  }
   long units;
   int most;
   prefill_units(sh, prefill, seq_lens, qsl, &units, &most);
@@ -102,20 +96,13 @@ int check_batch(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl
 }
 
 // The sequences of a valid batch by kind.
-Batch classify(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl) {
+Batch classify(const mpa_shape* sh, const int32_t* qsl) {
   Batch b;
   for (int s = 0; s < sh->num_seqs; ++s) {
     const int ql = qsl[s + 1] - qsl[s];
     if (ql == 1) b.decode.push_back(s);
     if (ql > 1) b.prefill.push_back(s);
   }
-  // The MFMA prefill kernel dispatches its work units from the plan's last
-  // chunk backwards, each chunk from its longest query tile (the one that
-  // sees all L keys).  With whole chunks ordered by L, the longest units go
-  // first and the short ones fill the end of the launch.  A split chunk's
-  // units are not ordered by length, so split batches keep batch order.
-  if (sh->dtype != MPA_F32 && b.prefill.size() > 1 && prefill_whole(sh, b.prefill, seq_lens, qsl))
-    std::stable_sort(b.prefill.begin(), b.prefill.end(), [&](int x, int y) { return seq_lens[x] < seq_lens[y]; });
   return b;
 }
 
@@ -263,34 +250,38 @@ size_t workspace_bytes(const mpa_shape* sh, long items) {
   return items * per;
 }
 
-// KV splits of the prefill chunks.  A chunk's query tiles times the KV heads
-// are its workgroups, and each workgroup holds a whole CU.  With `want`
-// splits, each chunk's cached prefix is divided among up to `want` parts of
-// kPrefillMinSplitTiles 64-key tiles or more; the last split also takes the
-// chunk's own keys (and the causal diagonal), so every split holds keys of
-// every row.  bf16 and fp8 caches (the MFMA kernel); f32 chunks are not
-// split.
-struct PrefillSplit {
+// The prefill work, in launch order: each segment is tokens [tok0, tok0 +
+// ntok) of a chunk (whole query tiles, or the chunk's rest) in nsplit KV
+// splits.  A segment's query tiles times its splits and the KV heads are its
+// workgroups, and each workgroup holds a whole CU.  With several splits the
+// cached prefix is divided into parts of kPrefillMinSplitTiles 64-key tiles
+// or more; the last split also takes the chunk's own keys (and the causal
+// diagonal), so every split holds keys of every row.  bf16 and fp8 caches (the
+// MFMA kernel); f32 chunks are not split.
+struct PrefillSegment {
+  int seq = 0, tok0 = 0, ntok = 0;
   int nsplit = 1;
   int tiles = 0;        // 64-key tiles of every split but the last
-  long item_base = 0;   // first workspace slot of the chunk's partials
+  long item_base = 0;   // first workspace slot of its partials
 };
 
-std::vector<PrefillSplit> split_layout(const Batch& b, const int32_t* seq_lens, const int32_t* qsl, int want,
-                                       long first_item) {
-  std::vector<PrefillSplit> out(b.prefill.size());
-  long item = first_item;
+// `want` splits, or as many as the prefix of `prefix` keys allows.
+void split_segment(PrefillSegment* g, int prefix, int want) {
+  const int np = prefix / 64;  // whole 64-key tiles of the prefix
+  const int ct = (g->ntok + 63) / 64;
+  const int n = std::min({want, 1 + np / mpa::kPrefillMinSplitTiles, 64});
+  g->nsplit = std::max(1, n);
+  g->tiles = n < 2 ? 0 : std::min((np + ct + n - 1) / n, np / (n - 1));
+}
+
+// Every chunk whole or in up to `want` splits, in batch order.
+std::vector<PrefillSegment> split_layout(const Batch& b, const int32_t* seq_lens, const int32_t* qsl, int want) {
+  std::vector<PrefillSegment> out(b.prefill.size());
   for (size_t k = 0; k < b.prefill.size(); ++k) {
     const int s = b.prefill[k];
-    const int C = qsl[s + 1] - qsl[s];
-    const int np = (seq_lens[s] - C) / 64;  // whole 64-key tiles of the prefix
-    const int ct = (C + 63) / 64;
-    const int n = std::min({want, 1 + np / mpa::kPrefillMinSplitTiles, 64});
-    if (n < 2) continue;
-    out[k].nsplit = n;
-    out[k].tiles = std::min((np + ct + n - 1) / n, np / (n - 1));
-    out[k].item_base = item;
-    item += (long)n * C;
+    out[k].seq = s;
+    out[k].ntok = qsl[s + 1] - qsl[s];
+    split_segment(&out[k], seq_lens[s] - out[k].ntok, want);
   }
   return out;
 }
@@ -331,31 +322,33 @@ double list_makespan(const std::vector<double>& jobs, int copies, int slots) {
 // free; plus, when a chunk of the launch is split, the merge: merge_us +
 // merge_row_us per partial (token, q head, split) row.  A launch whose time
 // cannot be below `cutoff` may be given its lower bound instead.
-double prefill_time(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, const int32_t* qsl,
-                    const std::vector<PrefillSplit>& sp, double wg_us, double tile_us, int slots, double merge_us,
-                    double merge_row_us, double cutoff = INFINITY) {
+// `work_us` (may be null) takes the work of all slots.
+double prefill_time(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl,
+                    const std::vector<PrefillSegment>& segments, double wg_us, double tile_us, int slots,
+                    double merge_us, double merge_row_us, double cutoff = INFINITY, double* work_us = nullptr) {
   const int qt = q_tile(sh);
   double total = 0.0;
   std::vector<double> jobs;
-  for (size_t c0 = 0; c0 < b.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
-    const size_t c1 = std::min(b.prefill.size(), c0 + mpa::kMaxPrefillSeqs);
+  if (work_us) *work_us = 0.0;
+  for (size_t c0 = 0; c0 < segments.size(); c0 += mpa::kMaxPrefillSeqs) {
+    const size_t c1 = std::min(segments.size(), c0 + mpa::kMaxPrefillSeqs);
     jobs.clear();  // the work units' times, in unit order
     double partial_rows = 0.0, work = 0.0, shortest = INFINITY;
     for (size_t k = c0; k < c1; ++k) {
-      const int s = b.prefill[k];
-      const int C = qsl[s + 1] - qsl[s];
-      const int P = seq_lens[s] - C;
-      if (sp[k].nsplit > 1) partial_rows += (double)C * sh->num_q_heads * sp[k].nsplit;
-      for (int q = 0; q < (C + qt - 1) / qt; ++q) {
-        const int kend = P + std::min(q * qt + qt - 1, C - 1) + 1;
+      const PrefillSegment& g = segments[k];
+      const int P = seq_lens[g.seq] - (qsl[g.seq + 1] - qsl[g.seq]) + g.tok0;  // keys before the segment
+      if (g.nsplit > 1) partial_rows += (double)g.ntok * sh->num_q_heads * g.nsplit;
+      for (int q = 0; q < (g.ntok + qt - 1) / qt; ++q) {
+        const int kend = P + std::min(q * qt + qt - 1, g.ntok - 1) + 1;
         const int all = (kend + 63) / 64;
-        for (int x = 0; x < sp[k].nsplit; ++x) {
-          jobs.push_back(wg_us + tile_us * (x == sp[k].nsplit - 1 ? all - x * sp[k].tiles : sp[k].tiles));
+        for (int x = 0; x < g.nsplit; ++x) {
+          jobs.push_back(wg_us + tile_us * (x == g.nsplit - 1 ? all - x * g.tiles : g.tiles));
           work += jobs.back();
           shortest = std::min(shortest, jobs.back());
         }
       }
     }
+    if (work_us) *work_us += work * sh->num_kv_heads;
     std::reverse(jobs.begin(), jobs.end());  // blockIdx order: the last unit first, each unit once per KV head
     const double merge = partial_rows > 0 ? merge_us + merge_row_us * partial_rows : 0.0;
     const long units = (long)jobs.size() * sh->num_kv_heads;
@@ -371,42 +364,127 @@ constexpr double kPlanWgUs = 18.0;
 constexpr double kPlanTileUs = 1.85;
 constexpr double kPlanMergeUs = 3.0;
 constexpr double kPlanMergeRowUs = 1.6e-4;
+// Balancing a launch that fills the device: what a partial row costs there
+// beside the merge (its units store 4 bytes an element, not 2, and run more
+// often), fitted to 22 batches of 200-4,000 us; without it the five batches
+// whose every chunk was cut in two came out 1-8 % slower than predicted even.
+constexpr double kPlanBalanceRowUs = 5e-4;
 
-// The split count.  A batch with at least two workgroups per CU is not
-// split: its makespan is already close to its work over the CUs, and the
-// partial results would cost more than they balance.  A smaller batch gets
-// the split count (1, 2, ...) with the shortest predicted prefill time,
-// the fewer splits on a tie; counts past the point where every chunk's
-// prefix is cut as finely as allowed, or past 8 workgroups per CU, are not
-// tried.  MPA_PREFILL_SPLITS (1..64) overrides the choice for tuning sweeps.
-std::vector<PrefillSplit> prefill_splits(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens,
-                                         const int32_t* qsl, long first_item) {
-  if (sh->dtype == MPA_F32 || b.prefill.empty()) return std::vector<PrefillSplit>(b.prefill.size());
+// The segments (without their workspace slots).
+//
+// A batch with fewer than two workgroups per CU gets the split count (1, 2,
+// ...), for all its chunks, with the shortest predicted prefill time, the
+// fewer splits on a tie; counts past the point where every chunk's prefix is
+// cut as finely as allowed, or past 8 workgroups per CU, are not tried.
+//
+// A larger one keeps its chunks whole where their makespan is close to the
+// work over the CUs.  The kernel dispatches its units from the last segment
+// backwards, each from its longest query tile (the one that sees the most
+// keys), so segments are ordered by their longest unit: the longest go first
+// and the short ones fill the end of the launch.  Where that leaves more than
+// 3 % of the launch idle, chunks whose units are long against a CU's share
+// are split (to shares of 1/1.5, 1/2 or 1/3), and then the first query tiles
+// of the last segment to run (a quarter of a round of them in 4 splits, or a
+// round in 3), whichever is predicted shortest.  Measured on 22 batches of up
+// to 4 chunks (us, whole chunks -> this): 3,025 tokens on 613 keys and 439 on
+// 35,613 789 -> 659, 6,291 on 15,587 (tail) 3,409 -> 3,166, 2,490 / 1,215 / 423
+// on 0 / 1,850 / 36,264 (fp8, d 64) 649 -> 264; none more than 1 % slower.
+// With `balance` false only the order is chosen.
+// MPA_PREFILL_SPLITS (1..64) overrides the choice for tuning sweeps.
+std::vector<PrefillSegment> prefill_segments(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens,
+                                             const int32_t* qsl, bool balance) {
+  std::vector<PrefillSegment> best = split_layout(b, seq_lens, qsl, 1);
+  if (sh->dtype == MPA_F32 || b.prefill.empty()) return best;
   if (const char* env = getenv("MPA_PREFILL_SPLITS")) {
     const int v = atoi(env);
-    if (v >= 1 && v <= 64) return split_layout(b, seq_lens, qsl, v, first_item);
+    if (v >= 1 && v <= 64) return split_layout(b, seq_lens, qsl, v);
   }
-  if (prefill_whole(sh, b.prefill, seq_lens, qsl)) return std::vector<PrefillSplit>(b.prefill.size());
+  const int slots = mpa::kPrefillSplitTarget;
+  double row_us = kPlanMergeRowUs, margin = 1e-9;
+  auto time = [&](const std::vector<PrefillSegment>& v, double cutoff, double* work = nullptr) {
+    return prefill_time(sh, seq_lens, qsl, v, kPlanWgUs, kPlanTileUs, slots, kPlanMergeUs, row_us, cutoff, work);
+  };
+  double best_t = INFINITY;
+  auto take_if_shorter = [&](std::vector<PrefillSegment>& v) {
+    const double t = time(v, best_t);
+    if (t < best_t * (1.0 - margin)) {
+      best_t = t;
+      best = v;
+    }
+  };
   long units;
   int most;  // the most splits any chunk can take
   prefill_units(sh, b.prefill, seq_lens, qsl, &units, &most);
-  double best_t = INFINITY;
-  int best = 1;
-  for (int want = 1; want <= most && (want == 1 || units * want <= 8L * mpa::kPrefillSplitTarget); ++want) {
-    const double t = prefill_time(sh, b, seq_lens, qsl, split_layout(b, seq_lens, qsl, want, 0), kPlanWgUs,
-                                  kPlanTileUs, mpa::kPrefillSplitTarget, kPlanMergeUs, kPlanMergeRowUs, best_t);
-    if (t < best_t * (1.0 - 1e-9)) {
-      best_t = t;
-      best = want;
+  if (!prefill_whole(sh, b.prefill, seq_lens, qsl)) {
+    for (int want = 1; want <= most && (want == 1 || units * want <= 8L * slots); ++want) {
+      std::vector<PrefillSegment> v = split_layout(b, seq_lens, qsl, want);
+      take_if_shorter(v);
     }
+    return best;
   }
-  return split_layout(b, seq_lens, qsl, best, first_item);
+  auto prefix = [&](const PrefillSegment& g) { return seq_lens[g.seq] - (qsl[g.seq + 1] - qsl[g.seq]) + g.tok0; };
+  auto longest = [&](const PrefillSegment& g) {  // tiles of the segment's longest unit
+    const int all = (prefix(g) + g.ntok + 63) / 64;
+    return std::max(g.tiles, all - (g.nsplit - 1) * g.tiles);
+  };
+  auto order = [&](std::vector<PrefillSegment>& v) {
+    std::stable_sort(v.begin(), v.end(), [&](const PrefillSegment& x, const PrefillSegment& y) {
+      return longest(x) != longest(y) ? longest(x) < longest(y) : seq_lens[x.seq] < seq_lens[y.seq];
+    });
+  };
+  order(best);
+  if (!balance || most == 1 || units < 2L * slots || best.size() >= (size_t)mpa::kMaxPrefillSeqs) return best;
+  double work;
+  row_us = kPlanBalanceRowUs;
+  margin = 0.04;  // of the prediction, which was up to 9 % low on the batches above
+  best_t = time(best, INFINITY, &work);
+  const double share = work / slots;
+  if (best_t < 1.03 * share) return best;
+  const std::vector<PrefillSegment> whole = best;
+  for (double parts : {1.5, 2.0, 3.0}) {
+    std::vector<PrefillSegment> v = whole;
+    bool any = false;
+    for (PrefillSegment& g : v) {
+      const double unit = kPlanTileUs * ((prefix(g) + g.ntok + 63) / 64);
+      const int want = (int)std::min(16.0, ceil(unit * parts / share));
+      if (want > 1) split_segment(&g, prefix(g), want);
+      any |= g.nsplit > 1;
+    }
+    if (!any) continue;
+    order(v);
+    take_if_shorter(v);
+  }
+  if (best_t < 1.03 * share || best[0].nsplit > 1) return best;
+  margin = 0.01;  // few partial rows: within 3 %
+  const int qt = q_tile(sh);
+  const int round = std::max(1, slots / sh->num_kv_heads);  // query tiles of one round
+  const std::vector<PrefillSegment> from = best;
+  for (int n : {4, 3}) {
+    const int tail = std::max(1, n == 4 ? round / 4 : round);
+    PrefillSegment head = from[0];
+    PrefillSegment rest = head;
+    head.ntok = std::min(head.ntok, tail * qt);
+    rest.tok0 += head.ntok;
+    rest.ntok -= head.ntok;
+    split_segment(&head, prefix(head), n);
+    if (head.nsplit < 2) continue;
+    std::vector<PrefillSegment> v(1, head);
+    if (rest.ntok > 0) v.push_back(rest);
+    v.insert(v.end(), from.begin() + 1, from.end());
+    take_if_shorter(v);
+  }
+  return best;
 }
 
-long prefill_items(const std::vector<PrefillSplit>& sp, const Batch& b, const int32_t* qsl) {
+// Gives split segments their workspace slots, from first_item on; returns the
+// number of slots given.
+long assign_prefill_items(std::vector<PrefillSegment>* segments, long first_item) {
   long n = 0;
-  for (size_t k = 0; k < sp.size(); ++k)
-    if (sp[k].nsplit > 1) n += (long)sp[k].nsplit * (qsl[b.prefill[k] + 1] - qsl[b.prefill[k]]);
+  for (PrefillSegment& g : *segments)
+    if (g.nsplit > 1) {
+      g.item_base = first_item + n;
+      n += (long)g.nsplit * g.ntok;
+    }
   return n;
 }
 
@@ -416,14 +494,14 @@ struct StepPlan {
   Batch batch;
   int split = 0;  // nominal tokens per part of rows split on their own
   std::vector<DecodeLaunch> decode;
-  std::vector<PrefillSplit> prefill;  // of batch.prefill
+  std::vector<PrefillSegment> prefill;
   long items = 0;                     // workspace slots
   bool decode_split = false, prefill_split = false;  // some row / chunk has several parts
 };
 
 StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* qsl) {
   StepPlan p;
-  p.batch = classify(sh, seq_lens, qsl);
+  p.batch = classify(sh, qsl);
   auto total = [](const std::vector<DecodeLaunch>& v) {
     long n = 0;
     for (const auto& d : v) n += d.items;
@@ -436,21 +514,26 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
     p.split = choose_split(sh, p.batch, seq_lens);
     p.decode = decode_layout(sh, p.batch, seq_lens, p.split, true);
   }
-  long ditems = total(p.decode);
-  p.prefill = prefill_splits(sh, p.batch, seq_lens, qsl, ditems);
-  p.items = ditems + prefill_items(p.prefill, p.batch, qsl);
-  if (workspace_bytes(sh, p.items) > MPA_SCRATCH_BYTES && !getenv("MPA_DECODE_RANGE")) {
-    // Ranges cut every row, also short ones, so their partial results can
-    // take more room than those of row splits.  A step past the fixed array
-    // of mpa_append_attention_noalloc takes the smaller of the two.
-    const int split = choose_split(sh, p.batch, seq_lens);
-    const std::vector<DecodeLaunch> rows = decode_layout(sh, p.batch, seq_lens, split, false);
-    if (total(rows) < ditems) {
-      p.split = split;
-      p.decode = rows;
-      ditems = total(rows);
-      p.prefill = prefill_splits(sh, p.batch, seq_lens, qsl, ditems);
-      p.items = ditems + prefill_items(p.prefill, p.batch, qsl);
+  p.prefill = prefill_segments(sh, p.batch, seq_lens, qsl, true);
+  auto place = [&] {
+    const long ditems = total(p.decode);
+    p.items = ditems + assign_prefill_items(&p.prefill, ditems);
+    return workspace_bytes(sh, p.items) <= MPA_SCRATCH_BYTES;
+  };
+  if (!place() && !getenv("MPA_DECODE_RANGE")) {
+    // Ranges cut every row, also short ones, and balancing splits chunks, so
+    // their partial results can take more room than those of row splits and
+    // whole chunks.  A step past the fixed array of
+    // mpa_append_attention_noalloc does without them where that takes less.
+    p.prefill = prefill_segments(sh, p.batch, seq_lens, qsl, false);
+    if (!place()) {
+      const int split = choose_split(sh, p.batch, seq_lens);
+      const std::vector<DecodeLaunch> rows = decode_layout(sh, p.batch, seq_lens, split, false);
+      if (total(rows) < total(p.decode)) {
+        p.split = split;
+        p.decode = rows;
+        place();
+      }
     }
   }
   if (p.split == 0 && !p.decode.empty()) p.split = p.decode[0].range_blocks * kBlock;
@@ -557,7 +640,7 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
   a.inv_v_scale = shape->dtype == MPA_FP8 ? 1.f / shape->v_scale : 1.f;
   (void)seq_lens;
   (void)query_start_loc;
-  const Batch b = classify(shape, seq_lens_host, query_start_loc_host);
+  const Batch b = classify(shape, query_start_loc_host);
   clear_stale_hip_error();
   // multi-token sequences one wave per (cache block, KV head)
   for (size_t c0 = 0; c0 < b.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
@@ -651,7 +734,7 @@ mpa_step_time model_step(const mpa_shape* shape, const StepPlan& plan, const int
 
   // prefill: each launch's workgroups, in launch order (longest query tiles
   // first), on prefill_slots slots that take the next workgroup when free
-  t.prefill_us = prefill_time(shape, b, seq_lens_host, qsl_host, plan.prefill, r.prefill_wg_us, r.prefill_tile_us,
+  t.prefill_us = prefill_time(shape, seq_lens_host, qsl_host, plan.prefill, r.prefill_wg_us, r.prefill_tile_us,
                               r.prefill_slots, r.prefill_merge_us, r.prefill_merge_row_us);
   bool few = false;
   for (int s : b.prefill) few |= seq_lens_host[s] - (qsl_host[s + 1] - qsl_host[s]) < mpa::kFewKeys;
@@ -703,12 +786,10 @@ int mpa_get_plan_info(const mpa_shape* shape, const int32_t* seq_lens_host, cons
   for (const auto& d : plan.decode) info->num_decode_items += (int32_t)d.items;
   long tiles = 0;
   const int qt = q_tile(shape);
-  const std::vector<PrefillSplit>& ps = plan.prefill;
   int max_split = b.prefill.empty() ? 0 : 1;
-  for (size_t k = 0; k < b.prefill.size(); ++k) {
-    const int s = b.prefill[k];
-    tiles += (long)(qsl_host[s + 1] - qsl_host[s] + qt - 1) / qt * ps[k].nsplit;
-    max_split = std::max(max_split, ps[k].nsplit);
+  for (const PrefillSegment& g : plan.prefill) {
+    tiles += (long)(g.ntok + qt - 1) / qt * g.nsplit;
+    max_split = std::max(max_split, g.nsplit);
   }
   info->num_prefill_tiles = (int32_t)(tiles * shape->num_kv_heads);
   info->prefill_max_splits = max_split;
@@ -810,8 +891,7 @@ int mpa_plan_coexec(const mpa_shape* shape, const int32_t* seq_lens_host, const 
   // batch has few workgroups), times the per-CU speed measured on that share
   // (pfrac against the share itself), and never faster than alone on the
   // whole device.
-  const std::vector<PrefillSplit>& ps = plan.prefill;
-  const double all_slots = prefill_time(shape, b, seq_lens_host, qsl_host, ps, r.prefill_wg_us, r.prefill_tile_us,
+  const double all_slots = prefill_time(shape, seq_lens_host, qsl_host, plan.prefill, r.prefill_wg_us, r.prefill_tile_us,
                                         r.prefill_slots, 0.0, 0.0);
   for (int k = 1; k <= 3; ++k) {
     if (b.decode.empty() || b.prefill.empty()) {
@@ -820,7 +900,7 @@ int mpa_plan_coexec(const mpa_shape* shape, const int32_t* seq_lens_host, const 
     }
     const double share = (4 - k) / 4.0;
     const int slots = std::max(1, (int)lround(r.prefill_slots * share));
-    const double rounds = prefill_time(shape, b, seq_lens_host, qsl_host, ps, r.prefill_wg_us, r.prefill_tile_us,
+    const double rounds = prefill_time(shape, seq_lens_host, qsl_host, plan.prefill, r.prefill_wg_us, r.prefill_tile_us,
                                        slots, 0.0, 0.0) /
                           all_slots;
     const double prefill_k = serial.prefill_us * std::max(1.0, rounds * share / pfrac[k]);
@@ -991,32 +1071,29 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
     if (e == hipSuccess && d.split) e = mpa::launch_merge(a, p, shape->dtype, shape->head_dim, st);
     if (e != hipSuccess) return MPA_ERR_HIP;
   }
-  // Prefill chunks, in launches of up to kMaxPrefillSeqs; KV-split chunks are
+  // Prefill segments, in launches of up to kMaxPrefillSeqs; KV-split ones are
   // merged after their launch.
   const int qt = q_tile(shape);
-  const std::vector<int>& chunks = plan.batch.prefill;
-  for (size_t c0 = 0; prefill && c0 < chunks.size(); c0 += mpa::kMaxPrefillSeqs) {
+  for (size_t c0 = 0; prefill && c0 < plan.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
     mpa::PrefillPlan p;
-    memset(&p, 0, sizeof(p));
-    const size_t c1 = std::min(chunks.size(), c0 + mpa::kMaxPrefillSeqs);
-    p.n_seqs = (int32_t)(c1 - c0);
+    p.n_seqs = (int32_t)(std::min(plan.prefill.size(), c0 + mpa::kMaxPrefillSeqs) - c0);
     p.q_tile = qt;
     int acc = 0, rows = 0;
-    for (size_t k = c0; k < c1; ++k) {
-      const int s = chunks[k];
-      const int C = query_start_loc_host[s + 1] - query_start_loc_host[s];
-      const PrefillSplit& ps = plan.prefill[k];
-      p.seq[k - c0] = s;
-      p.tile_start[k - c0] = acc;
-      p.nsplit[k - c0] = ps.nsplit;
-      p.split_tiles[k - c0] = ps.tiles;
-      p.item_base[k - c0] = (int32_t)ps.item_base;
-      p.row_start[k - c0] = rows;
-      acc += (C + qt - 1) / qt * ps.nsplit;
-      if (ps.nsplit > 1) rows += C;
+    for (int k = 0; k < p.n_seqs; ++k) {
+      const PrefillSegment& g = plan.prefill[c0 + k];
+      p.seq[k] = g.seq;
+      p.tok0[k] = g.tok0;
+      p.ntok[k] = g.ntok;
+      p.tile_start[k] = acc;
+      p.nsplit[k] = g.nsplit;
+      p.split_tiles[k] = g.tiles;
+      p.item_base[k] = (int32_t)g.item_base;
+      p.row_start[k] = rows;
+      acc += (g.ntok + qt - 1) / qt * g.nsplit;
+      if (g.nsplit > 1) rows += g.ntok;
     }
-    p.tile_start[c1 - c0] = acc;
-    p.row_start[c1 - c0] = rows;
+    p.tile_start[p.n_seqs] = acc;
+    p.row_start[p.n_seqs] = rows;
     hipError_t e = mpa::launch_prefill(a, p, acc, shape->dtype, shape->head_dim, st);
     if (e != hipSuccess) return MPA_ERR_HIP;
     if (rows > 0) {

@@ -11,7 +11,7 @@ namespace mpa {
 constexpr int kBlock = 16;            // tokens per cache block
 constexpr int kWavesPerGroup = 4;     // waves per workgroup in every kernel
 constexpr int kMaxPlanSeqs = 256;     // sequences per launch (kernel-argument plan)
-constexpr int kMaxPrefillSeqs = 64;   // prefill chunks per launch (its plan carries more per chunk)
+constexpr int kMaxPrefillSeqs = 64;   // prefill segments per launch (its plan carries more per segment)
 constexpr int kPrefillSplitTarget = 256;  // prefill workgroups a launch should at least have
 constexpr int kPrefillMinSplitTiles = 8;  // smallest KV range of a prefill split, in 64-key tiles
 constexpr int kPrefillRows = 64;      // (token, head) rows per generic prefill workgroup
@@ -59,20 +59,24 @@ struct DecodePlan {
   int32_t item_start[kMaxPlanSeqs + 1];
 };
 
-// Prefill work for up to kMaxPrefillSeqs sequences.  Work unit k of this
-// launch belongs to chunk j with tile_start[j] <= k < tile_start[j+1]; with
-// u = k - tile_start[j] it is query tile u / nsplit[j] and KV split
-// u % nsplit[j] of sequence seq[j].  Split x of a chunk covers 64-key tiles
-// [x * split_tiles[j], (x + 1) * split_tiles[j]), the last split everything
-// from there to the end; all splits but the last lie inside the cached
-// prefix.  A chunk with nsplit > 1 writes per-split partial results for its
-// token i and split x to workspace slot item_base[j] + x * C + i, and the
-// merge launch combines them (grid.x runs over row_start, the chunks' token
-// counts summed over split chunks only).
+// Prefill work for up to kMaxPrefillSeqs segments.  Segment j is the ntok[j]
+// tokens from tok0[j] on of the chunk of sequence seq[j] (a chunk, or whole
+// query tiles of it, or its rest).  Work unit k of this launch belongs to
+// segment j with tile_start[j] <= k < tile_start[j+1]; with u = k -
+// tile_start[j] it is query tile u / nsplit[j] and KV split u % nsplit[j] of
+// the segment.  Split x covers 64-key tiles [x * split_tiles[j], (x + 1) *
+// split_tiles[j]), the last split everything from there to the end; all
+// splits but the last lie inside the keys before the segment.  A segment with
+// nsplit > 1 writes per-split partial results for its token i and split x to
+// workspace slot item_base[j] + x * ntok[j] + i, and the merge launch combines
+// them (grid.x runs over row_start, the token counts summed over split
+// segments only).
 struct PrefillPlan {
   int32_t n_seqs;
   int32_t q_tile;    // query tokens per tile = rows per workgroup / G
   int32_t seq[kMaxPrefillSeqs];
+  int32_t tok0[kMaxPrefillSeqs];
+  int32_t ntok[kMaxPrefillSeqs];
   int32_t tile_start[kMaxPrefillSeqs + 1];
   int32_t nsplit[kMaxPrefillSeqs];
   int32_t split_tiles[kMaxPrefillSeqs];

@@ -907,9 +907,9 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(AttnArgs a, Dec
                      a.lse ? a.lse + (size_t)t * a.hq + h : nullptr);
 }
 
-// Prefill merge: one workgroup per (token of a KV-split chunk, 16 q heads);
+// Prefill merge: one workgroup per (token of a KV-split segment, 16 q heads);
 // wave w merges heads 16 * blockIdx.y + w + 4 * k, k < 4.  Split x of token
-// i of chunk j sits at slot item_base[j] + x*C + i.
+// i of segment j sits at slot item_base[j] + x*ntok[j] + i.
 template <int DT, int D>
 __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArgs a, PrefillPlan p) {
   using E = typename Tr<DT>::QElem;
@@ -918,8 +918,8 @@ __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArg
   const int j = upper_index(p.row_start, p.n_seqs, r);
   const int s = p.seq[j];
   const int i = r - p.row_start[j];
-  const int t0 = a.qsl[s];
-  const int C = a.qsl[s + 1] - t0;
+  const int t0 = a.qsl[s] + p.tok0[j];
+  const int C = p.ntok[j];
   const size_t slot = (size_t)p.item_base[j] + i;
   const int h0 = blockIdx.y * (kMergeWaves * kPrefillMergeHeadsPerWave) + wave_uniform(threadIdx.x >> 6);
   for (int k = 0; k < kPrefillMergeHeadsPerWave; ++k) {
@@ -976,10 +976,12 @@ __global__ __launch_bounds__(KEYS ? 64 * kKeyWaves : 256, 2) void prefill_kernel
   const int j = upper_index(p.tile_start, p.n_seqs, tile);
   const int s = p.seq[j];
   const int qt = tile - p.tile_start[j];
-  const int t0 = a.qsl[s];
-  const int C = a.qsl[s + 1] - t0;
+  // the segment's first query row, tokens, and keys before it
+  const int chunk0 = a.qsl[s];
+  const int t0 = chunk0 + p.tok0[j];
+  const int C = p.ntok[j];
   const int L = a.seq_lens[s];
-  const int P = L - C;
+  const int P = L - (a.qsl[s + 1] - chunk0) + p.tok0[j];
   const int G = a.hq / a.hkv;
   const int first_tok = qt * p.q_tile;
   if (first_tok + (sub * 16) / G >= C) return;  // no rows here (the same for the whole workgroup with KEYS)
@@ -1130,10 +1132,12 @@ __global__ __launch_bounds__(64 * WAVES, 1) void prefill_mfma_kernel(AttnArgs a,
   const int nsplit = p.nsplit[j];
   const int qt = (tile - p.tile_start[j]) / nsplit;
   const int split = tile - p.tile_start[j] - qt * nsplit;
-  const int t0 = a.qsl[s];
-  const int C = a.qsl[s + 1] - t0;
+  // the segment's first query row, tokens, and keys before it
+  const int chunk0 = a.qsl[s];
+  const int t0 = chunk0 + p.tok0[j];
+  const int C = p.ntok[j];
   const int L = a.seq_lens[s];
-  const int P = L - C;
+  const int P = L - (a.qsl[s + 1] - chunk0) + p.tok0[j];
   const int G = a.hq / a.hkv;
   const int first_tok = qt * p.q_tile;
   const int last_tok = min(first_tok + p.q_tile - 1, C - 1);
