@@ -182,6 +182,19 @@ int range_min_blocks(int dtype, int head_dim) {
   return head_dim == 128 ? 24 : 10;
 }
 
+// The launches that take one workgroup per (row, KV head) (decode_short_kernel)
+// with no row split: at most so many pairs, of rows of at most so many keys.
+// Measured against row splits and their merge (decode half, us; 12.3 is what
+// the host takes to issue a call), splits -> this:
+//   bf16, d 128: 8 rows of 8 heads of up to 700 keys 16.6 -> 13.0, 1,024 16.3
+//     -> 14.7, 1,500 16.7 -> 19.2; 64 rows of 1,024 40.3 -> 37.5;
+//   bf16, d 64: 64 rows of 2 heads, 2,048 keys 16.7 -> 15.6, 3,000 20.2 -> 21.5;
+//   fp8, d 128: 32 rows of 8 heads, 1,024 keys 17.2 -> 15.8; 64 rows of 700
+//     22.2 -> 23.1 (the split kernel reads the codes by 16 bytes);
+//   f32, d 128: 32 rows of 2 heads, 256 keys 19.5 -> 12.7, 700 20.9 -> 23.1.
+int short_row(int dtype, int head_dim) { return (dtype == MPA_F32 ? 512 : 1024) * (128 / head_dim); }
+long short_pairs(int dtype) { return dtype == MPA_BF16 ? 512 : 256; }
+
 // One decode launch: rows [c0, c1) of Batch::decode.
 struct DecodeLaunch {
   size_t c0 = 0, c1 = 0;
@@ -209,7 +222,12 @@ std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, con
     d.c1 = std::min(b.decode.size(), c0 + mpa::kMaxPlanSeqs);
     long blocks = 0;
     for (size_t k = d.c0; k < d.c1; ++k) blocks += row_blocks(seq_lens[b.decode[k]]);
-    if (ranges && blocks < (1L << 30)) {  // block counts are 32 bits in the plan
+    int longest = 0;
+    for (size_t k = d.c0; k < d.c1; ++k) longest = std::max(longest, seq_lens[b.decode[k]]);
+    if (forced < 0 && longest <= short_row(sh->dtype, sh->head_dim) &&
+        (long)(d.c1 - d.c0) * sh->num_kv_heads <= short_pairs(sh->dtype))
+      d.range_blocks = -1;
+    else if (ranges && blocks < (1L << 30)) {  // block counts are 32 bits in the plan
       const long per_head = std::max(1L, slots / sh->num_kv_heads);
       const long range = (blocks + per_head - 1) / per_head;
       if (forced > 0)
@@ -220,8 +238,9 @@ std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, con
     long at = 0;
     for (size_t k = d.c0; k < d.c1; ++k) {
       const int L = seq_lens[b.decode[k]];
-      const long parts =
-          d.range_blocks ? range_parts(at, row_blocks(L), d.range_blocks) : (long)row_split(L, split).parts;
+      const long parts = d.range_blocks > 0   ? range_parts(at, row_blocks(L), d.range_blocks)
+                         : d.range_blocks < 0 ? 1
+                                              : (long)row_split(L, split).parts;
       at += row_blocks(L);
       d.items += parts;
       d.split |= parts > 1;
@@ -509,7 +528,7 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
   };
   p.decode = decode_layout(sh, p.batch, seq_lens, 1024, true);
   bool all_ranges = true;
-  for (const auto& d : p.decode) all_ranges &= d.range_blocks > 0;
+  for (const auto& d : p.decode) all_ranges &= d.range_blocks != 0;
   if (!all_ranges) {
     p.split = choose_split(sh, p.batch, seq_lens);
     p.decode = decode_layout(sh, p.batch, seq_lens, p.split, true);
@@ -536,7 +555,7 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
       }
     }
   }
-  if (p.split == 0 && !p.decode.empty()) p.split = p.decode[0].range_blocks * kBlock;
+  if (p.split == 0 && !p.decode.empty() && p.decode[0].range_blocks > 0) p.split = p.decode[0].range_blocks * kBlock;
   if (p.split == 0) p.split = 1024;
   for (const auto& d : p.decode) p.decode_split |= d.split;
   for (const auto& c : p.prefill) p.prefill_split |= c.nsplit > 1;
@@ -724,10 +743,10 @@ mpa_step_time model_step(const mpa_shape* shape, const StepPlan& plan, const int
     for (size_t k = d.c0; k < d.c1; ++k) {
       const int L = seq_lens_host[b.decode[k]];
       bytes += (double)L * head_bytes * shape->num_kv_heads;
-      if (!d.range_blocks) wave = std::max(wave, (double)std::min(L, row_split(L, plan.split).tokens) * head_bytes);
+      if (d.range_blocks <= 0) wave = std::max(wave, (double)std::min(L, row_split(L, plan.split).tokens) * head_bytes);
     }
-    if (d.range_blocks) wave = (double)d.range_blocks * kBlock * head_bytes;
-    const double gbs = r.decode_gbs * (d.range_blocks ? kRangeSpeed : 1.0);
+    if (d.range_blocks > 0) wave = (double)d.range_blocks * kBlock * head_bytes;
+    const double gbs = r.decode_gbs * (d.range_blocks > 0 ? kRangeSpeed : 1.0);
     t.decode_us += r.decode_fixed_us + std::max(bytes / (gbs * 1e3), wave / (r.decode_wave_gbs * 1e3));
     if (d.split) t.decode_us += r.merge_us;
   }
@@ -882,7 +901,7 @@ int mpa_plan_coexec(const mpa_shape* shape, const int32_t* seq_lens_host, const 
   const StepPlan& plan = step_plan(shape, seq_lens_host, qsl_host);
   const Batch& b = plan.batch;
   for (const auto& d : plan.decode)
-    if (d.range_blocks) dfrac[3] = r.coexec_decode_q3 * kRangeSpeedQ3;
+    if (d.range_blocks > 0) dfrac[3] = r.coexec_decode_q3 * kRangeSpeedQ3;
   const mpa_step_time serial = model_step(shape, plan, seq_lens_host, qsl_host, r);
   double t[4];
   t[0] = serial.decode_us + serial.prefill_us;
@@ -1054,7 +1073,10 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
       const int L = seq_lens_host[s];
       p.seq[k] = s;
       p.item_start[k] = acc;
-      if (d.range_blocks) {
+      if (d.range_blocks < 0) {
+        p.part[k] = 0;
+        acc += 1;
+      } else if (d.range_blocks > 0) {
         p.part[k] = at;
         acc += (int)range_parts(at, row_blocks(L), d.range_blocks);
         at += row_blocks(L);

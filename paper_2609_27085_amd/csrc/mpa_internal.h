@@ -50,6 +50,8 @@ struct AttnArgs {
 // range_blocks > 0: the rows' cache blocks laid end to end (row j's are
 // part[j] .. part[j+1] - 1) are cut into ranges of range_blocks, one wave per
 // range and KV head; a row's parts are its intersections with the ranges.
+// range_blocks < 0: rows are not split (part is unused), one workgroup per row
+// and KV head.
 struct DecodePlan {
   int32_t n_seqs;
   int32_t item_base;

@@ -25,6 +25,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "mpa_internal.h"
@@ -639,6 +640,54 @@ __device__ inline void append_decode_token(const AttnArgs& a, int s, int pos, in
   }
 }
 
+// The results of a workgroup's kKeyWaves waves for the same 16 rows, each over
+// keys of its own, merged through LDS and written: (max, sum) of every wave
+// and row, then the accumulators, half of the dims at a time; wave w adds up
+// the rows' dims 16 * mt for its mt.  `l` is the row's sum over the lane
+// groups, out and lse (lse may be null) the lane's row.  A wave that saw no
+// key of a row has max -inf and weight 0; wave 0 has key 0, which every row
+// sees.
+constexpr int kKeyWaves = 8;
+
+template <int DT, int D>
+__device__ inline void merge_waves(const RowState<DT, D>& st, float l, bool poison, float v_scale, bool row_ok,
+                                   typename Tr<DT>::QElem* out, float* lse) {
+  constexpr int MT = D / 16;
+  const int lane = threadIdx.x & 63;
+  const int wave = wave_uniform(threadIdx.x >> 6);
+  const int n = lane & 15, grp = lane >> 4;
+  __shared__ float ml[kKeyWaves][2][16];
+  __shared__ f32x4 part[kKeyWaves][MT / 2][64];
+  if (grp == 0) {
+    ml[wave][0][n] = st.m;
+    ml[wave][1][n] = poison ? NAN : l;
+  }
+  float w[kKeyWaves], M = -INFINITY, sum = 0.f;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    if (half) __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < MT / 2; ++mt) part[wave][mt][lane] = st.acc[half * (MT / 2) + mt];
+    __syncthreads();
+    if (half == 0) {
+#pragma unroll
+      for (int k = 0; k < kKeyWaves; ++k) M = fmaxf(M, ml[k][0][n]);
+#pragma unroll
+      for (int k = 0; k < kKeyWaves; ++k) {
+        w[k] = exp2_fast(ml[k][0][n] - M);
+        sum += ml[k][1][n] * w[k];
+      }
+    }
+    if (wave < MT / 2 && row_ok) {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < kKeyWaves; ++k) v += part[k][wave][lane] * w[k];
+      Tr<DT>::store4(out + 16 * (half * (MT / 2) + wave) + 4 * grp, v * (v_scale / sum));
+    }
+  }
+  if (lse && wave == 0 && grp == 0 && row_ok) *lse = (M + log2f(sum)) * kLn2;
+}
+
 // ---------------------------------------------------------------------------
 // Decode; the G query heads of the group are the 16 MFMA columns (columns
 // >= G carry zero queries).
@@ -764,6 +813,57 @@ __global__ __launch_bounds__(64 * WPG, decode_waves_per_simd(DT, D)) void decode
     }
     if (!STREAM || blk >= blk_end) return;
   }
+}
+
+// Decode of few short rows: one workgroup per (row, KV head), whose waves each
+// take an eighth of the row's blocks and merge in LDS, so that the step needs
+// neither partial results nor a merge launch.  Latency bound.  4 rows of
+// 64-256 keys at 2 KV heads of 64: 5.6 us; the split kernel and its merge
+// took 5.9 and 3.1 and the gap between them 1.3.
+template <int DT, int D>
+__global__ __launch_bounds__(64 * kKeyWaves, 2) void decode_short_kernel(AttnArgs a, DecodePlan p) {
+  using T = Tr<DT>;
+  using QE = typename T::QElem;
+  constexpr int X = T::X;
+  constexpr int R = D / (4 * X);
+  constexpr int MT = D / 16;
+  const int lane = threadIdx.x & 63;
+  const int wave = wave_uniform(threadIdx.x >> 6);
+  const int j = blockIdx.x / a.hkv;
+  const int g = blockIdx.x - j * a.hkv;
+  if (j >= p.n_seqs) return;
+  const int s = p.seq[j];
+  const int L = a.seq_lens[s];
+  const int trow = a.qsl[s];
+  const int G = a.hq / a.hkv;
+  const int n = lane & 15, grp = lane >> 4;
+  const bool head_ok = n < G;
+  const int h = g * G + (head_ok ? n : 0);
+  const int nb = (L + kBlock - 1) / kBlock;
+  const int per = (nb + kKeyWaves - 1) / kKeyWaves;
+  const int kb0 = min(wave * per, nb), kb1 = min(nb, kb0 + per);
+  if (a.k_new != nullptr && kb0 < kb1 && kb1 == nb) {
+    append_decode_token<DT, D>(a, s, L - 1, trow, g, lane);
+    MPA_WAIT_VMCNT(0);  // stores are counted in vmcnt
+  }
+  const QE* q = reinterpret_cast<const QE*>(a.q) + ((size_t)trow * a.hq + h) * D;
+  typename T::Chunk qf[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) qf[r] = head_ok ? T::load_q(q + (4 * r + grp) * X) : T::zero_chunk();
+  RowState<DT, D> st;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) st.acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  st.m = -INFINITY;
+  st.l = 0.f;
+  bool poison = false;
+  int step = 0;
+  attend_blocks<DT, D, false>(a, qf, a.block_tables + (size_t)s * a.mb, g, kb0, kb1, L, INT32_MAX, INT32_MAX, st,
+                              poison, step);
+  float l = st.l + __shfl_xor(st.l, 16);
+  l += __shfl_xor(l, 32);
+  merge_waves<DT, D>(st, l, poison, a.v_scale, head_ok,
+                     reinterpret_cast<QE*>(a.out) + ((size_t)trow * a.hq + h) * D,
+                     a.lse ? a.lse + (size_t)trow * a.hq + h : nullptr);
 }
 
 // Split-K merge.  With split maxima m_k and sums l_k (log2 units), a row's
@@ -944,7 +1044,6 @@ __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArg
 // takes about 1.2 us per block of its longest row with most of the device
 // idle; an eighth of the keys a wave spreads the same products over four
 // times the workgroups and eighths of the time.
-constexpr int kKeyWaves = 8;
 
 // Which form a launch of this many (tile, KV head) pairs takes, measured
 // (us, KEYS false -> true; head_dim 128, tokens on prefix):
@@ -1021,40 +1120,7 @@ __global__ __launch_bounds__(KEYS ? 64 * kKeyWaves : 256, 2) void prefill_kernel
   l += __shfl_xor(l, 32);
   QE* o = reinterpret_cast<QE*>(a.out) + ((size_t)(t0 + i) * a.hq + h) * D;
   if constexpr (KEYS) {
-    // (max, sum) of every wave and row, then the accumulators, half of the
-    // dims at a time; wave w adds up the rows' dims 16 * mt for its mt.  A
-    // wave that saw no key of a row has max -inf and weight 0; wave 0 has key
-    // 0, which every row sees.
-    __shared__ float ml[kKeyWaves][2][16];
-    __shared__ f32x4 part[kKeyWaves][MT / 2][64];
-    if (grp == 0) {
-      ml[wave][0][n] = st.m;
-      ml[wave][1][n] = poison ? NAN : l;
-    }
-    float w[kKeyWaves], M = -INFINITY, sum = 0.f;
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      if (half) __syncthreads();
-#pragma unroll
-      for (int mt = 0; mt < MT / 2; ++mt) part[wave][mt][lane] = st.acc[half * (MT / 2) + mt];
-      __syncthreads();
-      if (half == 0) {
-#pragma unroll
-        for (int k = 0; k < kKeyWaves; ++k) M = fmaxf(M, ml[k][0][n]);
-#pragma unroll
-        for (int k = 0; k < kKeyWaves; ++k) {
-          w[k] = exp2_fast(ml[k][0][n] - M);
-          sum += ml[k][1][n] * w[k];
-        }
-      }
-      if (wave < MT / 2 && row_ok) {
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < kKeyWaves; ++k) v += part[k][wave][lane] * w[k];
-        T::store4(o + 16 * (half * (MT / 2) + wave) + 4 * grp, v * (a.v_scale / sum));
-      }
-    }
-    if (a.lse && wave == 0 && grp == 0 && row_ok) a.lse[(size_t)(t0 + i) * a.hq + h] = (M + log2f(sum)) * kLn2;
+    merge_waves<DT, D>(st, l, poison, a.v_scale, row_ok, o, a.lse ? a.lse + (size_t)(t0 + i) * a.hq + h : nullptr);
     return;
   }
   if (!row_ok) return;
@@ -1981,6 +2047,11 @@ struct DecodeL {
   static hipError_t run(const AttnArgs& a, const DecodePlan& p, int n_items, hipStream_t stream) {
     const long units = (long)n_items * a.hkv;
     if (units == 0) return hipSuccess;
+    if (p.range_blocks < 0) {
+      hipLaunchKernelGGL((decode_short_kernel<DT, D>), dim3((unsigned)p.n_seqs * a.hkv), dim3(64 * kKeyWaves), 0,
+                         stream, a, p);
+      return hipGetLastError();
+    }
     if (p.range_blocks > 0) {
       constexpr int W = kStreamWaves<DT, D>;
       const long waves = (long)((p.part[p.n_seqs] + p.range_blocks - 1) / p.range_blocks) * a.hkv;
@@ -2014,8 +2085,11 @@ template <int DT, int D>
 struct MergeL {
   static hipError_t run(const AttnArgs& a, const DecodePlan& p, hipStream_t stream) {
     if (p.n_seqs == 0) return hipSuccess;
-    const int parts = p.item_start[p.n_seqs];
-    if (parts >= 16L * p.n_seqs && (long)p.n_seqs * a.hq <= 4096)
+    // the wide form where a wave would go over many parts and there are few
+    // (row, q head) pairs (3 rows of 128 parts, 32 heads: 6.8 us, 16.5 before)
+    int most = 0;
+    for (int j = 0; j < p.n_seqs; ++j) most = std::max(most, p.item_start[j + 1] - p.item_start[j]);
+    if (most >= 16 && (long)p.n_seqs * a.hq <= 4096)
       hipLaunchKernelGGL((merge_kernel<DT, D, true>), dim3(p.n_seqs, a.hq), dim3(64 * kMergeWaves), 0, stream, a, p);
     else
       hipLaunchKernelGGL((merge_kernel<DT, D, false>), dim3(p.n_seqs, (a.hq + kMergeWaves - 1) / kMergeWaves),

@@ -57,3 +57,25 @@ def test_ranges_chosen_for_batches_that_fill_the_device(torch_gpu, dtype):  # no
     info = info_of(b)
     assert info.split_tokens % 16 == 0 and info.num_decode_items == parts(lens, info.split_tokens // 16)
     check_batch(b, f"ranges of {info.split_tokens} tokens, {info.num_decode_items} parts", fused=True)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32", "fp8"])
+@pytest.mark.parametrize("heads", [(8, 2, 128), (10, 2, 64), (16, 1, 128)],
+                         ids=lambda h: f"hq{h[0]}_hkv{h[1]}_d{h[2]}")
+def test_short_rows(torch_gpu, dtype, heads):  # noqa: F811
+    """Short rows take one workgroup per row and KV head, whose eight waves
+    share the row's blocks: rows of fewer blocks than waves, of one block more
+    or less than a whole share, and the longest that is not split."""
+    longest = (512 if dtype == "f32" else 1024) * (128 // heads[2])
+    lens = [1, 15, 16, 17, 64, 65, 112, 113, 128, 129, 145, 257, 400, longest - 1, longest]
+    b = make_batch([SeqSpec(n, 1) for n in lens], HeadSpec(*heads, 16), dtype, np.random.default_rng(820))
+    info = info_of(b)
+    assert info.num_decode_items == len(lens)
+    _, out, lse = check_batch(b, "short rows", fused=True)
+    out2, lse2 = run_step(to_device(b))
+    assert torch_gpu.equal(out, out2) and torch_gpu.equal(lse, lse2)
+    # one key more: the rows are split
+    b = make_batch([SeqSpec(n, 1) for n in lens[:-1] + [longest + 1]], HeadSpec(*heads, 16), dtype,
+                   np.random.default_rng(821))
+    assert info_of(b).num_decode_items > len(lens)
+    check_batch(b, "one row past the short ones", fused=True)
