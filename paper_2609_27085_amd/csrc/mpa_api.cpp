@@ -1007,6 +1007,39 @@ namespace {
 
 enum Phase { kDecode = 1, kPrefill = 2 };
 
+// (token, head) rows per workgroup of the launch of segments [c0, c1).  The
+// planner counts workgroups of 256 rows (eight waves, one to a CU).  bf16
+// launches of few of them run as workgroups of 128 (four waves, two to a CU,
+// or three at head_dim 64): a prompt's tiles grow from one 64-key tile to the
+// chunk's length, and half tiles let a long and a short one share a CU and
+// fill each other's gaps; larger launches read K and V twice as often for it.
+// Measured (us, 256 -> 128 rows):
+//   d 128: 64 workgroups (8/2 heads, 2,000 tokens on 0) 50.2 -> 38.8, 128
+//     (32/8, 1,000 on 500) 41.1 -> 34.4, 376 (3,000 on 0) 84.2 -> 81.1, 504
+//     (4,000 on 0) 126.8 -> 139.9; KV-split (2,048 on 4,096) 65.5 -> 68.9;
+//     three chunks of 500 in 48 20.3 -> 16.8, in 192 22.3 -> 24.4 (half tiles
+//     of several chunks meet on a CU in no particular order);
+//   d 64: 126 (16/2, 2,000 on 400) 44.7 -> 34.8, 256 (4,096 on 4,096) 139.0 ->
+//     124.4, 240 (300 on 20,011, KV-split) 49.7 -> 47.2, 512 (32/8, 4,096 on
+//     4,096) 223.8 -> 235.1, 1,024 (8,192 on 32,768) 2,512 -> 2,419.
+int prefill_rows(const mpa_shape* sh, const std::vector<PrefillSegment>& segments, size_t c0, size_t c1) {
+  if (sh->dtype == MPA_F32) return mpa::kPrefillRows;
+  if (sh->dtype != MPA_BF16) return mpa::kPrefillRowsMfma;
+  const int qt = q_tile(sh);
+  long groups = 0;
+  bool split = false;
+  for (size_t k = c0; k < c1; ++k) {
+    groups += (long)(segments[k].ntok + qt - 1) / qt * segments[k].nsplit * sh->num_kv_heads;
+    split |= segments[k].nsplit > 1;
+  }
+  bool half;
+  if (sh->head_dim == 64)
+    half = groups < 448 || groups >= 1024;
+  else
+    half = !split && groups < (c1 - c0 == 1 ? 448 : 128);
+  return half ? mpa::kPrefillRowsHalf : mpa::kPrefillRowsMfma;
+}
+
 int run_attention(int phases, const mpa_shape* shape, const void* q, const void* k_cache, const void* v_cache,
                   const int32_t* block_tables, const int32_t* seq_lens, const int32_t* query_start_loc,
                   const int32_t* seq_lens_host, const int32_t* query_start_loc_host,
@@ -1095,11 +1128,12 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
   }
   // Prefill segments, in launches of up to kMaxPrefillSeqs; KV-split ones are
   // merged after their launch.
-  const int qt = q_tile(shape);
   for (size_t c0 = 0; prefill && c0 < plan.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
     mpa::PrefillPlan p;
     p.n_seqs = (int32_t)(std::min(plan.prefill.size(), c0 + mpa::kMaxPrefillSeqs) - c0);
-    p.q_tile = qt;
+    p.rows = prefill_rows(shape, plan.prefill, c0, c0 + p.n_seqs);
+    p.q_tile = p.rows / (shape->num_q_heads / shape->num_kv_heads);
+    const int qt = p.q_tile;
     int acc = 0, rows = 0;
     for (int k = 0; k < p.n_seqs; ++k) {
       const PrefillSegment& g = plan.prefill[c0 + k];

@@ -16,6 +16,7 @@ constexpr int kPrefillSplitTarget = 256;  // prefill workgroups a launch should 
 constexpr int kPrefillMinSplitTiles = 8;  // smallest KV range of a prefill split, in 64-key tiles
 constexpr int kPrefillRows = 64;      // (token, head) rows per generic prefill workgroup
 constexpr int kFewKeys = 64;          // rows that see at most this many keys get the 16-bit P pass
+constexpr int kPrefillRowsHalf = 128; // the same of the four-wave form
 constexpr int kPrefillRowsMfma = 256; // (token, head) rows per bf16 prefill workgroup (8 waves)
 
 // Pointers and sizes common to the attention kernels.
@@ -76,6 +77,7 @@ struct DecodePlan {
 struct PrefillPlan {
   int32_t n_seqs;
   int32_t q_tile;    // query tokens per tile = rows per workgroup / G
+  int32_t rows;      // (token, head) rows per workgroup
   int32_t seq[kMaxPrefillSeqs];
   int32_t tok0[kMaxPrefillSeqs];
   int32_t ntok[kMaxPrefillSeqs];

@@ -1132,7 +1132,7 @@ __global__ __launch_bounds__(KEYS ? 64 * kKeyWaves : 256, 2) void prefill_kernel
 }
 
 // ---------------------------------------------------------------------------
-// Prefill chunks, bf16: the tensor-core path.  One workgroup of WAVES waves
+// Prefill chunks, bf16: the tensor-core path.  One workgroup of WAVES (8 or 4) waves
 // per (sequence, 32*WAVES-row query tile, KV head); row r of the tile is token
 // r / G and head r % G of the group, so the G heads that share a KV head share
 // every K/V tile.  Each wave owns 32 rows (one 32-wide MFMA column tile).
@@ -1162,7 +1162,7 @@ __global__ __launch_bounds__(KEYS ? 64 * kKeyWaves : 256, 2) void prefill_kernel
 // than 8 (log2 units), so exp2(s - m) <= 2^8 and the O / l rescale is skipped
 // for almost every tile; the final O / l is the same quotient either way.
 template <int CT, int D, int WAVES, int STAGES>
-__global__ __launch_bounds__(64 * WAVES, 1) void prefill_mfma_kernel(AttnArgs a, PrefillPlan p) {
+__global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : D == 64 ? 3 : 2) void prefill_mfma_kernel(AttnArgs a, PrefillPlan p) {
   using f32x16 = float __attribute__((ext_vector_type(16)));
   using cint = const __attribute__((address_space(4))) int32_t;
   constexpr int BN = 64;                   // keys per tile
@@ -1384,7 +1384,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void prefill_mfma_kernel(AttnArgs a,
   // arbiter favours the older one, so the upper half finishes each tile
   // last and the lower half waits for it at the barrier.  Raising the upper
   // half's priority shortens that critical path.
-  if (wave >= WAVES / 2) __builtin_amdgcn_s_setprio(1);
+  if (WAVES == 8 && wave >= WAVES / 2) __builtin_amdgcn_s_setprio(1);
   for (int kt = kt_begin; kt < ntile; ++kt) {
     // tile kt+STAGES-1 is copied into the stage tile kt-1 used (all waves are
     // past it): by an active wave between its QK products, so that the
@@ -2101,10 +2101,10 @@ struct MergeL {
 constexpr int kPrefillWaves = 8;   // waves per bf16 prefill workgroup
 constexpr int kPrefillStages = 3;  // LDS ring depth of the bf16 prefill kernel
 
-template <int CT, int D>
+template <int CT, int D, int WAVES, int STAGES>
 hipError_t launch_prefill_mfma(const AttnArgs& a, const PrefillPlan& p, int n_tiles, hipStream_t stream) {
-  constexpr size_t lds = 2 * kPrefillStages * 4 * kBlock * D * sizeof(uint16_t);
-  auto kern = prefill_mfma_kernel<CT, D, kPrefillWaves, kPrefillStages>;
+  constexpr size_t lds = 2 * STAGES * 4 * kBlock * D * sizeof(uint16_t);
+  auto kern = prefill_mfma_kernel<CT, D, WAVES, STAGES>;
   // The ring exceeds the default 64 KB of dynamic LDS; raise the limit once
   // per device (each GPU keeps its own function attributes).
   static std::atomic<unsigned long long> ready{0};
@@ -2117,7 +2117,7 @@ hipError_t launch_prefill_mfma(const AttnArgs& a, const PrefillPlan& p, int n_ti
     if (e != hipSuccess) return e;
     ready.fetch_or(bit, std::memory_order_relaxed);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles * a.hkv), dim3(64 * kPrefillWaves), lds, stream, a, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles * a.hkv), dim3(64 * WAVES), lds, stream, a, p);
   return hipGetLastError();
 }
 
@@ -2128,7 +2128,11 @@ struct PrefillL {
   static hipError_t run(const AttnArgs& a, const PrefillPlan& p, int n_tiles, hipStream_t stream) {
     if (n_tiles == 0) return hipSuccess;
     if constexpr (DT == 0 || DT == 2) {
-      return launch_prefill_mfma<DT, D>(a, p, n_tiles, stream);
+      if constexpr (DT == 0) {
+        // two workgroups of a two-stage ring (64 KB) to a CU, or three of a three-stage one (48 KB)
+        if (p.rows == kPrefillRowsHalf) return launch_prefill_mfma<DT, D, 4, D == 64 ? 3 : 2>(a, p, n_tiles, stream);
+      }
+      return launch_prefill_mfma<DT, D, kPrefillWaves, kPrefillStages>(a, p, n_tiles, stream);
     } else {
       if (prefill_by_keys((long)n_tiles * a.hkv))
         hipLaunchKernelGGL((prefill_kernel<DT, D, true>), dim3((unsigned)n_tiles * 4 * a.hkv), dim3(64 * kKeyWaves), 0, stream, a,
