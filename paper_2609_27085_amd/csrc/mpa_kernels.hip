@@ -957,7 +957,6 @@ __device__ inline void merge_store(const MergeState& r, typename Tr<DT>::QElem* 
 // small workgroup per pair is bound by the dispatcher's workgroup rate
 // (about 1.2 per ns), not by the bytes it moves.
 constexpr int kMergeWaves = 4;
-constexpr int kPrefillMergeHeadsPerWave = 4;
 
 // Decode merge: one workgroup per (split decode sequence, 4 q heads); wave w
 // merges head 4 * blockIdx.y + w.  WIDE: one workgroup per (sequence, q
@@ -1007,11 +1006,12 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(AttnArgs a, Dec
                      a.lse ? a.lse + (size_t)t * a.hq + h : nullptr);
 }
 
-// Prefill merge: one workgroup per (token of a KV-split segment, 16 q heads);
-// wave w merges heads 16 * blockIdx.y + w + 4 * k, k < 4.  Split x of token
-// i of segment j sits at slot item_base[j] + x*ntok[j] + i.
+// Prefill merge: one workgroup per (token of a KV-split segment, 4 * per_wave q
+// heads); wave w merges heads 4 * (per_wave * blockIdx.y + k) + w, k <
+// per_wave.  Split x of token i of segment j sits at slot item_base[j] +
+// x*ntok[j] + i.
 template <int DT, int D>
-__global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArgs a, PrefillPlan p) {
+__global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArgs a, PrefillPlan p, int per_wave) {
   using E = typename Tr<DT>::QElem;
   const int r = blockIdx.x;
   if (r >= p.row_start[p.n_seqs]) return;
@@ -1021,8 +1021,8 @@ __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArg
   const int t0 = a.qsl[s] + p.tok0[j];
   const int C = p.ntok[j];
   const size_t slot = (size_t)p.item_base[j] + i;
-  const int h0 = blockIdx.y * (kMergeWaves * kPrefillMergeHeadsPerWave) + wave_uniform(threadIdx.x >> 6);
-  for (int k = 0; k < kPrefillMergeHeadsPerWave; ++k) {
+  const int h0 = blockIdx.y * (kMergeWaves * per_wave) + wave_uniform(threadIdx.x >> 6);
+  for (int k = 0; k < per_wave; ++k) {
     const int h = h0 + k * kMergeWaves;
     if (h >= a.hq) break;
     const MergeState m = merge_range<D>(a.ws_ml + (slot * a.hq + h) * 2, (size_t)C * a.hq * 2,
@@ -2086,10 +2086,11 @@ struct MergeL {
   static hipError_t run(const AttnArgs& a, const DecodePlan& p, hipStream_t stream) {
     if (p.n_seqs == 0) return hipSuccess;
     // the wide form where a wave would go over many parts and there are few
-    // (row, q head) pairs (3 rows of 128 parts, 32 heads: 6.8 us, 16.5 before)
+    // (row, q head) pairs (3 rows of 128 parts, 32 heads: 6.8 us, 16.5 before;
+    // 64 rows of 64 heads, one in ten with 16 parts: 8.5 wide, 6.5 not)
     int most = 0;
     for (int j = 0; j < p.n_seqs; ++j) most = std::max(most, p.item_start[j + 1] - p.item_start[j]);
-    if (most >= 16 && (long)p.n_seqs * a.hq <= 4096)
+    if (most >= 16 && (long)p.n_seqs * a.hq <= 1024)
       hipLaunchKernelGGL((merge_kernel<DT, D, true>), dim3(p.n_seqs, a.hq), dim3(64 * kMergeWaves), 0, stream, a, p);
     else
       hipLaunchKernelGGL((merge_kernel<DT, D, false>), dim3(p.n_seqs, (a.hq + kMergeWaves - 1) / kMergeWaves),
@@ -2193,9 +2194,13 @@ struct PrefillMergeL {
   static hipError_t run(const AttnArgs& a, const PrefillPlan& p, hipStream_t stream) {
     const int rows = p.row_start[p.n_seqs];
     if (rows == 0) return hipSuccess;
-    constexpr int heads = kMergeWaves * kPrefillMergeHeadsPerWave;
+    // Four heads in turn keep the workgroups of a large launch few; one of few
+    // tokens has its heads side by side (300 tokens of 16 heads in 12 splits:
+    // 9.9 -> 6.6 us).
+    const int per_wave = (long)rows * a.hq >= 16384 ? 4 : 1;
+    const int heads = kMergeWaves * per_wave;
     hipLaunchKernelGGL((prefill_merge_kernel<DT, D>), dim3(rows, (a.hq + heads - 1) / heads),
-                       dim3(64 * kMergeWaves), 0, stream, a, p);
+                       dim3(64 * kMergeWaves), 0, stream, a, p, per_wave);
     return hipGetLastError();
   }
 };
