@@ -177,9 +177,11 @@ int mpa_kv_append_rope(const mpa_shape* shape, void* q, const void* k_new, const
 /*
  * Bytes of device workspace that mpa_mixed_paged_attention needs for this
  * batch: the split-K partial results of long decode rows, and of prefill
- * chunks whose cached prefix is split across workgroups (short bf16 chunks
- * on long prefixes, when the batch's prefill tiles alone would leave most of
- * the device idle).  Depends only on the shape and the host metadata.
+ * chunks whose cached prefix is split across workgroups (short chunks on
+ * long prefixes, when the batch's prefill tiles alone would leave most of
+ * the device idle, and chunks that would leave it idle at the end of a
+ * launch).  Depends only on the shape, the host metadata and the current
+ * device's size.
  * Returns 0 for an invalid batch, and when nothing is split.
  */
 size_t mpa_workspace_size(const mpa_shape* shape, const int32_t* seq_lens_host,
@@ -200,7 +202,8 @@ size_t mpa_workspace_size(const mpa_shape* shape, const int32_t* seq_lens_host,
  *
  * Decode rows (q_len = 1) run as split-K over KV blocks with an LSE merge;
  * prefill chunks (q_len > 1) run as causal MFMA tiles, their cached prefix
- * also split (and merged the same way) when the chunks are short.
+ * also split (and merged the same way) when the chunks are short, or where
+ * that evens out a launch of chunks of unlike lengths.
  *
  * q                 device [T][Hq][d]
  * out               device [T][Hq][d], written for every row of every

@@ -743,7 +743,9 @@ mpa_step_time model_step(const mpa_shape* shape, const StepPlan& plan, const int
     for (size_t k = d.c0; k < d.c1; ++k) {
       const int L = seq_lens_host[b.decode[k]];
       bytes += (double)L * head_bytes * shape->num_kv_heads;
-      if (d.range_blocks <= 0) wave = std::max(wave, (double)std::min(L, row_split(L, plan.split).tokens) * head_bytes);
+      // the most keys one wave goes over; a short row's eight waves share it
+      const int part = d.range_blocks < 0 ? short_row(shape->dtype, shape->head_dim) / 8 : row_split(L, plan.split).tokens;
+      if (d.range_blocks <= 0) wave = std::max(wave, (double)std::min(L, part) * head_bytes);
     }
     if (d.range_blocks > 0) wave = (double)d.range_blocks * kBlock * head_bytes;
     const double gbs = r.decode_gbs * (d.range_blocks > 0 ? kRangeSpeed : 1.0);
