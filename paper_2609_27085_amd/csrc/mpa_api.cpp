@@ -661,13 +661,21 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
   (void)query_start_loc;
   const Batch b = classify(shape, query_start_loc_host);
   clear_stale_hip_error();
-  // multi-token sequences one wave per (cache block, KV head)
-  for (size_t c0 = 0; c0 < b.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
+  // multi-token sequences one wave per (cache block, KV head); with the rotary
+  // embedding (appended by no attention call) the single tokens beside them
+  // too, where one launch holds all
+  std::vector<int> blocks(b.prefill);
+  bool tokens_left = !multi_only;
+  if (rope && !b.prefill.empty() && b.prefill.size() + b.decode.size() <= (size_t)mpa::kMaxPrefillSeqs) {
+    blocks.insert(blocks.end(), b.decode.begin(), b.decode.end());
+    tokens_left = false;
+  }
+  for (size_t c0 = 0; c0 < blocks.size(); c0 += mpa::kMaxPrefillSeqs) {
     mpa::AppendBlockPlan p;
-    p.n_seqs = (int32_t)(std::min(b.prefill.size(), c0 + mpa::kMaxPrefillSeqs) - c0);
+    p.n_seqs = (int32_t)(std::min(blocks.size(), c0 + mpa::kMaxPrefillSeqs) - c0);
     int units = 0, tokens = 0;
     for (int k = 0; k < p.n_seqs; ++k) {
-      const int s = b.prefill[c0 + k];
+      const int s = blocks[c0 + k];
       const int ql = query_start_loc_host[s + 1] - query_start_loc_host[s];
       const int pos0 = seq_lens_host[s] - ql;
       p.seq[k] = s;
@@ -686,7 +694,7 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
   }
   // single-token sequences one wave per token, unless the decode kernel
   // appends them
-  for (size_t c0 = 0; !multi_only && c0 < b.decode.size(); c0 += mpa::kMaxPlanSeqs) {
+  for (size_t c0 = 0; tokens_left && c0 < b.decode.size(); c0 += mpa::kMaxPlanSeqs) {
     mpa::AppendPlan p;
     p.n_seqs = (int32_t)(std::min(b.decode.size(), c0 + mpa::kMaxPlanSeqs) - c0);
     for (int k = 0; k < p.n_seqs; ++k) {
