@@ -1760,22 +1760,25 @@ __device__ inline u32x4 rope_chunk(const typename Tr<DT>::Elem* row, int c, int 
 #pragma clang fp contract(off)
   using T = Tr<DT>;
   constexpr int X = T::X;
-  const u32x4 w = *reinterpret_cast<const u32x4*>(row + c * X);
+  // no branch, so that a lane's loads for several chunks are in flight together
   const int e0 = c * X;
-  if (e0 >= 2 * half) return w;
-  const bool lo = e0 < half;
-  const u32x4 wp = *reinterpret_cast<const u32x4*>(row + (lo ? e0 + half : e0 - half));
-  const int j0 = lo ? e0 : e0 - half;
+  const bool turned = e0 < 2 * half, lo = e0 < half;
+  const u32x4 w = *reinterpret_cast<const u32x4*>(row + e0);
+  const u32x4 wp = *reinterpret_cast<const u32x4*>(row + (!turned ? e0 : lo ? e0 + half : e0 - half));
+  const float* ang = cs + 2 * (!turned ? 0 : lo ? e0 : e0 - half);
   float x[X], xp[X], y[X];
   T::unpack(w, x);
   T::unpack(wp, xp);
 #pragma unroll
   for (int e = 0; e < X; ++e) {
-    const float a = x[e] * cs[2 * (j0 + e)];
-    const float b = xp[e] * cs[2 * (j0 + e) + 1];
+    const float a = x[e] * ang[2 * e];
+    const float b = xp[e] * ang[2 * e + 1];
     y[e] = lo ? a - b : a + b;
   }
-  return T::pack(y);
+  u32x4 r = T::pack(y);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = turned ? r[i] : w[i];
+  return r;
 }
 
 // Rotates the hq head rows of one token's query in place (angle row cs): a
@@ -1835,7 +1838,7 @@ __device__ inline void rotate_query(typename Tr<DT>::Elem* q, int hq, int half, 
 // stored are the plain append's.
 // ROPE: the keys are rotated on the way, and the launch's further waves, one
 // per new token, rotate the query rows.  3,001 tokens of 32 / 8 heads of 128
-// (74 MB): 20.6 us; a wave per token for all three, with the single-token
+// (74 MB): 17.6 us; a wave per token for all three, with the single-token
 // append's scattered V elements and each query chunk loaded twice, took 31.8.
 template <int DT, int D, bool ROPE>
 __global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendBlockPlan p, RopeArgs rope) {
@@ -1905,20 +1908,25 @@ __global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendB
   }
 
   // V: this lane's dims d = DPL * lane + i of every new token of the block
-  CE vals[kBlock][DPL];
+  // (slots outside [s0, s1) reload a valid row, so that all loads are in
+  // flight before the first is converted)
+  NE raw[kBlock][DPL];
 #pragma unroll
   for (int t = 0; t < kBlock; ++t) {
-    if (t < s0 || t >= s1) continue;
-    const NE* src = vn + (size_t)(row_s0 + t - s0) * rstride + DPL * lane;
+    const NE* src = vn + (size_t)(row_s0 + min(max(t, s0), s1 - 1) - s0) * rstride + DPL * lane;
+#pragma unroll
+    for (int i = 0; i < DPL; ++i) raw[t][i] = src[i];
+  }
+  CE vals[kBlock][DPL];
+#pragma unroll
+  for (int t = 0; t < kBlock; ++t)
 #pragma unroll
     for (int i = 0; i < DPL; ++i) {
-      if constexpr (DT == 2) {
-        vals[t][i] = (uint8_t)f32_to_e4m3(__uint_as_float((unsigned)src[i] << 16) * a.inv_v_scale);
-      } else {
-        vals[t][i] = src[i];
-      }
+      if constexpr (DT == 2)
+        vals[t][i] = (uint8_t)f32_to_e4m3(__uint_as_float((unsigned)raw[t][i] << 16) * a.inv_v_scale);
+      else
+        vals[t][i] = raw[t][i];
     }
-  }
   CE* vdst = reinterpret_cast<CE*>(a.v_cache) + (head * D + DPL * lane) * kBlock;
   if (s0 == 0 && s1 == kBlock) {
 #pragma unroll
