@@ -106,6 +106,21 @@ Batch classify(const mpa_shape* sh, const int32_t* qsl) {
   return b;
 }
 
+// The tuning overrides in the environment, read at each call: the value when
+// it is a whole number in [lo, hi] and a multiple of `step`, else -1 (not set).
+// The planner and the memo's key both go through these, so that an override
+// that is not taken plans (and is remembered) as none at all.
+int env_override(const char* name, long lo, long hi, long step) {
+  const char* e = getenv(name);
+  if (!e) return -1;
+  char* end = nullptr;
+  const long v = strtol(e, &end, 10);
+  return end != e && v >= lo && v <= hi && v % step == 0 ? (int)v : -1;
+}
+int env_split_tokens() { return env_override("MPA_SPLIT_TOKENS", kBlock, 1024, kBlock); }
+int env_prefill_splits() { return env_override("MPA_PREFILL_SPLITS", 1, 64, 1); }
+int env_decode_range() { return env_override("MPA_DECODE_RANGE", 0, 1 << 30, 1); }
+
 // How a decode row of L keys is split at nominal split size S: into
 // n = ceil(L / S) parts of equal size, rounded up to whole cache blocks, so
 // that the waves of a launch stream about the same number of bytes (a fixed
@@ -133,10 +148,7 @@ RowSplit row_split(int L, int S) {
 // merge work).  MPA_SPLIT_TOKENS (a multiple of 16, at most 1024) overrides
 // it for tuning sweeps.
 int choose_split(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens) {
-  if (const char* env = getenv("MPA_SPLIT_TOKENS")) {
-    const int v = atoi(env);
-    if (v >= kBlock && v <= 1024 && v % kBlock == 0) return v;
-  }
+  if (const int v = env_split_tokens(); v > 0) return v;
   if (b.decode.empty()) return 1024;
   const long slots = mpa::decode_wave_slots(sh->dtype, sh->head_dim, false);
   const long overhead = 64;
@@ -213,8 +225,8 @@ long range_parts(long at, long nb, int range) { return (at + nb - 1) / range - a
 std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, int split,
                                         bool ranges) {
   std::vector<DecodeLaunch> out;
-  const char* env = getenv("MPA_DECODE_RANGE");
-  const int forced = env ? atoi(env) : getenv("MPA_SPLIT_TOKENS") ? 0 : -1;
+  const int range_env = env_decode_range();
+  const int forced = range_env < 0 && env_split_tokens() > 0 ? 0 : range_env;
   const long slots = ranges && forced != 0 ? mpa::decode_wave_slots(sh->dtype, sh->head_dim, true) : 0;
   for (size_t c0 = 0; c0 < b.decode.size(); c0 += mpa::kMaxPlanSeqs) {
     DecodeLaunch d;
@@ -231,7 +243,7 @@ std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, con
       const long per_head = std::max(1L, slots / sh->num_kv_heads);
       const long range = (blocks + per_head - 1) / per_head;
       if (forced > 0)
-        d.range_blocks = forced;
+        d.range_blocks = (int)std::min((long)forced, blocks);
       else if (slots > 0 && range >= range_min_blocks(sh->dtype, sh->head_dim))
         d.range_blocks = (int)range;
     }
@@ -414,10 +426,7 @@ std::vector<PrefillSegment> prefill_segments(const mpa_shape* sh, const Batch& b
                                              const int32_t* qsl, bool balance) {
   std::vector<PrefillSegment> best = split_layout(b, seq_lens, qsl, 1);
   if (sh->dtype == MPA_F32 || b.prefill.empty()) return best;
-  if (const char* env = getenv("MPA_PREFILL_SPLITS")) {
-    const int v = atoi(env);
-    if (v >= 1 && v <= 64) return split_layout(b, seq_lens, qsl, v);
-  }
+  if (const int v = env_prefill_splits(); v > 0) return split_layout(b, seq_lens, qsl, v);
   const int slots = mpa::kPrefillSplitTarget;
   double row_us = kPlanMergeRowUs, margin = 1e-9;
   auto time = [&](const std::vector<PrefillSegment>& v, double cutoff, double* work = nullptr) {
@@ -539,7 +548,7 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
     p.items = ditems + assign_prefill_items(&p.prefill, ditems);
     return workspace_bytes(sh, p.items) <= MPA_SCRATCH_BYTES;
   };
-  if (!place() && !getenv("MPA_DECODE_RANGE")) {
+  if (!place() && env_decode_range() < 0) {
     // Ranges cut every row, also short ones, and balancing splits chunks, so
     // their partial results can take more room than those of row splits and
     // whole chunks.  A step past the fixed array of
@@ -562,11 +571,6 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
   return p;
 }
 
-int env_int(const char* name) {
-  const char* e = getenv(name);
-  return e ? atoi(e) : -1;
-}
-
 // The plan of a valid batch, from a per-thread memo of the last one: one step
 // asks for its plan several times (workspace sizing, the append, each
 // attention half, the step model).  The key is everything the plan depends
@@ -587,7 +591,7 @@ const StepPlan& step_plan(const mpa_shape* sh, const int32_t* seq_lens, const in
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) dev = -1;
   const int32_t key[8] = {sh->num_q_heads, sh->num_kv_heads, sh->head_dim, (int32_t)sh->dtype, dev,
-                          env_int("MPA_SPLIT_TOKENS"), env_int("MPA_PREFILL_SPLITS"), env_int("MPA_DECODE_RANGE")};
+                          env_split_tokens(), env_prefill_splits(), env_decode_range()};
   const size_t n = (size_t)sh->num_seqs;
   if (memcmp(key, m.key, sizeof key) != 0 || m.seq_lens.size() != n || m.qsl.size() != n + 1 ||
       (n && memcmp(m.seq_lens.data(), seq_lens, n * sizeof(int32_t)) != 0) ||
@@ -1110,6 +1114,7 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
     p.n_seqs = (int32_t)(d.c1 - d.c0);
     p.item_base = (int32_t)base;
     p.range_blocks = d.range_blocks;
+    p.n_ranges = 0;
     int acc = 0, at = 0;
     for (int k = 0; k < p.n_seqs; ++k) {
       const int s = plan.batch.decode[d.c0 + k];
@@ -1130,6 +1135,7 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
       }
     }
     p.part[p.n_seqs] = at;
+    if (d.range_blocks > 0) p.n_ranges = (int32_t)(((long)at + d.range_blocks - 1) / d.range_blocks);
     p.item_start[p.n_seqs] = acc;
     base += acc;
     hipError_t e = mpa::launch_decode(a, p, acc, shape->dtype, shape->head_dim, st);

@@ -57,6 +57,7 @@ struct DecodePlan {
   int32_t n_seqs;
   int32_t item_base;
   int32_t range_blocks;
+  int32_t n_ranges;  // of this launch; waves past them (the last workgroup's padding) have no work
   int32_t seq[kMaxPlanSeqs];
   int32_t part[kMaxPlanSeqs + 1];
   int32_t item_start[kMaxPlanSeqs + 1];

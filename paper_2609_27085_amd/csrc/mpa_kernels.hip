@@ -722,9 +722,9 @@ __global__ __launch_bounds__(64 * WPG, decode_waves_per_simd(DT, D)) void decode
   const int G = a.hq / a.hkv;
   int j, blk = 0, blk_end = 0;
   if constexpr (STREAM) {
+    if (item >= p.n_ranges) return;  // by number: item * range_blocks may pass 2^31 here
     blk = item * p.range_blocks;
     blk_end = min(blk + p.range_blocks, p.part[p.n_seqs]);
-    if (blk >= blk_end) return;
     j = upper_index(p.part, p.n_seqs, blk);
   } else {
     if (item >= p.item_start[p.n_seqs]) return;
@@ -2064,7 +2064,7 @@ struct DecodeL {
     }
     if (p.range_blocks > 0) {
       constexpr int W = kStreamWaves<DT, D>;
-      const long waves = (long)((p.part[p.n_seqs] + p.range_blocks - 1) / p.range_blocks) * a.hkv;
+      const long waves = (long)p.n_ranges * a.hkv;
       hipLaunchKernelGGL((decode_kernel<DT, D, W, true>), dim3((unsigned)((waves + W - 1) / W)), dim3(64 * W), 0, stream,
                          a, p);
       return hipGetLastError();
