@@ -119,7 +119,7 @@ int env_override(const char* name, long lo, long hi, long step) {
 }
 int env_split_tokens() { return env_override("MPA_SPLIT_TOKENS", kBlock, 1024, kBlock); }
 int env_prefill_splits() { return env_override("MPA_PREFILL_SPLITS", 1, 64, 1); }
-int env_decode_range() { return env_override("MPA_DECODE_RANGE", 0, 1 << 30, 1); }
+int env_decode_range() { return env_override("MPA_DECODE_RANGE", 0, 1 << 26, 1); }  // in tokens below 2^31
 
 // How a decode row of L keys is split at nominal split size S: into
 // n = ceil(L / S) parts of equal size, rounded up to whole cache blocks, so
@@ -243,7 +243,7 @@ std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, con
       const long per_head = std::max(1L, slots / sh->num_kv_heads);
       const long range = (blocks + per_head - 1) / per_head;
       if (forced > 0)
-        d.range_blocks = (int)std::min((long)forced, blocks);
+        d.range_blocks = forced;
       else if (slots > 0 && range >= range_min_blocks(sh->dtype, sh->head_dim))
         d.range_blocks = (int)range;
     }
@@ -564,7 +564,8 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
       }
     }
   }
-  if (p.split == 0 && !p.decode.empty() && p.decode[0].range_blocks > 0) p.split = p.decode[0].range_blocks * kBlock;
+  if (p.split == 0 && !p.decode.empty() && p.decode[0].range_blocks > 0)
+    p.split = (int)std::min((long)INT32_MAX, (long)p.decode[0].range_blocks * kBlock);
   if (p.split == 0) p.split = 1024;
   for (const auto& d : p.decode) p.decode_split |= d.split;
   for (const auto& c : p.prefill) p.prefill_split |= c.nsplit > 1;
@@ -814,7 +815,7 @@ int mpa_get_plan_info(const mpa_shape* shape, const int32_t* seq_lens_host, cons
   info->num_prefill_seqs = (int32_t)b.prefill.size();
   // the nominal part size: that of the first launch's ranges, if it has them
   const bool ranged = !plan.decode.empty() && plan.decode[0].range_blocks > 0;
-  info->split_tokens = ranged ? plan.decode[0].range_blocks * kBlock : plan.split;
+  info->split_tokens = ranged ? (int32_t)std::min((long)INT32_MAX, (long)plan.decode[0].range_blocks * kBlock) : plan.split;
   info->num_decode_items = 0;
   for (const auto& d : plan.decode) info->num_decode_items += (int32_t)d.items;
   long tiles = 0;

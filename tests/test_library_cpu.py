@@ -375,8 +375,7 @@ def test_noalloc_refuses_batches_beyond_its_array():
 def test_tuning_overrides_out_of_range_are_ignored(monkeypatch):
     """A tuning override that is no valid value plans, and is remembered, as
     no override at all, in this thread (which planned the batch before) and in
-    a fresh one; a decode range past the batch's blocks is cut to them, so
-    that a wave's first block always lies inside the launch."""
+    a fresh one.  The longest decode range (2^26 blocks) is one part per row."""
     import threading
 
     sl, qsl = np.asarray([900, 400], np.int32), np.asarray([0, 1, 2], np.int32)
@@ -395,14 +394,13 @@ def test_tuning_overrides_out_of_range_are_ignored(monkeypatch):
 
     unset = plan()
     for name, values in (("MPA_SPLIT_TOKENS", ("-1", "0", "8", "24", "2048", "many", "")),
-                         ("MPA_DECODE_RANGE", ("-1", "-7", "9999999999999", "many", "")),
+                         ("MPA_DECODE_RANGE", ("-1", "-7", "1000000000", "67108865", "9999999999999", "many", "")),
                          ("MPA_PREFILL_SPLITS", ("-1", "0", "65", "many"))):
         for v in values:
             monkeypatch.setenv(name, v)
             assert plan() == unset == fresh(), (name, v)
         monkeypatch.delenv(name)
     blocks = -(-900 // 16) + -(-400 // 16)
-    for v, n in (("1000000000", 2), (str(blocks), 2), (str(blocks - 1), 3)):
-        monkeypatch.setenv("MPA_DECODE_RANGE", v)
-        items = plan()[1]
-        assert plan() == fresh() and plan()[0] == 16 * min(int(v), blocks) and items == n, (v, plan())
+    for v, n in ((1 << 26, 2), (blocks, 2), (blocks - 1, 3)):
+        monkeypatch.setenv("MPA_DECODE_RANGE", str(v))
+        assert plan() == fresh() and plan()[:2] == (16 * v, n), (v, plan())
