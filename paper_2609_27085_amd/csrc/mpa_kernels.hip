@@ -647,9 +647,12 @@ __device__ inline void append_decode_token(const AttnArgs& a, int s, int pos, in
 // and row, then the accumulators, half of the dims at a time; wave w adds up
 // the rows' dims 16 * mt for its mt.  `l` is the row's sum over the lane
 // groups, out and lse (lse may be null) the lane's row.  A wave that saw no
-// key of a row has max -inf and weight 0; wave 0 has key 0, which every row
-// sees.
+// key of a row (or only keys of score -inf) has max -inf and weight 0.
 constexpr int kKeyWaves = 8;
+
+// 2^(m - M) for a partial result's maximum m <= M: 0 where m is -inf, also
+// when every partial result's is.
+__device__ inline float partial_weight(float m, float M) { return exp2_fast(m - (M == -INFINITY ? 0.f : M)); }
 
 template <int DT, int D>
 __device__ inline void merge_waves(const RowState<DT, D>& st, float l, bool poison, float v_scale, bool row_ok,
@@ -676,7 +679,7 @@ __device__ inline void merge_waves(const RowState<DT, D>& st, float l, bool pois
       for (int k = 0; k < kKeyWaves; ++k) M = fmaxf(M, ml[k][0][n]);
 #pragma unroll
       for (int k = 0; k < kKeyWaves; ++k) {
-        w[k] = exp2_fast(ml[k][0][n] - M);
+        w[k] = partial_weight(ml[k][0][n], M);
         sum += ml[k][1][n] * w[k];
       }
     }
@@ -917,9 +920,9 @@ __device__ inline MergeState merge_range(const float* ml, size_t ml_stride, cons
       mk = v.x;
       lk = v.y;
     }
-    const float gm = fmaxf(r.M, wave_max64(mk));  // every split holds a key: finite
-    const float wk = lane < cnt ? exp2_fast(mk - gm) : 0.f;
-    const float rescale = exp2_fast(r.M - gm);    // M = -inf on the first group: 0
+    const float gm = fmaxf(r.M, wave_max64(mk));
+    const float wk = lane < cnt ? partial_weight(mk, gm) : 0.f;
+    const float rescale = partial_weight(r.M, gm);  // M = -inf on the first group: 0
     r.lsum = r.lsum * rescale + wave_sum64(wk * lk);
     r.o *= rescale;
     for (int k = 0; k < cnt; k += RPI * kMergeUnroll) {
@@ -992,13 +995,13 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(AttnArgs a, Dec
     if (lane < D / 4) rows[wave][lane] = r.o;
     __syncthreads();
     if (wave != 0) return;
-    float M = ml[0][0];  // wave 0 has splits: finite
+    float M = ml[0][0];
 #pragma unroll
     for (int w = 1; w < kMergeWaves; ++w) M = fmaxf(M, ml[w][0]);
     MergeState all = {M, 0.f, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int w = 0; w < kMergeWaves; ++w) {
-      const float f = exp2_fast(ml[w][0] - M);  // a wave without splits: 0
+      const float f = partial_weight(ml[w][0], M);  // a wave without splits: 0
       all.lsum += ml[w][1] * f;
       all.o += rows[w][lane % (D / 4)] * f;
     }
@@ -1477,7 +1480,9 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : D == 64 ? 3 : 2) void 
       // The reference maximum m_ref moves only when some score of the wave
       // exceeds it by more than thresh (probabilities stay <= 2^8).  On a
       // wave's first tile it is still -inf and is taken from the tile's row
-      // maximum; on later tiles the probabilities are formed with the current
+      // maximum, but not below -2^63 in log2 units: a row whose scores there
+      // are all -inf then has probabilities 0 (not 2^(-inf + inf)), and any
+      // later score moves the reference.  On later tiles the probabilities are formed with the current
       // reference first, and since a score past the threshold makes its
       // probability -- and so this lane's row-sum partial -- at least 2^8
       // after bf16 rounding, the tile's maximum is taken only when some
@@ -1522,6 +1527,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : D == 64 ? 3 : 2) void 
       if (kt == kt_begin) {
         const float mx = row_max(st);
         if (__any(mx > m_ref + thresh)) move_reference(mx);
+        m_ref = fmaxf(m_ref, -0x1p60f * thresh);
       }
       make_p(st, m_ref * c);
       if (kt != kt_begin && __any(!((l4[0] + l4[1]) + (l4[2] + l4[3]) < 256.f))) {
