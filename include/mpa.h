@@ -331,13 +331,23 @@ typedef struct {
                                 cut into ranges of split_tokens instead, and a row's parts are
                                 its intersections with them */
   int32_t num_decode_items;  /* (sequence, split) work items */
-  int32_t num_prefill_tiles; /* (sequence, query tile, KV split, KV head) work items */
+  int32_t num_prefill_tiles; /* (sequence, query tile, KV split, KV head) work items, in tiles of 256
+                                (token, head) rows (f32 caches: 64) whatever the launch's form
+                                (mpa_get_prefill_rows) */
   int32_t decode_launches;   /* decode kernel launches (sequence chunks) */
   int32_t prefill_max_splits; /* most KV splits of any prefill chunk (0: no chunk) */
 } mpa_plan_info;
 
 int mpa_get_plan_info(const mpa_shape* shape, const int32_t* seq_lens_host,
                       const int32_t* query_start_loc_host, mpa_plan_info* info);
+
+/*
+ * The (token, head) rows per workgroup of prefill launch `launch` (0, 1, ...)
+ * of a batch: the form the library takes for its size.  bf16: 256, or 128
+ * (half tiles); fp8: 256; f32: 64.  MPA_ERR_INVALID past the batch's last launch.
+ */
+int mpa_get_prefill_rows(const mpa_shape* shape, const int32_t* seq_lens_host,
+                         const int32_t* query_start_loc_host, int32_t launch, int32_t* rows);
 
 /*
  * Step-time model (host only; launches nothing).

@@ -45,6 +45,7 @@ EXPORTS = (
     "mpa_workspace_size",
     "mpa_status_string",
     "mpa_get_plan_info",
+    "mpa_get_prefill_rows",
     "mpa_decode_attention",
     "mpa_prefill_attention",
     "mpa_default_rates",
@@ -172,6 +173,8 @@ def lib() -> ctypes.CDLL:
         L.mpa_status_string.argtypes = [ctypes.c_int]
         L.mpa_get_plan_info.restype = ctypes.c_int
         L.mpa_get_plan_info.argtypes = [_SHP, _I32P, _I32P, ctypes.POINTER(MpaPlanInfo)]
+        L.mpa_get_prefill_rows.restype = ctypes.c_int
+        L.mpa_get_prefill_rows.argtypes = [_SHP, _I32P, _I32P, ctypes.c_int32, _I32P]
         L.mpa_default_rates.restype = None
         L.mpa_default_rates.argtypes = [ctypes.POINTER(MpaRates)]
         L.mpa_predict_step.restype = ctypes.c_int
@@ -260,6 +263,17 @@ def plan_info(shape: MpaShape, seq_lens_host, qsl_host) -> MpaPlanInfo:
     if rc != MPA_OK:
         raise MpaError(rc, "mpa_get_plan_info")
     return info
+
+
+def prefill_rows(shape: MpaShape, seq_lens_host, qsl_host, launch: int = 0) -> int:
+    """The (token, head) rows per workgroup of a batch's prefill launch
+    (mpa_get_prefill_rows)."""
+    sl, qs = _host_i32(seq_lens_host), _host_i32(qsl_host)
+    rows = ctypes.c_int32()
+    rc = lib().mpa_get_prefill_rows(ctypes.byref(shape), _i32p(sl), _i32p(qs), int(launch), ctypes.byref(rows))
+    if rc != MPA_OK:
+        raise MpaError(rc, "mpa_get_prefill_rows")
+    return rows.value
 
 
 def default_rates() -> MpaRates:

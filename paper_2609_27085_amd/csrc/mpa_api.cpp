@@ -346,6 +346,17 @@ double list_makespan(const std::vector<double>& jobs, int copies, int slots) {
   return makespan;
 }
 
+// The work units of segment g in unit order, in query tiles of qt tokens:
+// f(64-key tiles of the unit).
+template <typename F>
+void segment_units(const PrefillSegment& g, const int32_t* seq_lens, const int32_t* qsl, int qt, F f) {
+  const int P = seq_lens[g.seq] - (qsl[g.seq + 1] - qsl[g.seq]) + g.tok0;  // keys before the segment
+  for (int q = 0; q < (g.ntok + qt - 1) / qt; ++q) {
+    const int all = (P + std::min(q * qt + qt, g.ntok) + 63) / 64;
+    for (int x = 0; x < g.nsplit; ++x) f(x == g.nsplit - 1 ? all - x * g.tiles : g.tiles);
+  }
+}
+
 // Predicted device time of the prefill launches for a split layout: per
 // launch (kMaxPrefillSeqs chunks), the makespan of its workgroups -- each
 // wg_us + tile_us per 64-key tile -- dealt in launch order (the longest
@@ -367,17 +378,12 @@ double prefill_time(const mpa_shape* sh, const int32_t* seq_lens, const int32_t*
     double partial_rows = 0.0, work = 0.0, shortest = INFINITY;
     for (size_t k = c0; k < c1; ++k) {
       const PrefillSegment& g = segments[k];
-      const int P = seq_lens[g.seq] - (qsl[g.seq + 1] - qsl[g.seq]) + g.tok0;  // keys before the segment
       if (g.nsplit > 1) partial_rows += (double)g.ntok * sh->num_q_heads * g.nsplit;
-      for (int q = 0; q < (g.ntok + qt - 1) / qt; ++q) {
-        const int kend = P + std::min(q * qt + qt - 1, g.ntok - 1) + 1;
-        const int all = (kend + 63) / 64;
-        for (int x = 0; x < g.nsplit; ++x) {
-          jobs.push_back(wg_us + tile_us * (x == g.nsplit - 1 ? all - x * g.tiles : g.tiles));
-          work += jobs.back();
-          shortest = std::min(shortest, jobs.back());
-        }
-      }
+      segment_units(g, seq_lens, qsl, qt, [&](int tiles) {
+        jobs.push_back(wg_us + tile_us * tiles);
+        work += jobs.back();
+        shortest = std::min(shortest, jobs.back());
+      });
     }
     if (work_us) *work_us += work * sh->num_kv_heads;
     std::reverse(jobs.begin(), jobs.end());  // blockIdx order: the last unit first, each unit once per KV head
@@ -504,6 +510,73 @@ std::vector<PrefillSegment> prefill_segments(const mpa_shape* sh, const Batch& b
   return best;
 }
 
+// (token, head) rows per workgroup of the bf16 launch of segments [c0, c1).
+// The planner counts workgroups of 256 rows (eight waves, one to a CU).
+// Launches of few of them may run as workgroups of 128 (four waves, two to a
+// CU, or three at head_dim 64): a prompt's tiles grow from one 64-key tile to
+// the chunk's length, and half tiles let a long and a short one share a CU and
+// fill each other's gaps.  They read K and V twice as often for it, which
+// costs up to a tenth where the tiles are alike (a long prefix), so a launch
+// takes the form with the shorter predicted time: its longest queue of
+// workgroups dealt in launch order to the CUs (half tiles as if one after
+// another), its work per CU (a tile takes longer the more CUs are busy) and,
+// for half tiles, its longest one (which runs beside others to its end).  The
+// figures are fitted to 226 launches of whole chunks (rms 3-6 %).  On those
+// and 173 KV-split ones, half tiles by this rule were at most 3.7 % slower
+// than whole tiles and 6 % faster in the mean.  Measured (us, 256 -> 128 rows):
+//   d 128: 1,003 tokens of 32 / 8 heads on 500 41.4 -> 33.4, on 2,000 61.0 ->
+//     64.2; 2,027 on 0 53.5 -> 49.4, on 8,000 261 -> 272, on 32,000 883 -> 942;
+//     2,987 on 0 80.8 -> 78.6, on 2,000 165.9 -> 176.6; 3,499 on 0 97.6 -> 105.8;
+//   d 64: 2,038 of 16 / 2 on 0 38.9 -> 29.5, on 32,000 (KV-split) 301 -> 317;
+//     2,539 of 32 / 8 on 2,000 95.8 -> 85.2, on 32,000 755 -> 728; 3,499 on
+//     2,000 126.5 -> 130.6.
+// The model is not asked where it was not fitted: KV-split launches of
+// 128-wide heads stay whole, those of 64-wide heads from 1,024 workgroups on
+// are half tiles (0.93-0.97 of the time in 12 launches), and other launches
+// past 448, or at 128-wide heads past 128 with several chunks (which meet on a
+// CU in no particular order), stay whole.
+int prefill_rows_bf16(const mpa_shape* sh, const std::vector<PrefillSegment>& segments, size_t c0, size_t c1,
+                      const int32_t* seq_lens, const int32_t* qsl) {
+  const int qt = q_tile(sh);
+  const bool d64 = sh->head_dim == 64;
+  long groups = 0;
+  bool split = false;
+  for (size_t k = c0; k < c1; ++k) {
+    groups += (long)(segments[k].ntok + qt - 1) / qt * segments[k].nsplit * sh->num_kv_heads;
+    split |= segments[k].nsplit > 1;
+  }
+  if (d64 && groups >= 1024) return mpa::kPrefillRowsHalf;
+  if (groups >= (d64 || c1 - c0 == 1 ? 448 : 128) || (split && !d64)) return mpa::kPrefillRowsMfma;
+  // a form's time: fixed + per_slot * (tiles of the longest queue, each unit
+  // `start` more) + per_cu * (tiles per CU) + longest * (tiles of the longest unit)
+  auto predict = [&](int rows, double fixed_us, double start, double per_slot, double per_cu, double longest) {
+    std::vector<double> jobs;
+    double tiles = 0.0, most = 0.0;
+    for (size_t k = c0; k < c1; ++k)
+      segment_units(segments[k], seq_lens, qsl, rows / (sh->num_q_heads / sh->num_kv_heads), [&](int n) {
+        jobs.push_back(start + n);
+        tiles += n;
+        most = std::max(most, (double)n);
+      });
+    std::reverse(jobs.begin(), jobs.end());  // launch order
+    return fixed_us + per_slot * list_makespan(jobs, sh->num_kv_heads, mpa::kPrefillSplitTarget) +
+           per_cu * tiles * sh->num_kv_heads / mpa::kPrefillSplitTarget + longest * most;
+  };
+  const double whole = d64 ? predict(mpa::kPrefillRowsMfma, 4.7, 6.0, 0.79, 0.252, 0.0)
+                           : predict(mpa::kPrefillRowsMfma, 1.8, 8.0, 1.123, 0.456, 0.023);
+  const double half = d64 ? predict(mpa::kPrefillRowsHalf, 10.1, 0.0, 0.295, 0.18, 0.166)
+                          : predict(mpa::kPrefillRowsHalf, 8.5, 4.0, 0.406, 0.325, 0.382);
+  return half < 0.98 * whole ? mpa::kPrefillRowsHalf : mpa::kPrefillRowsMfma;
+}
+
+// The same for a launch of any cache type.
+int prefill_rows(const mpa_shape* sh, const std::vector<PrefillSegment>& segments, size_t c0, size_t c1,
+                 const int32_t* seq_lens, const int32_t* qsl) {
+  if (sh->dtype == MPA_F32) return mpa::kPrefillRows;
+  if (sh->dtype == MPA_FP8) return mpa::kPrefillRowsMfma;
+  return prefill_rows_bf16(sh, segments, c0, c1, seq_lens, qsl);
+}
+
 // Gives split segments their workspace slots, from first_item on; returns the
 // number of slots given.
 long assign_prefill_items(std::vector<PrefillSegment>* segments, long first_item) {
@@ -523,6 +596,7 @@ struct StepPlan {
   int split = 0;  // nominal tokens per part of rows split on their own
   std::vector<DecodeLaunch> decode;
   std::vector<PrefillSegment> prefill;
+  std::vector<int> prefill_rows;      // (token, head) rows per workgroup of each prefill launch
   long items = 0;                     // workspace slots
   bool decode_split = false, prefill_split = false;  // some row / chunk has several parts
 };
@@ -569,6 +643,9 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
   if (p.split == 0) p.split = 1024;
   for (const auto& d : p.decode) p.decode_split |= d.split;
   for (const auto& c : p.prefill) p.prefill_split |= c.nsplit > 1;
+  for (size_t c0 = 0; c0 < p.prefill.size(); c0 += mpa::kMaxPrefillSeqs)
+    p.prefill_rows.push_back(
+        prefill_rows(sh, p.prefill, c0, std::min(p.prefill.size(), c0 + mpa::kMaxPrefillSeqs), seq_lens, qsl));
   return p;
 }
 
@@ -831,6 +908,17 @@ int mpa_get_plan_info(const mpa_shape* shape, const int32_t* seq_lens_host, cons
   return MPA_OK;
 }
 
+int mpa_get_prefill_rows(const mpa_shape* shape, const int32_t* seq_lens_host, const int32_t* qsl_host, int32_t launch,
+                         int32_t* rows) {
+  if (!rows || launch < 0) return MPA_ERR_INVALID;
+  int rc = check_batch(shape, seq_lens_host, qsl_host, nullptr, false);
+  if (rc != MPA_OK) return rc;
+  const StepPlan& plan = step_plan(shape, seq_lens_host, qsl_host);
+  if ((size_t)launch >= plan.prefill_rows.size()) return MPA_ERR_INVALID;
+  *rows = plan.prefill_rows[launch];
+  return MPA_OK;
+}
+
 void mpa_default_rates(mpa_rates* r) {
   if (!r) return;
   // Least-squares fit (log error) to the phase times bench.py measured on
@@ -1022,39 +1110,6 @@ namespace {
 
 enum Phase { kDecode = 1, kPrefill = 2 };
 
-// (token, head) rows per workgroup of the launch of segments [c0, c1).  The
-// planner counts workgroups of 256 rows (eight waves, one to a CU).  bf16
-// launches of few of them run as workgroups of 128 (four waves, two to a CU,
-// or three at head_dim 64): a prompt's tiles grow from one 64-key tile to the
-// chunk's length, and half tiles let a long and a short one share a CU and
-// fill each other's gaps; larger launches read K and V twice as often for it.
-// Measured (us, 256 -> 128 rows):
-//   d 128: 64 workgroups (8/2 heads, 2,000 tokens on 0) 50.2 -> 38.8, 128
-//     (32/8, 1,000 on 500) 41.1 -> 34.4, 376 (3,000 on 0) 84.2 -> 81.1, 504
-//     (4,000 on 0) 126.8 -> 139.9; KV-split (2,048 on 4,096) 65.5 -> 68.9;
-//     three chunks of 500 in 48 20.3 -> 16.8, in 192 22.3 -> 24.4 (half tiles
-//     of several chunks meet on a CU in no particular order);
-//   d 64: 126 (16/2, 2,000 on 400) 44.7 -> 34.8, 256 (4,096 on 4,096) 139.0 ->
-//     124.4, 240 (300 on 20,011, KV-split) 49.7 -> 47.2, 512 (32/8, 4,096 on
-//     4,096) 223.8 -> 235.1, 1,024 (8,192 on 32,768) 2,512 -> 2,419.
-int prefill_rows(const mpa_shape* sh, const std::vector<PrefillSegment>& segments, size_t c0, size_t c1) {
-  if (sh->dtype == MPA_F32) return mpa::kPrefillRows;
-  if (sh->dtype != MPA_BF16) return mpa::kPrefillRowsMfma;
-  const int qt = q_tile(sh);
-  long groups = 0;
-  bool split = false;
-  for (size_t k = c0; k < c1; ++k) {
-    groups += (long)(segments[k].ntok + qt - 1) / qt * segments[k].nsplit * sh->num_kv_heads;
-    split |= segments[k].nsplit > 1;
-  }
-  bool half;
-  if (sh->head_dim == 64)
-    half = groups < 448 || groups >= 1024;
-  else
-    half = !split && groups < (c1 - c0 == 1 ? 448 : 128);
-  return half ? mpa::kPrefillRowsHalf : mpa::kPrefillRowsMfma;
-}
-
 int run_attention(int phases, const mpa_shape* shape, const void* q, const void* k_cache, const void* v_cache,
                   const int32_t* block_tables, const int32_t* seq_lens, const int32_t* query_start_loc,
                   const int32_t* seq_lens_host, const int32_t* query_start_loc_host,
@@ -1148,7 +1203,7 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
   for (size_t c0 = 0; prefill && c0 < plan.prefill.size(); c0 += mpa::kMaxPrefillSeqs) {
     mpa::PrefillPlan p;
     p.n_seqs = (int32_t)(std::min(plan.prefill.size(), c0 + mpa::kMaxPrefillSeqs) - c0);
-    p.rows = prefill_rows(shape, plan.prefill, c0, c0 + p.n_seqs);
+    p.rows = plan.prefill_rows[c0 / mpa::kMaxPrefillSeqs];
     p.q_tile = p.rows / (shape->num_q_heads / shape->num_kv_heads);
     const int qt = p.q_tile;
     int acc = 0, rows = 0;
