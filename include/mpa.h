@@ -344,7 +344,8 @@ int mpa_get_plan_info(const mpa_shape* shape, const int32_t* seq_lens_host,
 /*
  * The (token, head) rows per workgroup of prefill launch `launch` (0, 1, ...)
  * of a batch: the form the library takes for its size.  bf16: 256, or 128
- * (half tiles); fp8: 256; f32: 64.  MPA_ERR_INVALID past the batch's last launch.
+ * (half tiles); fp8: 256; f32: 64, or 16 with the keys dealt to a workgroup's
+ * waves.  MPA_ERR_INVALID past the batch's last launch.
  */
 int mpa_get_prefill_rows(const mpa_shape* shape, const int32_t* seq_lens_host,
                          const int32_t* query_start_loc_host, int32_t launch, int32_t* rows);

@@ -569,10 +569,64 @@ int prefill_rows_bf16(const mpa_shape* sh, const std::vector<PrefillSegment>& se
   return half < 0.98 * whole ? mpa::kPrefillRowsHalf : mpa::kPrefillRowsMfma;
 }
 
+// (token, head) rows per workgroup of the f32 launch of segments [c0, c1): 64
+// (a tile: four waves of 16 rows, all their keys each) or 16 (eight waves, an
+// eighth of the keys each, merged in LDS; four workgroups to a tile).  A wave
+// needs 2,048 MFMA cycles per 16 keys and 128 dims in either form.  Up to two
+// tiles of a launch run on a CU at once, so one of up to 512 takes as long as
+// its longest tile or its longest pair (tile i and i + 256 of the launch);
+// 16-row workgroups spread over four times the slots, at the price of reading
+// K and V for 16 rows, not 64.  The form with the shorter predicted time is
+// taken.  The figures, in 16-key blocks, are fitted to 234 launches of 128-512
+// tiles (rms 2-3 %); on those the keys form, where taken, was at most 0.1 %
+// slower than tiles, and the better form was missed by 5 % at most.  Measured
+// (us, tiles -> keys; tokens on prefix):
+//   d 128: 128 tiles (8 / 2 heads, 1,024 on 500) 115.9 -> 56.7, 200 (1,600 on
+//     2,000) 262.9 -> 244.2, on 8,000 670 -> 745; 248 (1,984 on 500) 183.5 ->
+//     148.9, 256 (32 / 8, 512 on 500) 79.9 -> 88.2, 264 (528 on 500) 137.3 ->
+//     103.4, 496 (992 on 500) 215.9 -> 213.3, 504 (8 / 2, 4,032 on 500) 601 -> 470;
+//   d 64: 128 (16 / 2, 512 on 500) 43.8 -> 23.9, 200 (64 / 8, 200 on 0) 13.5 ->
+//     18.6, 496 (496 on 0) 32.3 -> 47.1, 496 (16 / 2, 1,984 on 0) 111.0 -> 101.3.
+// Larger launches keep whole tiles (600 tiles: 0.82-1.42 of their time in the
+// keys form, which the model does not tell apart).
+int prefill_rows_f32(const mpa_shape* sh, const std::vector<PrefillSegment>& segments, size_t c0, size_t c1,
+                     const int32_t* seq_lens, const int32_t* qsl) {
+  const int G = sh->num_q_heads / sh->num_kv_heads;
+  const int qt = q_tile(sh);
+  const int hkv = sh->num_kv_heads;
+  const size_t slots = mpa::kPrefillSplitTarget;
+  size_t tiles = 0;
+  for (size_t k = c0; k < c1; ++k) tiles += (size_t)(segments[k].ntok + qt - 1) / qt * hkv;
+  if (tiles > 2 * slots) return mpa::kPrefillRows;
+  const bool d64 = sh->head_dim == 64;
+  std::vector<int> blocks;   // of the tiles, in launch order, each once per KV head
+  std::vector<double> jobs;  // the 16-row workgroups of one KV head, in launch order
+  for (size_t k = c1; k-- > c0;) {
+    const PrefillSegment& g = segments[k];
+    const int P = seq_lens[g.seq] - (qsl[g.seq + 1] - qsl[g.seq]) + g.tok0;
+    for (int q = (g.ntok + qt - 1) / qt; q-- > 0;) {
+      const int first = q * qt;
+      blocks.insert(blocks.end(), hkv, row_blocks(P + std::min(first + qt, g.ntok)));
+      for (int sub = 0; sub < 4 && first + sub * 16 / G < g.ntok; ++sub) {
+        const int nb = row_blocks(P + std::min(first + std::min((sub * 16 + 15) / G + 1, qt), g.ntok));
+        jobs.push_back((d64 ? 2.35 : 3.4) + (d64 ? 1.18 : 2.75) * ((nb + 7) / 8));
+      }
+    }
+  }
+  int longest = 0, pair = 0;
+  for (size_t i = 0; i < tiles; ++i) {
+    longest = std::max(longest, blocks[i]);
+    if (i + slots < tiles) pair = std::max(pair, blocks[i] + blocks[i + slots]);
+  }
+  const double whole = (d64 ? 6.1 : 6.5) + std::max((d64 ? 0.611 : 1.138) * longest, (d64 ? 0.566 : 1.323) * pair);
+  const double keys = (d64 ? 4.5 : 3.7) + list_makespan(jobs, hkv, (int)slots);
+  return keys < 0.98 * whole ? mpa::kPrefillRowsKeys : mpa::kPrefillRows;
+}
+
 // The same for a launch of any cache type.
 int prefill_rows(const mpa_shape* sh, const std::vector<PrefillSegment>& segments, size_t c0, size_t c1,
                  const int32_t* seq_lens, const int32_t* qsl) {
-  if (sh->dtype == MPA_F32) return mpa::kPrefillRows;
+  if (sh->dtype == MPA_F32) return prefill_rows_f32(sh, segments, c0, c1, seq_lens, qsl);
   if (sh->dtype == MPA_FP8) return mpa::kPrefillRowsMfma;
   return prefill_rows_bf16(sh, segments, c0, c1, seq_lens, qsl);
 }
@@ -1204,7 +1258,8 @@ int run_attention(int phases, const mpa_shape* shape, const void* q, const void*
     mpa::PrefillPlan p;
     p.n_seqs = (int32_t)(std::min(plan.prefill.size(), c0 + mpa::kMaxPrefillSeqs) - c0);
     p.rows = plan.prefill_rows[c0 / mpa::kMaxPrefillSeqs];
-    p.q_tile = p.rows / (shape->num_q_heads / shape->num_kv_heads);
+    // 16-row workgroups are quarters of a 64-row tile
+    p.q_tile = std::max(p.rows, mpa::kPrefillRows) / (shape->num_q_heads / shape->num_kv_heads);
     const int qt = p.q_tile;
     int acc = 0, rows = 0;
     for (int k = 0; k < p.n_seqs; ++k) {

@@ -15,6 +15,7 @@ constexpr int kMaxPrefillSeqs = 64;   // prefill segments per launch (its plan c
 constexpr int kPrefillSplitTarget = 256;  // prefill workgroups a launch should at least have
 constexpr int kPrefillMinSplitTiles = 8;  // smallest KV range of a prefill split, in 64-key tiles
 constexpr int kPrefillRows = 64;      // (token, head) rows per generic prefill workgroup
+constexpr int kPrefillRowsKeys = 16;  // the same of its form with the keys dealt to the waves
 constexpr int kFewKeys = 64;          // rows that see at most this many keys get the 16-bit P pass
 constexpr int kPrefillRowsHalf = 128; // the same of the four-wave form
 constexpr int kPrefillRowsMfma = 256; // (token, head) rows per bf16 prefill workgroup (8 waves)

@@ -1049,19 +1049,6 @@ __global__ __launch_bounds__(64 * kMergeWaves) void prefill_merge_kernel(AttnArg
 // takes about 1.2 us per block of its longest row with most of the device
 // idle; an eighth of the keys a wave spreads the same products over four
 // times the workgroups and eighths of the time.
-
-// Which form a launch of this many (tile, KV head) pairs takes, measured
-// (us, KEYS false -> true; head_dim 128, tokens on prefix):
-//   64 tiles  (8/2 heads, 500 on 1,000)  112.5 ->  41.4
-//   152       (32/8, 300 on 1,000)        99.6 ->  89.8
-//   250       (8/2, 2,000 on 500)        182.5 -> 152.9
-//   256       (32/8, 500 on 1,000)       115.4 -> 128.1  (one full round of tiles)
-//   352       (32/8, 700 on 1,000)       246.2 -> 202.3
-//   504       (32/8, 1,000 on 0)         134.1 -> 133.0
-//   752       (32/8, 1,500 on 2,000)     710.7 -> 755.6  (K and V read for 16 rows, not 64)
-// A launch that just fills one round, or makes two, keeps whole tiles.
-constexpr bool prefill_by_keys(long tiles) { return tiles <= 224 || (tiles > 256 && tiles < 504); }
-
 template <int DT, int D, bool KEYS>
 __global__ __launch_bounds__(KEYS ? 64 * kKeyWaves : 256, 2) void prefill_kernel(AttnArgs a, PrefillPlan p) {
   using T = Tr<DT>;
@@ -2151,7 +2138,7 @@ struct PrefillL {
       }
       return launch_prefill_mfma<DT, D, kPrefillWaves, kPrefillStages>(a, p, n_tiles, stream);
     } else {
-      if (prefill_by_keys((long)n_tiles * a.hkv))
+      if (p.rows == kPrefillRowsKeys)
         hipLaunchKernelGGL((prefill_kernel<DT, D, true>), dim3((unsigned)n_tiles * 4 * a.hkv), dim3(64 * kKeyWaves), 0, stream, a,
                            p);
       else

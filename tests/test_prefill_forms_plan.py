@@ -1,5 +1,6 @@
 """The form the planner gives a prefill launch, on the host: half or whole
-tiles of bf16 caches, at points where the two forms' measured times are at least 4 % apart."""
+tiles of bf16 caches and whole tiles or dealt keys of f32 ones, at points
+where the two forms' measured times are at least 4 % apart."""
 
 import numpy as np
 import pytest
@@ -37,6 +38,27 @@ def rows(dtype, heads, chunks):
 def test_bf16_form(heads, chunks, expected):
     assert rows(mpa.MPA_BF16, heads, chunks) == expected
     assert rows(mpa.MPA_FP8, heads, chunks) == 256
+
+
+@pytest.mark.parametrize("heads,chunks,expected", [
+    # tiles -> keys (us): 115.9 -> 56.7, 183.5 -> 148.9 (248 tiles), 189 -> 154 (256), 137 -> 103, 601 -> 470 (504)
+    ((8, 2, 128), [(1024, 500)], 16),
+    ((8, 2, 128), [(1984, 500)], 16),
+    ((8, 2, 128), [(2048, 500)], 16),
+    ((32, 8, 128), [(528, 500)], 16),
+    ((8, 2, 128), [(4032, 500)], 16),
+    ((16, 2, 64), [(512, 500)], 16),
+    ((16, 2, 64), [(1984, 0)], 16),
+    # 670 -> 745 (200 tiles), 79.9 -> 88.2 (256); d 64: 13.5 -> 18.6 (200), 32.3 -> 47.1 (496)
+    ((8, 2, 128), [(1600, 8000)], 64),
+    ((32, 8, 128), [(512, 500)], 64),
+    ((64, 8, 64), [(200, 0)], 64),
+    ((64, 8, 64), [(496, 0)], 64),
+    # past 512 tiles
+    ((8, 2, 128), [(4800, 0)], 64),
+])
+def test_f32_form(heads, chunks, expected):
+    assert rows(mpa.MPA_F32, heads, chunks) == expected
 
 
 def test_one_form_per_launch():
