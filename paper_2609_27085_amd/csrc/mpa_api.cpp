@@ -194,6 +194,48 @@ int range_min_blocks(int dtype, int head_dim) {
   return head_dim == 128 ? 24 : 10;
 }
 
+// Whether ranges of `range` blocks pay by the rows they meet.  A wave goes over
+// the rows of its range one after another, and each costs it a start (and its
+// new token a wait), about a block's time and more at fp8 and in a step that
+// appends; the launch takes as long as its most crowded range.  Measured as
+// row splits -> ranges (us, 32 / 8 heads, step with its tokens), with the rows
+// past the first in the most crowded range over its blocks:
+//   bf16, d 128: 0.06 354 -> 314, 0.15 417 -> 399, 0.24 221 -> 244, 0.25 416
+//     -> 427 (100 rows of 64 keys behind 4 of 131,072), 0.41 805 -> 994 (248
+//     rows of 1-64 behind 8);
+//   bf16, d 64: 0.07 174 -> 161, 0.15 83.1 -> 82.8, 0.24 110 -> 125;
+//   f32: 0.1 198 -> 194, 0.2 191 -> 189, 0.24 423 -> 459;
+//   fp8, d 128: 0.05 197 -> 182, 0.25 236 -> 264, 0.41 448 -> 575;
+//   fp8, d 64: 0.08 90.3 -> 90.5 (83.8 -> 81.7 without tokens), 0.24 65 -> 83.
+// fp8 rows whose splits fill at most one round of waves are split (d 64: 128
+// rows of 1,100 35.1 -> 38.8, 256 of 2,000 98.4 -> 100.4; more rounds, 256 of
+// 100-8,000 without tokens 83.8 -> 81.7; d 128: 128 of 3,000 134 -> 141, two
+// rounds, 256 of 2,000 203 -> 201), and so are bf16 rows of 64-wide heads whose
+// ranges are the shortest and whose splits are few to merge (256 of 400 49.0
+// -> 50.4; with 16 parts a row 128 of 3,000 44.5 -> 42.6).
+bool ranges_pay(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, size_t c0, size_t c1, int range,
+                int* split) {
+  int most = 0, here = 0;
+  long at = 0, last = -1;  // the last range met, by `here` rows so far
+  for (size_t k = c0; k < c1; ++k) {
+    const int nb = row_blocks(seq_lens[b.decode[k]]);
+    here = at / range == last ? here + 1 : 1;
+    most = std::max(most, here);
+    if ((at + nb - 1) / range > at / range) here = 1;
+    last = (at + nb - 1) / range;
+    at += nb;
+  }
+  const bool fp8 = sh->dtype == MPA_FP8;
+  if ((most - 1) * (fp8 ? 8 : 5) > range) return false;
+  const bool shortest = sh->dtype == MPA_BF16 && sh->head_dim == 64 && range < 14;
+  if (!fp8 && !shortest) return true;
+  if (*split == 0) *split = choose_split(sh, b, seq_lens);
+  long items = 0;
+  for (size_t k = c0; k < c1; ++k) items += row_split(seq_lens[b.decode[k]], *split).parts;
+  if (fp8) return items * sh->num_kv_heads > mpa::decode_wave_slots(sh->dtype, sh->head_dim, false);
+  return items >= 4 * (long)(c1 - c0);
+}
+
 // The launches that take one workgroup per (row, KV head) (decode_short_kernel)
 // with no row split: at most so many pairs, of rows of at most so many keys.
 // Measured against row splits and their merge (decode half, us; 12.3 is what
@@ -219,10 +261,10 @@ struct DecodeLaunch {
 long range_parts(long at, long nb, int range) { return (at + nb - 1) / range - at / range + 1; }
 
 // The decode launches, with ranges where they pay (`ranges`) or all rows
-// split on their own.  MPA_DECODE_RANGE (blocks; 0: none) overrides the
-// choice of ranges for tuning sweeps and tests; MPA_SPLIT_TOKENS asks for row
-// splits.
-std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, int split,
+// split on their own.  `split` takes the nominal part size when it is needed
+// and 0.  MPA_DECODE_RANGE (blocks; 0: none) overrides the choice of ranges
+// for tuning sweeps and tests; MPA_SPLIT_TOKENS asks for row splits.
+std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens, int* split,
                                         bool ranges) {
   std::vector<DecodeLaunch> out;
   const int range_env = env_decode_range();
@@ -244,15 +286,17 @@ std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, con
       const long range = (blocks + per_head - 1) / per_head;
       if (forced > 0)
         d.range_blocks = forced;
-      else if (slots > 0 && range >= range_min_blocks(sh->dtype, sh->head_dim))
+      else if (slots > 0 && range >= range_min_blocks(sh->dtype, sh->head_dim) &&
+               ranges_pay(sh, b, seq_lens, d.c0, d.c1, (int)range, split))
         d.range_blocks = (int)range;
     }
+    if (d.range_blocks == 0 && *split == 0) *split = choose_split(sh, b, seq_lens);
     long at = 0;
     for (size_t k = d.c0; k < d.c1; ++k) {
       const int L = seq_lens[b.decode[k]];
       const long parts = d.range_blocks > 0   ? range_parts(at, row_blocks(L), d.range_blocks)
                          : d.range_blocks < 0 ? 1
-                                              : (long)row_split(L, split).parts;
+                                              : (long)row_split(L, *split).parts;
       at += row_blocks(L);
       d.items += parts;
       d.split |= parts > 1;
@@ -663,13 +707,7 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
     for (const auto& d : v) n += d.items;
     return n;
   };
-  p.decode = decode_layout(sh, p.batch, seq_lens, 1024, true);
-  bool all_ranges = true;
-  for (const auto& d : p.decode) all_ranges &= d.range_blocks != 0;
-  if (!all_ranges) {
-    p.split = choose_split(sh, p.batch, seq_lens);
-    p.decode = decode_layout(sh, p.batch, seq_lens, p.split, true);
-  }
+  p.decode = decode_layout(sh, p.batch, seq_lens, &p.split, true);
   p.prefill = prefill_segments(sh, p.batch, seq_lens, qsl, true);
   auto place = [&] {
     const long ditems = total(p.decode);
@@ -683,10 +721,8 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
     // mpa_append_attention_noalloc does without them where that takes less.
     p.prefill = prefill_segments(sh, p.batch, seq_lens, qsl, false);
     if (!place()) {
-      const int split = choose_split(sh, p.batch, seq_lens);
-      const std::vector<DecodeLaunch> rows = decode_layout(sh, p.batch, seq_lens, split, false);
+      const std::vector<DecodeLaunch> rows = decode_layout(sh, p.batch, seq_lens, &p.split, false);
       if (total(rows) < total(p.decode)) {
-        p.split = split;
         p.decode = rows;
         place();
       }

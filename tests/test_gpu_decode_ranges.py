@@ -9,7 +9,8 @@ import numpy as np
 import pytest
 
 import paper_2609_27085_amd as mpa
-from test_gpu_parity import check_batch, run_step, torch_gpu  # noqa: F401  (torch_gpu: the module's fixture)
+from test_gpu_parity import (as_f64, assert_close, check_batch, oracle_for, run_step,  # noqa: F401  (torch_gpu: the
+                             torch_gpu)                                                # module's fixture)
 from workloads import HeadSpec, SeqSpec, make_batch
 from workloads.device import to_device
 
@@ -52,11 +53,106 @@ def test_ranges(torch_gpu, dtype, heads, blocks, monkeypatch):  # noqa: F811
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 def test_ranges_chosen_for_batches_that_fill_the_device(torch_gpu, dtype):  # noqa: F811
     rng = np.random.default_rng(810)
-    lens = [int(n) for n in rng.integers(2000, 8000, size=24)]
+    # fp8 rows are split on their own while one round of the device's waves holds their parts
+    lens = [int(n) for n in rng.integers(2000, 8000, size=80 if dtype == "fp8" else 24)]
     b = make_batch([SeqSpec(n, 1) for n in lens], HeadSpec(16, 16, 64), dtype, rng)
     info = info_of(b)
     assert info.split_tokens % 16 == 0 and info.num_decode_items == parts(lens, info.split_tokens // 16)
     check_batch(b, f"ranges of {info.split_tokens} tokens, {info.num_decode_items} parts", fused=True)
+
+
+def plan_of(heads, lens, dtype):
+    sl = np.asarray(lens, np.int32)
+    qsl = np.arange(len(lens) + 1, dtype=np.int32)
+    sh = mpa.make_shape(len(lens), *heads, 10 ** 6, 10 ** 5, len(lens), 0.1, DTYPE[dtype], k_scale=0.01, v_scale=0.01)
+    return mpa.plan_info(sh, sl, qsl), mpa.workspace_size(sh, sl, qsl)
+
+
+def row_parts(lens, split):
+    """Parts of rows that are split on their own."""
+    per = [-(-n // -(-n // split)) for n in lens]
+    return sum(-(-n // max(16, -(-p // 16) * 16)) for n, p in zip(lens, per))
+
+
+@pytest.mark.parametrize("dtype,heads,crowded,spread", [
+    # 805 -> 994 us as ranges; 821 -> 741
+    ("bf16", (32, 8, 128), [131072] * 8 + [1 + k % 64 for k in range(248)], [65536] * 16 + [300] * 240),
+    # 185 -> 261; 174 -> 161
+    ("bf16", (32, 8, 64), [65536] * 8 + [32] * 64, [100 + 31 * k for k in range(256)]),
+    # 719 -> 953; 379 -> 342
+    ("f32", (32, 8, 128), [65536] * 8 + [32] * 64, [1100] * 256),
+    # 448 -> 575; 204 -> 182
+    ("fp8", (32, 8, 128), [131072] * 8 + [1 + k % 64 for k in range(248)], [100 + 31 * k for k in range(256)]),
+    # splits that fill one round of waves: 35.1 -> 38.8; more: 83.8 -> 81.7 (without tokens)
+    ("fp8", (32, 8, 64), [1100] * 128, [100 + 31 * k for k in range(256)]),
+], ids=lambda x: x if isinstance(x, str) else "")
+def test_rows_that_crowd_a_range_are_split(torch_gpu, dtype, heads, crowded, spread):  # noqa: F811
+    """A wave walks the rows of its range one after another: a batch whose
+    fullest range holds many rows for its blocks is split row by row."""
+    for lens in (crowded, crowded[::-1]):
+        info, _ = plan_of(heads, lens, dtype)
+        assert info.split_tokens <= 1024 and info.num_decode_items == row_parts(lens, info.split_tokens)
+    info, _ = plan_of(heads, spread, dtype)
+    assert info.num_decode_items == parts(spread, info.split_tokens // 16)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_crowded_batch(torch_gpu, dtype):  # noqa: F811
+    lens = [9000, 11000] + [1 + k % 40 for k in range(100)] + [8000]
+    b = make_batch([SeqSpec(n, 1) for n in lens], HeadSpec(16, 16, 64), dtype, np.random.default_rng(811))
+    assert info_of(b).num_decode_items == row_parts(lens, info_of(b).split_tokens)
+    check_batch(b, f"long rows before short ones {dtype}", fused=True)
+
+
+def test_ranges_give_way_to_row_splits_past_the_fixed_array(torch_gpu):  # noqa: F811
+    """Ranges cut every launch of 256 rows at 384 places, row splits cut these
+    rows rarely: past the no-allocation call's array the step takes those."""
+    heads = (128, 8, 128)
+    few, ws = plan_of(heads, [700] * 1280, "bf16")
+    assert few.num_decode_items > row_parts([700] * 1280, 1024) and ws <= mpa.MPA_SCRATCH_BYTES
+    assert few.num_decode_items == 5 * parts([700] * 256, few.split_tokens // 16)
+    lens = [700] * 1792
+    many, ws = plan_of(heads, lens, "bf16")
+    assert 7 * parts([700] * 256, few.split_tokens // 16) * 128 * 130 * 4 > mpa.MPA_SCRATCH_BYTES
+    assert many.num_decode_items == row_parts(lens, many.split_tokens) and ws <= mpa.MPA_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("route,dtype,specs", [
+    ("MPA_DECODE_RANGE=7", "bf16", [(100, 1), (260, 1), (40, 1), (900, 1)]),
+    ("MPA_DECODE_RANGE=7", "f32", [(100, 1), (260, 1), (40, 1), (900, 1)]),
+    ("MPA_DECODE_RANGE=7", "fp8", [(100, 1), (260, 1), (40, 1), (900, 1)]),
+    ("MPA_SPLIT_TOKENS=128", "fp8", [(100, 1), (260, 1), (40, 1), (900, 1)]),
+    ("", "bf16", [(100, 1), (260, 1), (40, 1), (900, 1)]),  # short rows
+    ("", "f32", [(100, 100), (260, 60), (300, 40)]),        # keys dealt to the waves
+    ("", "bf16", [(100, 100), (260, 60), (300, 40)]),       # half tiles
+], ids=lambda x: x.replace("=", "") if isinstance(x, str) else "")
+def test_bad_block_id(torch_gpu, route, dtype, specs, monkeypatch):  # noqa: F811
+    """A block id outside the pool in the device's table makes the rows that
+    read it NaN and leaves the others right, in each kernel's own walk."""
+    if route:
+        monkeypatch.setenv(*route.split("="))
+    b = make_batch([SeqSpec(*s) for s in specs], HeadSpec(8, 2, 64), dtype, np.random.default_rng(812))
+    if not route and specs[0][1] > 1:
+        sh = mpa.make_shape(b.num_seqs, 8, 2, 64, b.num_blocks, b.block_tables.shape[1], b.total_q, b.scale,
+                            DTYPE[dtype])
+        assert mpa.prefill_rows(sh, b.seq_lens, b.query_start_loc) == {"f32": 16, "bf16": 128}[dtype]
+    o_ref, _ = oracle_for(b)
+    d = to_device(b)
+    mpa.kv_append(d.k_new, d.v_new, d.k_cache, d.v_cache, d.block_tables, d.seq_lens, d.query_start_loc,
+                  d.seq_lens_host, d.qsl_host, k_scale=d.k_scale, v_scale=d.v_scale)
+    bt = d.block_tables.clone()
+    bt[1, 3] = b.num_blocks + 1000  # sequence 1, keys 48-63: read by all its rows
+    out = torch_gpu.zeros_like(d.q)
+    ws = mpa.alloc_workspace(d.q, d.k_cache, d.block_tables, d.seq_lens_host, d.qsl_host, d.scale)
+    print(f"[gpu] bad block id {route} {dtype}", flush=True)
+    mpa.mixed_paged_attention(d.q, d.k_cache, d.v_cache, bt, d.seq_lens, d.query_start_loc, d.seq_lens_host,
+                              d.qsl_host, out, workspace=ws, scale=d.scale, k_scale=d.k_scale, v_scale=d.v_scale)
+    torch_gpu.cuda.synchronize()
+    got = as_f64(out)
+    t0, t1 = int(b.query_start_loc[1]), int(b.query_start_loc[2])
+    assert np.isnan(got[t0:t1]).all()
+    others = np.r_[0:t0, t1:b.total_q]
+    assert_close(got[others], o_ref[others], dtype, "rows that do not read the bad block")
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32", "fp8"])
