@@ -4,6 +4,7 @@ sequences, and that a step which fits the fixed array of
 mpa_append_attention_noalloc with whole chunks still fits it."""
 
 import itertools
+import time
 
 import numpy as np
 import pytest
@@ -62,3 +63,18 @@ def test_balance_stays_within_the_fixed_array():
         assert (ws > 0) == (info.prefill_max_splits > 1) and ws <= mpa.MPA_SCRATCH_BYTES
         sizes.append(ws)
     assert sum(n > 0 for n in sizes) > 30 and max(sizes) > mpa.MPA_SCRATCH_BYTES // 2
+
+
+def test_launches_too_long_to_end_unevenly_are_not_simulated():
+    # 60 chunks of 8,192 tokens on 8,192, 10 KV heads: the longest of 98,400
+    # units is 0.5 % of a CU's share.  Dealing them all out took the planner
+    # 3.9 ms; the pass over the units takes 0.1 ms
+    chunks = [(8192, 8192)] * 60
+    plan((40, 10, 128), chunks)
+    best = 1.0
+    for k in range(10):
+        t = time.perf_counter()
+        info, ws = plan((40, 10, 128), [(8192 - k, 8192)] + chunks[1:])
+        best = min(best, time.perf_counter() - t)
+        assert info.prefill_max_splits == 1 and ws == 0
+    assert best < 1.5e-3, best
