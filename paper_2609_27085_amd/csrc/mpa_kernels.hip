@@ -424,7 +424,9 @@ __device__ inline void consume_block(const AttnArgs& a, const typename Tr<DT>::C
 // per coalesced load, one per lane, broadcast with readlane.  The next 64
 // are loaded when a group is begun, so that the loads of the blocks never
 // wait for their ids.  Blocks are asked for in order (a block at or past
-// kb_end, asked for by a prefetch, is the last one).
+// kb_end, asked for by a prefetch, is the last one).  REFILL false: a run of at
+// most 64 blocks (a part of a row that is split on its own).
+template <bool REFILL>
 struct BlockIds {
   const int32_t* bt;
   int base, last, nb;
@@ -433,7 +435,7 @@ struct BlockIds {
   __device__ inline BlockIds(const int32_t* table, int kb_begin, int kb_end, int num_blocks)
       : bt(table), base(kb_begin), last(kb_end - 1), nb(num_blocks), poison(false) {
     cur = fetch(base);
-    nxt = fetch(base + 64);
+    if constexpr (REFILL) nxt = fetch(base + 64);
   }
   __device__ inline int fetch(int kb) const {
     const int k = kb + (int)(threadIdx.x & 63);
@@ -441,10 +443,12 @@ struct BlockIds {
   }
   __device__ inline int operator()(int kb) {
     kb = min(kb, last);
-    if (kb - base >= 64) {
-      base += 64;
-      cur = nxt;
-      nxt = fetch(base + 64);
+    if constexpr (REFILL) {
+      if (kb - base >= 64) {
+        base += 64;
+        cur = nxt;
+        nxt = fetch(base + 64);
+      }
     }
     int blk = __builtin_amdgcn_readlane(cur, kb - base);
     if (blk < 0 || blk >= nb) {
@@ -487,7 +491,7 @@ __device__ inline void attend_blocks(const AttnArgs& a, const typename Tr<DT>::C
   const int whole = min_limit < kend ? min_limit + 1 : kend;  // keys that every row sees
   const int kb_edge = few_keys ? kb_begin : max(kb_begin, min(kb_end, whole / kBlock));
   if (kb_begin >= kb_end) return;
-  BlockIds id(bt, kb_begin, kb_end, a.nb);
+  BlockIds<true> id(bt, kb_begin, kb_end, a.nb);
   BlockFrags<DT, D> fa, fb;
   load_block<DT, D>(a, id(kb_begin), g, fa);
   int kb = kb_begin;
@@ -529,8 +533,11 @@ __device__ inline void attend_blocks(const AttnArgs& a, const typename Tr<DT>::C
 // bytes, its V read 256).  `ring` is the wave's 3 * 2 * 16 * D bytes of LDS.
 // The copies are counted in vmcnt only (the compiler does not see them), so
 // the waits are explicit; the only other vector-memory operation of the loop
-// is a load of 64 block ids every 64 blocks, which makes the waits stricter.
-template <int D>
+// is a load of 64 block ids every 64 blocks, which makes the waits stricter.  A
+// part of a row that is split on its own has at most 64 blocks (1,024 keys), so
+// it loads its ids once and its copies test for no refill (16 rows of 4,096
+// keys, 8 heads of 128: 31.3 -> 30.5 us; 100 of 1,500 66.6 -> 64.9).
+template <int D, bool STREAM>
 __device__ inline void attend_blocks_fp8_lds(const AttnArgs& a, const bf16x8* qf, const int32_t* bt, int g,
                                              int kb_begin, int kb_end, int kend, int limit, int min_limit,
                                              RowState<2, D>& st, bool& poison, uint8_t* ring) {
@@ -547,7 +554,7 @@ __device__ inline void attend_blocks_fp8_lds(const AttnArgs& a, const bf16x8* qf
   const int whole = min_limit < kend ? min_limit + 1 : kend;
   const int kb_edge = few_keys ? kb_begin : max(kb_begin, min(kb_end, whole / kBlock));
   if (kb_begin >= kb_end) return;
-  BlockIds id(bt, kb_begin, kb_end, a.nb);
+  BlockIds<STREAM> id(bt, kb_begin, kb_end, a.nb);
   auto copy = [&](int kb, int slot) {
     const size_t gran = ((size_t)id(kb) * a.hkv + g) * GB;
     const uint8_t* kp = reinterpret_cast<const uint8_t*>(a.k_cache) + gran;
@@ -707,8 +714,10 @@ __device__ inline void merge_waves(const RowState<DT, D>& st, float l, bool pois
 // GB (256 rows) 1,375 -> 1,205 us, 10.8 GB (32 rows) 1,767 -> 1,554 us (6.97
 // TB/s; a contiguous read of 2 GiB takes 7.08), fp8 1.46 GB 265 -> 237 us,
 // 64-wide heads 1.6 GB 271 -> 247 us.
-// Decode waves a SIMD holds at the kernels' register use.
-constexpr int decode_waves_per_simd(int dt, int d) { return d == 128 ? (dt == 1 ? 2 : 3) : 4; }
+// Decode waves a SIMD holds at the kernels' register use (fp8 at 64-wide heads
+// is held to 80 registers for six, which its LDS allows: at 82 and five, 256
+// rows of 2,000 keys in row splits took 100.9 us, now 93.6).
+constexpr int decode_waves_per_simd(int dt, int d) { return d == 128 ? (dt == 1 ? 2 : 3) : dt == 2 ? 6 : 4; }
 
 template <int DT, int D, int WPG, bool STREAM>
 __global__ __launch_bounds__(64 * WPG, decode_waves_per_simd(DT, D)) void decode_kernel(AttnArgs a, DecodePlan p) {
@@ -787,8 +796,8 @@ __global__ __launch_bounds__(64 * WPG, decode_waves_per_simd(DT, D)) void decode
     bool poison = false;
     if constexpr (DT == 2) {
       __shared__ __attribute__((aligned(16))) uint8_t ring[WPG][3 * 2 * kBlock * D];
-      attend_blocks_fp8_lds<D>(a, qf, a.block_tables + (size_t)s * a.mb, g, k0 / kBlock, (k1 + kBlock - 1) / kBlock,
-                               k1, INT32_MAX, INT32_MAX, st, poison, ring[wave]);
+      attend_blocks_fp8_lds<D, STREAM>(a, qf, a.block_tables + (size_t)s * a.mb, g, k0 / kBlock,
+                                       (k1 + kBlock - 1) / kBlock, k1, INT32_MAX, INT32_MAX, st, poison, ring[wave]);
     } else {
       attend_blocks<DT, D, STREAM>(a, qf, a.block_tables + (size_t)s * a.mb, g, k0 / kBlock,
                                    (k1 + kBlock - 1) / kBlock, k1, INT32_MAX, INT32_MAX, st, poison, step);
