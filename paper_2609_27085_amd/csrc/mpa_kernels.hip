@@ -890,7 +890,8 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void decode_short_kernel(AttnArg
 // 16 bytes, so the wave reads 256 / D rows per instruction, kMergeUnroll of
 // them in flight; each lane adds its 4 elements of every (256 / D)-th split,
 // and the lanes' sums are combined at the end.  Only the n real splits are
-// read.  ml points at split 0's (m, l) pair (8-byte aligned), acc at split
+// read, by as many loads as they need (four loads of two splits' rows took a
+// prompt of 1,000 tokens, 32 heads, from 75.5 us to 78.6).  ml points at split 0's (m, l) pair (8-byte aligned), acc at split
 // 0's row (16-byte aligned); consecutive splits are ml_stride and acc_stride
 // floats apart.
 __device__ inline float wave_max64(float x) {
@@ -938,11 +939,13 @@ __device__ inline MergeState merge_range(const float* ml, size_t ml_stride, cons
       f32x4 v[kMergeUnroll];
 #pragma unroll
       for (int u = 0; u < kMergeUnroll; ++u) {
+        if (k + u * RPI >= cnt) break;
         const int i = min(k + u * RPI + sub, cnt - 1);
         v[u] = *reinterpret_cast<const f32x4*>(acc + (size_t)(c0 + i) * acc_stride);
       }
 #pragma unroll
       for (int u = 0; u < kMergeUnroll; ++u) {
+        if (k + u * RPI >= cnt) break;
         const int i = k + u * RPI + sub;
         const float w = __shfl(wk, min(i, cnt - 1));
         if (i < cnt) r.o += v[u] * w;
