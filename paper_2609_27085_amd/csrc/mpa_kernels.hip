@@ -109,16 +109,28 @@ __device__ inline V ld_stream(const void* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
 }
 
-// New tokens are written with non-temporal stores beside a decode step: a
-// token's K is D / 8 pieces of 16 bytes and its transposed V D single
-// elements 16 apart, so every line they touch is written in part, and such
-// lines left dirty in the L2 slow the streaming reads that evict them.
-// Decode with its tokens, 128 rows of 8 heads: 424 us with plain stores, 403
-// with these, 392 with none; 256 rows 1,242 / 1,205 / 1,190; fp8 264 / 253 /
-// 247.
+// New tokens are written with non-temporal stores beside a decode step whose
+// rows stream as ranges: a token's K is D / 8 pieces of 16 bytes and its
+// transposed V D single elements 16 apart, so every line they touch is written
+// in part, and such lines left dirty in the L2 slow the streaming reads that
+// evict them.  Decode with its tokens, 128 rows of 8 heads: 424 us with plain
+// stores, 403 with these, 392 with none; 256 rows 1,242 / 1,205 / 1,190; fp8
+// 264 / 253 / 247.  Rows that are split on their own or not at all take plain
+// stores: there a wave waits for its token before its first block, a larger
+// part of its time, and a plain store is complete in the L2 (32 / 8 heads,
+// non-temporal -> plain: 32 rows of 900 23.0 -> 21.0 us, 256 of 600 137.1 ->
+// 132.9, fp8 79.2 -> 75.0, 16 of 4,096 31.8 -> 31.0; 128 of 1,500, two rounds
+// of waves, 142.1 -> 144.8).
 template <typename V>
 __device__ inline void st_stream(void* p, V v) {
   __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+}
+template <bool NT, typename V>
+__device__ inline void st_token(void* p, V v) {
+  if constexpr (NT)
+    st_stream(p, v);
+  else
+    *reinterpret_cast<V*>(p) = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -607,7 +619,7 @@ __device__ inline void store_fp8_chunk(const AppendArgs& a, size_t head, int c, 
 // as 16 bytes a lane, V as each lane's D / 64 dims of the slot.  The wave
 // waits for its stores before it loads any block.  A bad block id writes
 // nothing (the row comes out NaN).
-template <int DT, int D>
+template <int DT, int D, bool NT>
 __device__ inline void append_decode_token(const AttnArgs& a, int s, int pos, int t, int g, int lane) {
   constexpr int RT = DT == 2 ? 0 : DT;  // new rows: bf16 beside an fp8 cache
   using NE = typename Tr<RT>::Elem;
@@ -634,18 +646,18 @@ __device__ inline void append_decode_token(const AttnArgs& a, int s, int pos, in
       u32x2 kc = {0u, 0u};
 #pragma unroll
       for (int e = 0; e < 8; ++e) kc[e / 4] |= f32_to_e4m3(kx[e] * a.inv_k_scale) << (8 * (e % 4));
-      st_stream(dst, kc);
+      st_token<NT>(dst, kc);
     } else {
-      st_stream(dst, kw);
+      st_token<NT>(dst, kw);
     }
   }
   CE* vc = reinterpret_cast<CE*>(const_cast<void*>(a.v_cache)) + (head * D + DPL * lane) * kBlock + slot;
 #pragma unroll
   for (int i = 0; i < DPL; ++i) {
     if constexpr (DT == 2)
-      st_stream(vc + i * kBlock, (uint8_t)f32_to_e4m3(__uint_as_float((unsigned)v[i] << 16) * a.inv_v_scale));
+      st_token<NT>(vc + i * kBlock, (uint8_t)f32_to_e4m3(__uint_as_float((unsigned)v[i] << 16) * a.inv_v_scale));
     else
-      st_stream(vc + i * kBlock, v[i]);
+      st_token<NT>(vc + i * kBlock, v[i]);
   }
 }
 
@@ -749,12 +761,12 @@ __global__ __launch_bounds__(64 * WPG, decode_waves_per_simd(DT, D)) void decode
     if constexpr (STREAM) {
       for (int k = j; k < p.n_seqs && p.part[k + 1] <= blk_end; ++k) {
         const int s = p.seq[k];
-        append_decode_token<DT, D>(a, s, a.seq_lens[s] - 1, a.qsl[s], g, lane);
+        append_decode_token<DT, D, STREAM>(a, s, a.seq_lens[s] - 1, a.qsl[s], g, lane);
         stored = true;
       }
     } else if (item == p.item_start[j + 1] - 1) {
       const int s = p.seq[j];
-      append_decode_token<DT, D>(a, s, a.seq_lens[s] - 1, a.qsl[s], g, lane);
+      append_decode_token<DT, D, STREAM>(a, s, a.seq_lens[s] - 1, a.qsl[s], g, lane);
       stored = true;
     }
     if (stored) MPA_WAIT_VMCNT(0);  // stores are counted in vmcnt
@@ -857,7 +869,7 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void decode_short_kernel(AttnArg
   const int per = (nb + kKeyWaves - 1) / kKeyWaves;
   const int kb0 = min(wave * per, nb), kb1 = min(nb, kb0 + per);
   if (a.k_new != nullptr && kb0 < kb1 && kb1 == nb) {
-    append_decode_token<DT, D>(a, s, L - 1, trow, g, lane);
+    append_decode_token<DT, D, false>(a, s, L - 1, trow, g, lane);
     MPA_WAIT_VMCNT(0);  // stores are counted in vmcnt
   }
   const QE* q = reinterpret_cast<const QE*>(a.q) + ((size_t)trow * a.hq + h) * D;
