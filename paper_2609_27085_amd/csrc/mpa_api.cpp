@@ -810,6 +810,24 @@ int check_append_slots(const mpa_shape* sh, const int32_t* seq_lens, const int32
   return MPA_OK;
 }
 
+// Whether single tokens are written with non-temporal stores.  What they leave
+// in part-written lines slows the decode that follows when it streams more
+// than the caches hold; below that a plain store is complete sooner.  Append
+// and decode, us, plain -> non-temporal: bf16 none slower (256 rows of 300, 2
+// heads of 128, 78 MB 30.5 -> 30.5; 256 of 600, 8 heads 133.7 -> 130.0); f32
+// 26 MB 25.1 -> 26.0, 59 MB 27.9 -> 29.6, 134 MB 32.1 -> 32.7, 315 MB 69.8 ->
+// 66.7; fp8 26 MB 27.8 -> 29.6, 92 MB 28.0 -> 29.2, 184 MB (100 rows of 900 in
+// the mean) 47.9 -> 46.3, 393 MB (128 of 1,500) 79.9 -> 78.3, but 157 and 315
+// MB as 256 rows of 300 and 600 38.8 -> 42.3 and 80.4 -> 84.8: a store there
+// is a single code, 2,048 of them for a row's token.
+bool token_stores_stream(const mpa_shape* sh, const Batch& b, const int32_t* seq_lens) {
+  if (sh->dtype == MPA_BF16) return true;
+  double keys = 0.0;
+  for (int s : b.decode) keys += seq_lens[s];
+  if (sh->dtype == MPA_FP8 && keys < 800.0 * b.decode.size()) return false;
+  return keys * sh->num_kv_heads * sh->head_dim * 2 * (sh->dtype == MPA_F32 ? 4 : 1) >= 160e6;
+}
+
 // The append launches (plain, or with the rotary embedding when rope is
 // given).
 int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
@@ -836,9 +854,8 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
   a.nb = shape->num_blocks;
   a.inv_k_scale = shape->dtype == MPA_FP8 ? 1.f / shape->k_scale : 1.f;
   a.inv_v_scale = shape->dtype == MPA_FP8 ? 1.f / shape->v_scale : 1.f;
-  (void)seq_lens;
-  (void)query_start_loc;
   const Batch b = classify(shape, query_start_loc_host);
+  a.nt = token_stores_stream(shape, b, seq_lens_host);
   clear_stale_hip_error();
   // multi-token sequences one wave per (cache block, KV head); with the rotary
   // embedding (appended by no attention call) the single tokens beside them

@@ -98,6 +98,7 @@ struct AppendArgs {
   const int32_t* block_tables;
   int32_t hkv, mb, nb;
   float inv_k_scale, inv_v_scale;  // fp8 caches: 1 / scale, rounded to f32 (1 otherwise)
+  bool nt;  // single tokens are written with non-temporal stores (bf16: always)
 };
 
 // The rotary embedding applied by the rope append: query rows (in place,

@@ -609,9 +609,6 @@ __device__ inline void attend_blocks_fp8_lds(const AttnArgs& a, const bf16x8* qf
   poison |= id.poison;
 }
 
-template <int D>
-__device__ inline void store_fp8_chunk(const AppendArgs& a, size_t head, int c, int slot, u32x4 kw, u32x4 vw);
-
 // A decode row's new token (query row t, position pos) for KV head g,
 // written by the wave that reads the row's last part -- parts' edges are
 // block-aligned, so no other wave reads this (block, head) granule -- with
@@ -1689,7 +1686,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : D == 64 ? 3 : 2) void 
 // Stores chunk c (8 consecutive bf16 elements, packed) of a new key row and
 // of a new value row into slot `slot` of cache head `head` of an fp8 cache:
 // each element x becomes the E4M3 code of x * (1 / scale).
-template <int D>
+template <int D, bool NT>
 __device__ inline void store_fp8_chunk(const AppendArgs& a, size_t head, int c, int slot, u32x4 kw, u32x4 vw) {
   constexpr int NC = D / 8;
   float kx[8], vx[8];
@@ -1698,10 +1695,10 @@ __device__ inline void store_fp8_chunk(const AppendArgs& a, size_t head, int c, 
   u32x2 kc = {0u, 0u};
 #pragma unroll
   for (int e = 0; e < 8; ++e) kc[e / 4] |= f32_to_e4m3(kx[e] * a.inv_k_scale) << (8 * (e % 4));
-  st_stream(reinterpret_cast<uint8_t*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * 8, kc);
+  st_token<NT>(reinterpret_cast<uint8_t*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * 8, kc);
   uint8_t* vc = reinterpret_cast<uint8_t*>(a.v_cache) + (head * D + c * 8) * kBlock + slot;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) st_stream(vc + e * kBlock, (uint8_t)f32_to_e4m3(vx[e] * a.inv_v_scale));
+  for (int e = 0; e < 8; ++e) st_token<NT>(vc + e * kBlock, (uint8_t)f32_to_e4m3(vx[e] * a.inv_v_scale));
 }
 
 // ---------------------------------------------------------------------------
@@ -1710,7 +1707,7 @@ __device__ inline void store_fp8_chunk(const AppendArgs& a, size_t head, int c, 
 // scalar load; the wave then copies the token's Hkv*d key elements as 16-byte
 // chunks and its value elements into the V^T rows of the slot, issuing the
 // loads of up to 4 chunks per lane before their stores.
-template <int DT, int D>
+template <int DT, int D, bool NT>
 __global__ __launch_bounds__(256) void append_kernel(AppendArgs a, AppendPlan p) {
   using T = Tr<DT>;
   using E = typename T::Elem;
@@ -1734,7 +1731,7 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a, AppendPlan p)
     const uint16_t* vn = reinterpret_cast<const uint16_t*>(a.v_new) + (size_t)t * a.hkv * D;
     for (int ci = lane; ci < nchunk; ci += 64) {
       const int h = ci / NC, c = ci - h * NC;
-      store_fp8_chunk<D>(a, (size_t)blk * a.hkv + h, c, slot, *reinterpret_cast<const u32x4*>(kn + h * D + c * 8),
+      store_fp8_chunk<D, NT>(a, (size_t)blk * a.hkv + h, c, slot, *reinterpret_cast<const u32x4*>(kn + h * D + c * 8),
                          *reinterpret_cast<const u32x4*>(vn + h * D + c * 8));
     }
   } else {
@@ -1756,10 +1753,10 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a, AppendPlan p)
       if (ci >= nchunk) continue;
       const int h = ci / NC, c = ci - h * NC;
       const size_t head = (size_t)blk * a.hkv + h;
-      st_stream(reinterpret_cast<E*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * X, kv[u]);
+      st_token<NT>(reinterpret_cast<E*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * X, kv[u]);
       E* vc = reinterpret_cast<E*>(a.v_cache) + (head * D + c * X) * kBlock + slot;
 #pragma unroll
-      for (int e = 0; e < X; ++e) st_stream(vc + e * kBlock, vv[u][e]);
+      for (int e = 0; e < X; ++e) st_token<NT>(vc + e * kBlock, vv[u][e]);
     }
   }
   }
@@ -1972,7 +1969,7 @@ __global__ __launch_bounds__(256) void append_block_kernel(AppendArgs a, AppendB
 // its rotated key row into the cache and copies its value row, as the plain
 // append does.  A head's chunks all fall in one pass of the 64 lanes (D / X
 // divides 64), so a pass loads every partner chunk before it stores any.
-template <int DT, int D>
+template <int DT, int D, bool NT>
 __global__ __launch_bounds__(256) void rope_append_kernel(AppendArgs a, AppendPlan p, RopeArgs r) {
   constexpr int RT = DT == 2 ? 0 : DT;  // queries and new rows: bf16 beside an fp8 cache
   using T = Tr<RT>;
@@ -2000,18 +1997,18 @@ __global__ __launch_bounds__(256) void rope_append_kernel(AppendArgs a, AppendPl
     const size_t head = (size_t)blk * a.hkv + h;
     if constexpr (DT == 2) {
       // fp8 cache: the rotated key, rounded to bf16, is quantized like a plain new key
-      store_fp8_chunk<D>(a, head, c, slot, rope_chunk<RT>(kn + h * D, c, r.half, cs),
+      store_fp8_chunk<D, NT>(a, head, c, slot, rope_chunk<RT>(kn + h * D, c, r.half, cs),
                          *reinterpret_cast<const u32x4*>(vn + h * D + c * X));
       continue;
     }
-    st_stream(reinterpret_cast<E*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * X,
+    st_token<NT>(reinterpret_cast<E*>(a.k_cache) + ((head * NC + c) * kBlock + slot) * X,
               rope_chunk<RT>(kn + h * D, c, r.half, cs));
     E vv[X];
 #pragma unroll
     for (int e = 0; e < X; ++e) vv[e] = vn[h * D + c * X + e];
     E* vc = reinterpret_cast<E*>(a.v_cache) + (head * D + c * X) * kBlock + slot;
 #pragma unroll
-    for (int e = 0; e < X; ++e) st_stream(vc + e * kBlock, vv[e]);
+    for (int e = 0; e < X; ++e) st_token<NT>(vc + e * kBlock, vv[e]);
   }
 }
 
@@ -2031,8 +2028,11 @@ struct AppendL {
   static hipError_t run(const AppendArgs& a, const AppendPlan& p, hipStream_t stream) {
     const int tokens = p.n_seqs;
     if (tokens == 0) return hipSuccess;
-    hipLaunchKernelGGL((append_kernel<DT, D>), dim3((tokens + kWavesPerGroup - 1) / kWavesPerGroup),
-                       dim3(64 * kWavesPerGroup), 0, stream, a, p);
+    const dim3 grid((tokens + kWavesPerGroup - 1) / kWavesPerGroup), block(64 * kWavesPerGroup);
+    if (DT == 0 || a.nt)
+      hipLaunchKernelGGL((append_kernel<DT, D, true>), grid, block, 0, stream, a, p);
+    else
+      hipLaunchKernelGGL((append_kernel<DT, D, DT == 0>), grid, block, 0, stream, a, p);
     return hipGetLastError();
   }
 };
@@ -2056,8 +2056,11 @@ struct RopeAppendL {
   static hipError_t run(const AppendArgs& a, const AppendPlan& p, const RopeArgs& r, hipStream_t stream) {
     const int tokens = p.n_seqs;
     if (tokens == 0) return hipSuccess;
-    hipLaunchKernelGGL((rope_append_kernel<DT, D>), dim3((tokens + kWavesPerGroup - 1) / kWavesPerGroup),
-                       dim3(64 * kWavesPerGroup), 0, stream, a, p, r);
+    const dim3 grid((tokens + kWavesPerGroup - 1) / kWavesPerGroup), block(64 * kWavesPerGroup);
+    if (DT == 0 || a.nt)
+      hipLaunchKernelGGL((rope_append_kernel<DT, D, true>), grid, block, 0, stream, a, p, r);
+    else
+      hipLaunchKernelGGL((rope_append_kernel<DT, D, DT == 0>), grid, block, 0, stream, a, p, r);
     return hipGetLastError();
   }
 };
