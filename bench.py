@@ -474,9 +474,8 @@ def main(argv=None) -> int:
                          d.seq_lens_host, d.qsl_host)
     if dom == "decode":
         achieved, peak, unit, bound = dec_gbs, HBM_PEAK_GBS, "GB/s", "hbm"
-        split_rows = any(-(-int(L) // info.split_tokens) > 1
-                         for L, c in zip(d.seq_lens_host, np.diff(d.qsl_host)) if c == 1)
-        kernel = "decode_kernel+merge_kernel" if split_rows else "decode_kernel"
+        split_rows = info.num_decode_items > info.num_decode_seqs
+        kernel = "decode_kernel+merge_kernel" if split_rows else "decode_kernel or decode_short_kernel"
     else:
         achieved, peak, unit, bound = pre_tflops, MFMA_BF16_PEAK_TFLOPS, "TFLOP/s", "mfma"
         kernel = "prefill_mfma_kernel"

@@ -329,7 +329,9 @@ typedef struct {
                                 blocks (the last part ends at L).  On a device that the batch's
                                 rows fill for long, the rows laid end to end, block by block, are
                                 cut into ranges of split_tokens instead, and a row's parts are
-                                its intersections with them */
+                                its intersections with them.  Few short rows are not split (a
+                                batch of no others reports a size that none passes).  Of a
+                                batch of several launches, the first launch's */
   int32_t num_decode_items;  /* (sequence, split) work items */
   int32_t num_prefill_tiles; /* (sequence, query tile, KV split, KV head) work items, in tiles of 256
                                 (token, head) rows (f32 caches: 64) whatever the launch's form

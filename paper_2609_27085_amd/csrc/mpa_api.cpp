@@ -737,7 +737,7 @@ StepPlan make_plan(const mpa_shape* sh, const int32_t* seq_lens, const int32_t* 
   }
   if (p.split == 0 && !p.decode.empty() && p.decode[0].range_blocks > 0)
     p.split = (int)std::min((long)INT32_MAX, (long)p.decode[0].range_blocks * kBlock);
-  if (p.split == 0) p.split = 1024;
+  if (p.split == 0) p.split = std::max(1024, short_row(sh->dtype, sh->head_dim));  // no row is split
   for (const auto& d : p.decode) p.decode_split |= d.split;
   for (const auto& c : p.prefill) p.prefill_split |= c.nsplit > 1;
   for (size_t c0 = 0; c0 < p.prefill.size(); c0 += mpa::kMaxPrefillSeqs)

@@ -404,3 +404,11 @@ def test_tuning_overrides_out_of_range_are_ignored(monkeypatch):
     for v, n in ((1 << 26, 2), (blocks, 2), (blocks - 1, 3)):
         monkeypatch.setenv("MPA_DECODE_RANGE", str(v))
         assert plan() == fresh() and plan()[:2] == (16 * v, n), (v, plan())
+
+
+@pytest.mark.parametrize("dtype,head_dim,longest", [(mpa.MPA_BF16, 64, 2048), (mpa.MPA_BF16, 128, 1024),
+                                                    (mpa.MPA_F32, 64, 1024), (mpa.MPA_F32, 128, 512)])
+def test_short_rows_report_a_split_size_none_passes(dtype, head_dim, longest):
+    sh = shape(head_dim=head_dim, dtype=dtype, max_blocks_per_seq=1024, total_q_tokens=2)
+    info = mpa.plan_info(sh, [longest, 3], [0, 1, 2])
+    assert info.num_decode_items == 2 and info.split_tokens >= longest
