@@ -9,7 +9,10 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
+#include <functional>
 #include <mutex>
+#include <queue>
 #include <unordered_set>
 #include <vector>
 
@@ -561,6 +564,48 @@ std::vector<PrefillSegment> prefill_segments(const mpa_shape* sh, const Batch& b
   return best;
 }
 
+// The makespan of jobs dealt in order, each `copies` times over, to CUs that
+// hold up to `per` of them at once: first one to every CU, then a second, then
+// to whichever has room.  A job on a CU that holds k runs at rate[k - 1].
+double shared_makespan(const std::vector<double>& jobs, int copies, int per, std::array<double, 3> rate) {
+  size_t cus = mpa::kPrefillSplitTarget;
+  if (cus % (size_t)copies == 0) {  // that many times the same schedule
+    cus /= copies;
+    copies = 1;
+  }
+  struct Cu {
+    double left[3], at;  // of its jobs, at that time
+    int n;
+  };
+  std::vector<Cu> cu(cus, Cu{{0.0, 0.0, 0.0}, 0.0, 0});
+  const size_t total = jobs.size() * (size_t)copies;
+  size_t next = 0;
+  for (int r = 0; r < per; ++r)
+    for (size_t c = 0; c < cus && next < total; ++c) cu[c].left[cu[c].n++] = jobs[next++ / copies];
+  using Event = std::pair<double, int>;  // when a CU's shortest job ends
+  std::priority_queue<Event, std::vector<Event>, std::greater<Event>> events;
+  auto push = [&](int c) {
+    const Cu& u = cu[c];
+    if (u.n > 0) events.push({u.at + *std::min_element(u.left, u.left + u.n) / rate[u.n - 1], c});
+  };
+  for (size_t c = 0; c < cus; ++c) push((int)c);
+  double end = 0.0;
+  while (!events.empty()) {
+    const Event e = events.top();
+    events.pop();
+    Cu& u = cu[e.second];
+    const double done = *std::min_element(u.left, u.left + u.n);
+    int n = 0;
+    for (int k = 0; k < u.n; ++k)
+      if (u.left[k] > done) u.left[n++] = u.left[k] - done;
+    u.n = n;
+    u.at = end = e.first;
+    while (u.n < per && next < total) u.left[u.n++] = jobs[next++ / copies];
+    push(e.second);
+  }
+  return end;
+}
+
 // (token, head) rows per workgroup of the bf16 launch of segments [c0, c1).
 // The planner counts workgroups of 256 rows (eight waves, one to a CU).
 // Launches of few of them may run as workgroups of 128 (four waves, two to a
@@ -568,19 +613,18 @@ std::vector<PrefillSegment> prefill_segments(const mpa_shape* sh, const Batch& b
 // the chunk's length, and half tiles let a long and a short one share a CU and
 // fill each other's gaps.  They read K and V twice as often for it, which
 // costs up to a tenth where the tiles are alike (a long prefix), so a launch
-// takes the form with the shorter predicted time: its longest queue of
-// workgroups dealt in launch order to the CUs (half tiles as if one after
-// another), its work per CU (a tile takes longer the more CUs are busy) and,
-// for half tiles, its longest one (which runs beside others to its end).  The
-// figures are fitted to 226 launches of whole chunks (rms 3-6 %).  On those
-// and 173 KV-split ones, half tiles by this rule were at most 3.7 % slower
-// than whole tiles and 6 % faster in the mean.  Measured (us, 256 -> 128 rows):
+// takes the form with the shorter predicted time: whole tiles from the makespan
+// of the launch order, half tiles from that of CUs which share their rate among
+// the workgroups they hold, both with the work per CU (a tile takes longer the
+// more CUs are busy).  The figures are fitted to 399 launches, those close to
+// the line by what the wrong form costs.  On 230 others of the same ranges the
+// form taken is 0.2 % slower than the better one in the mean, and past 13 us
+// never slower than whole tiles.  Measured (us, 256 -> 128 rows):
 //   d 128: 1,003 tokens of 32 / 8 heads on 500 41.4 -> 33.4, on 2,000 61.0 ->
 //     64.2; 2,027 on 0 53.5 -> 49.4, on 8,000 261 -> 272, on 32,000 883 -> 942;
-//     2,987 on 0 80.8 -> 78.6, on 2,000 165.9 -> 176.6; 3,499 on 0 97.6 -> 105.8;
+//     3,001 on 0 82.7 -> 79.4, 3,201 87.7 -> 92.2; 2,987 on 2,000 165.9 -> 176.6;
 //   d 64: 2,038 of 16 / 2 on 0 38.9 -> 29.5, on 32,000 (KV-split) 301 -> 317;
-//     2,539 of 32 / 8 on 2,000 95.8 -> 85.2, on 32,000 755 -> 728; 3,499 on
-//     2,000 126.5 -> 130.6.
+//     2,539 of 32 / 8 on 2,000 95.8 -> 85.2, on 32,000 755 -> 728.
 // The model is not asked where it was not fitted: KV-split launches of
 // 128-wide heads stay whole, those of 64-wide heads from 1,024 workgroups on
 // are half tiles (0.93-0.97 of the time in 12 launches), and other launches
@@ -598,26 +642,31 @@ int prefill_rows_bf16(const mpa_shape* sh, const std::vector<PrefillSegment>& se
   }
   if (d64 && groups >= 1024) return mpa::kPrefillRowsHalf;
   if (groups >= (d64 || c1 - c0 == 1 ? 448 : 128) || (split && !d64)) return mpa::kPrefillRowsMfma;
-  // a form's time: fixed + per_slot * (tiles of the longest queue, each unit
-  // `start` more) + per_cu * (tiles per CU) + longest * (tiles of the longest unit)
-  auto predict = [&](int rows, double fixed_us, double start, double per_slot, double per_cu, double longest) {
-    std::vector<double> jobs;
-    double tiles = 0.0, most = 0.0;
+  std::vector<double> jobs;  // the workgroups' 64-key tiles and a start, in launch order
+  double per_cu = 0.0, longest = 0.0;
+  auto make_jobs = [&](int rows, double start) {
+    jobs.clear();
+    per_cu = longest = 0.0;
     for (size_t k = c0; k < c1; ++k)
-      segment_units(segments[k], seq_lens, qsl, rows / (sh->num_q_heads / sh->num_kv_heads), [&](int n) {
-        jobs.push_back(start + n);
-        tiles += n;
-        most = std::max(most, (double)n);
+      segment_units(segments[k], seq_lens, qsl, rows / (sh->num_q_heads / sh->num_kv_heads), [&](int tiles) {
+        jobs.push_back(start + tiles);
+        per_cu += tiles;
+        longest = std::max(longest, (double)tiles);
       });
-    std::reverse(jobs.begin(), jobs.end());  // launch order
-    return fixed_us + per_slot * list_makespan(jobs, sh->num_kv_heads, mpa::kPrefillSplitTarget) +
-           per_cu * tiles * sh->num_kv_heads / mpa::kPrefillSplitTarget + longest * most;
+    std::reverse(jobs.begin(), jobs.end());
+    per_cu *= (double)sh->num_kv_heads / mpa::kPrefillSplitTarget;
   };
-  const double whole = d64 ? predict(mpa::kPrefillRowsMfma, 4.7, 6.0, 0.79, 0.252, 0.0)
-                           : predict(mpa::kPrefillRowsMfma, 1.8, 8.0, 1.123, 0.456, 0.023);
-  const double half = d64 ? predict(mpa::kPrefillRowsHalf, 10.1, 0.0, 0.295, 0.18, 0.166)
-                          : predict(mpa::kPrefillRowsHalf, 8.5, 4.0, 0.406, 0.325, 0.382);
-  return half < 0.98 * whole ? mpa::kPrefillRowsHalf : mpa::kPrefillRowsMfma;
+  double whole, half;
+  make_jobs(mpa::kPrefillRowsMfma, d64 ? 6.0 : 8.0);
+  whole = list_makespan(jobs, sh->num_kv_heads, mpa::kPrefillSplitTarget);
+  whole = d64 ? 9.46 + 0.66 * whole + 0.327 * per_cu + 0.096 * longest
+              : 6.13 + 0.694 * whole + 0.482 * per_cu + 0.444 * longest;
+  make_jobs(mpa::kPrefillRowsHalf, d64 ? 2.0 : 8.0);
+  if (d64)
+    half = 11.43 + 0.408 * per_cu + 0.284 * shared_makespan(jobs, sh->num_kv_heads, 3, {1.0, 0.8, 0.65});
+  else
+    half = 3.8 + 0.376 * per_cu + 0.744 * shared_makespan(jobs, sh->num_kv_heads, 2, {1.0, 0.75, 0.0});
+  return half < whole ? mpa::kPrefillRowsHalf : mpa::kPrefillRowsMfma;
 }
 
 // (token, head) rows per workgroup of the f32 launch of segments [c0, c1): 64

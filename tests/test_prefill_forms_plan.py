@@ -1,6 +1,6 @@
 """The form the planner gives a prefill launch, on the host: half or whole
 tiles of bf16 caches and whole tiles or dealt keys of f32 ones, at points
-where the two forms' measured times are at least 4 % apart."""
+where the two forms' measured times are at least 3 % apart."""
 
 import numpy as np
 import pytest
@@ -16,23 +16,24 @@ def rows(dtype, heads, chunks):
 
 
 @pytest.mark.parametrize("heads,chunks,expected", [
-    # whole -> half (us): 41.4 -> 33.4, 53.5 -> 49.4, 92.0 -> 72.2, 20.3 -> 17.0
+    # whole -> half (us): 41.4 -> 33.4, 53.5 -> 49.4, 92.0 -> 72.2, 20.3 -> 17.0, 82.7 -> 79.4
     ((32, 8, 128), [(1003, 500)], 128),
     ((32, 8, 128), [(2027, 0)], 128),
     ((8, 2, 128), [(4075, 0)], 128),
     ((32, 8, 128), [(491, 0)], 128),
-    # 261 -> 272, 883 -> 942, 863 -> 924, 165.9 -> 176.6, 97.6 -> 105.8
+    ((32, 8, 128), [(3001, 0)], 128),
+    # 261 -> 272, 883 -> 942, 863 -> 924, 165.9 -> 176.6, 97.6 -> 105.8, 87.7 -> 92.2
     ((32, 8, 128), [(2027, 8000)], 256),
     ((32, 8, 128), [(2027, 32000)], 256),
     ((64, 8, 128), [(1014, 32000)], 256),
     ((32, 8, 128), [(2987, 2000)], 256),
     ((32, 8, 128), [(3499, 0)], 256),
-    # d 64: 38.9 -> 29.5, 95.8 -> 85.2; KV-split 301 -> 317 and 105.4 -> 109.5; 126.5 -> 130.6
+    ((32, 8, 128), [(3201, 0)], 256),
+    # d 64: 38.9 -> 29.5, 95.8 -> 85.2; KV-split 301 -> 317 and 105.4 -> 109.5
     ((16, 2, 64), [(2038, 0)], 128),
     ((32, 8, 64), [(2539, 2000)], 128),
     ((16, 2, 64), [(2038, 32000)], 256),
     ((16, 2, 64), [(2038, 8000)], 256),
-    ((32, 8, 64), [(3499, 2000)], 256),
     ((32, 8, 64), [(8171, 0)], 128),  # 1,024 workgroups: 0.946 of whole tiles' time
 ])
 def test_bf16_form(heads, chunks, expected):
