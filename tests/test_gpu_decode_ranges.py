@@ -175,3 +175,60 @@ def test_short_rows(torch_gpu, dtype, heads):  # noqa: F811
                    np.random.default_rng(821))
     assert info_of(b).num_decode_items > len(lens)
     check_batch(b, "one row past the short ones", fused=True)
+
+
+@pytest.fixture(scope="module")
+def ranged_step(torch_gpu):  # noqa: F811
+    """A step whose decode rows are dealt as ranges, beside chunks that are
+    split, on the device."""
+    rng = np.random.default_rng(815)
+    specs = [SeqSpec(int(n), 1) for n in rng.integers(2000, 8000, size=24)]
+    specs += [SeqSpec(3000 + 100, 100), SeqSpec(700, 700)]
+    b = make_batch(specs, HeadSpec(16, 16, 64), "bf16", rng)
+    info = info_of(b)
+    assert info.num_decode_items == parts([n.ctx for n in specs[:24]], info.split_tokens // 16)
+    assert info.prefill_max_splits > 1
+    return to_device(b)
+
+
+def test_graph_replays_of_ranges(torch_gpu, ranged_step):  # noqa: F811
+    torch, d = torch_gpu, ranged_step
+    out, lse = torch.full_like(d.q, float("nan")), torch.full(d.q.shape[:2], float("nan"), device=d.q.device)
+    ws = mpa.alloc_workspace(d.q, d.k_cache, d.block_tables, d.seq_lens_host, d.qsl_host, d.scale)
+
+    def step():
+        mpa.append_attention(d.q, d.k_new, d.v_new, d.k_cache, d.v_cache, d.block_tables, d.seq_lens,
+                             d.query_start_loc, d.seq_lens_host, d.qsl_host, out, lse=lse, workspace=ws, scale=d.scale)
+
+    step()
+    torch.cuda.synchronize()
+    eager = [t.clone() for t in (out, lse, d.k_cache, d.v_cache)]
+    assert torch.isfinite(eager[0]).all()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for replay in range(3):
+        out.fill_(float("nan"))
+        lse.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for name, got, e in zip(("out", "lse", "K", "V"), (out, lse, d.k_cache, d.v_cache), eager):
+            assert torch.equal(got.view(torch.uint8), e.view(torch.uint8)), (replay, name)
+
+
+def test_coexec_modes_of_ranges(torch_gpu, ranged_step):  # noqa: F811
+    torch, d = torch_gpu, ranged_step
+    mpa.kv_append(d.k_new, d.v_new, d.k_cache, d.v_cache, d.block_tables, d.seq_lens, d.query_start_loc,
+                  d.seq_lens_host, d.qsl_host)
+    ws = mpa.alloc_workspace(d.q, d.k_cache, d.block_tables, d.seq_lens_host, d.qsl_host, d.scale)
+    args = (d.q, d.k_cache, d.v_cache, d.block_tables, d.seq_lens, d.query_start_loc, d.seq_lens_host, d.qsl_host)
+    o0, l0 = torch.full_like(d.q, float("nan")), torch.full(d.q.shape[:2], float("nan"), device=d.q.device)
+    mpa.mixed_paged_attention(*args, o0, lse=l0, workspace=ws, scale=d.scale)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o0).all()
+    for mode in (1, 2, 3):
+        o, l = torch.full_like(d.q, float("nan")), torch.full_like(l0, float("nan"))
+        assert mpa.coexec_attention(*args, o, lse=l, workspace=ws, scale=d.scale, mode=mode) == mode
+        torch.cuda.synchronize()
+        assert torch.equal(o.view(torch.int16), o0.view(torch.int16)) and torch.equal(l, l0), mode

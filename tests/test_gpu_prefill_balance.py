@@ -1,8 +1,7 @@
 """Prefill batches of more than two workgroups per CU that the planner cuts:
 chunks whose units are long beside the others are KV-split (against the
-oracle), and the last query tiles to run are (against the same batch with
-every chunk whole, each of the two within the bars of the exact result, so
-they are within twice the bars of each other)."""
+oracle), and the last query tiles to run are (against float64 on the first and
+last KV head, 32 tokens at a time: the split tiles are few beside the rest)."""
 
 import numpy as np
 import pytest
@@ -30,6 +29,28 @@ def test_long_units_are_split(torch_gpu, dtype, chunks):  # noqa: F811
     info = mpa.plan_info(sh, b.seq_lens, b.query_start_loc)
     assert info.prefill_max_splits > 1 and info.num_prefill_tiles > 512
     check_batch(b, f"long units split {info.prefill_max_splits} ways {dtype}")
+
+
+def exact_heads(torch, d, s, t0, C, heads, dtype, kv):
+    """(out, lse) of sequence s's C query rows from t0 on, for KV head kv's
+    query heads, in float64."""
+    G = heads[0] // heads[1]
+    n = int(d.seq_lens_host[s])
+    blocks = d.block_tables[s, : -(-n // 16)].long()
+
+    def values(cache, scale):
+        t = cache[blocks, kv]
+        return t.view(torch.float8_e4m3fn).double() * scale if dtype == "fp8" else t.double()
+
+    k = values(d.k_cache, d.k_scale).permute(0, 2, 1, 3).reshape(-1, heads[2])[:n]
+    v = values(d.v_cache, d.v_scale).permute(0, 2, 1).reshape(-1, heads[2])[:n].contiguous()
+    q = d.q[t0: t0 + C, kv * G: (kv + 1) * G].double().reshape(-1, heads[2])
+    scores = (q @ k.t().contiguous()).view(C, G, n) * d.scale
+    last = torch.arange(n - C, n, device=q.device)[:, None, None]
+    scores.masked_fill_(torch.arange(n, device=q.device) > last, -float("inf"))
+    lse = torch.logsumexp(scores, -1)
+    p = torch.exp_(scores.sub_(lse[..., None]))
+    return (p.view(-1, n) @ v).view(C, G, heads[2]), lse
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
@@ -63,6 +84,17 @@ def test_last_tiles_are_split(torch_gpu, dtype, heads, chunks, monkeypatch):  # 
     assert whole_info.prefill_max_splits == 1 and info.prefill_max_splits in (3, 4)
     # fewer units than if whole chunks were split
     assert whole_info.num_prefill_tiles < info.num_prefill_tiles < 2 * whole_info.num_prefill_tiles
-    err = (out - whole).abs()
-    assert torch.isfinite(out).all() and err.max() <= 2e-2 and err.mean() <= 2e-3, (err.max(), err.mean())
-    assert (lse - whole_lse).abs().max() <= 4e-3
+    # Rounding the output to bf16 and each probability to bf16 before the PV
+    # product are errors of up to 2^-9 each, 1.1e-3 rms of a result whose
+    # terms add up at random: 1.7e-3 together, a third of the bar.  One key's
+    # value taken wrongly in 6,000 is 1.8e-2.
+    G = heads[0] // heads[1]
+    for s in range(len(chunks)):
+        t0, t1 = int(d.qsl_host[s]), int(d.qsl_host[s + 1])
+        for kv in (0, heads[1] - 1):
+            ref, ref_lse = exact_heads(torch, d, s, t0, t1 - t0, heads, dtype, kv)
+            for got, got_lse in ((out, lse), (whole, whole_lse)):
+                o, l = got[t0:t1, kv * G: (kv + 1) * G], got_lse[t0:t1, kv * G: (kv + 1) * G]
+                assert torch.isfinite(o).all() and (l - ref_lse).abs().max() <= 2e-3
+                err = [(o[a: a + 32] - ref[a: a + 32]).norm() / ref[a: a + 32].norm() for a in range(0, t1 - t0, 32)]
+                assert max(err) <= 5e-3, (s, kv, [f"{float(e):.1e}" for e in err])
