@@ -9,7 +9,7 @@
 namespace mpa {
 
 constexpr int kBlock = 16;            // tokens per cache block
-constexpr int kWavesPerGroup = 4;     // waves per workgroup in every kernel
+constexpr int kWavesPerGroup = 4;     // waves per workgroup of the appends, the row splits and the f32 tiles
 constexpr int kMaxPlanSeqs = 256;     // sequences per launch (kernel-argument plan)
 constexpr int kMaxPrefillSeqs = 64;   // prefill segments per launch (its plan carries more per segment)
 constexpr int kPrefillSplitTarget = 256;  // prefill workgroups a launch should at least have

@@ -900,9 +900,9 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void decode_short_kernel(AttnArg
 // them in flight; each lane adds its 4 elements of every (256 / D)-th split,
 // and the lanes' sums are combined at the end.  Only the n real splits are
 // read, by as many loads as they need (four loads of two splits' rows took a
-// prompt of 1,000 tokens, 32 heads, from 75.5 us to 78.6).  ml points at split 0's (m, l) pair (8-byte aligned), acc at split
-// 0's row (16-byte aligned); consecutive splits are ml_stride and acc_stride
-// floats apart.
+// prompt of 1,000 tokens, 32 heads, from 75.5 us to 78.6).  ml points at split
+// 0's (m, l) pair (8-byte aligned), acc at split 0's row (16-byte aligned);
+// consecutive splits are ml_stride and acc_stride floats apart.
 __device__ inline float wave_max64(float x) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
@@ -1490,8 +1490,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : D == 64 ? 3 : 2) void 
       // wave's first tile it is still -inf and is taken from the tile's row
       // maximum, but not below -2^63 in log2 units: a row whose scores there
       // are all -inf then has probabilities 0 (not 2^(-inf + inf)), and any
-      // later score moves the reference.  On later tiles the probabilities are formed with the current
-      // reference first, and since a score past the threshold makes its
+      // later score moves the reference.  On later tiles the probabilities are
+      // formed with the current reference first, and since a score past the threshold makes its
       // probability -- and so this lane's row-sum partial -- at least 2^8
       // after bf16 rounding, the tile's maximum is taken only when some
       // lane's partial reaches 2^8.  Then S is recomputed from the operands
