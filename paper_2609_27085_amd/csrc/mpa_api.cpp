@@ -197,6 +197,18 @@ int range_min_blocks(int dtype, int head_dim) {
   return head_dim == 128 ? 24 : 10;
 }
 
+// bf16 and f32 launches of ranges hold waves for three quarters of the device's
+// slots, whole workgroups of a CU each: 192 of 256 CUs draw all that the memory
+// gives, with less contention among them (32 / 8 heads, steps of 6-200 rows,
+// all slots -> three quarters: bf16 281 MB 116.0 -> 113.8 us, 3.2 GB 520.6 ->
+// 503.9, 6.5 GB 990 -> 966; f32 703 -> 674; 7 / 8 of them between the two, 2 / 3
+// slower), and on three quarters of the CUs, where a partitioned step runs its
+// decode, they are still one round (256 rows of 4-8K beside 4,096 tokens, decode
+// there: 1,264 -> 965 us).  Ranges of fewer blocks than this lose more to
+// being longer (64-wide heads, 10 blocks: 37.7 -> 39.3), and so do fp8 launches,
+// whose small workgroups leave waves on every CU short (276.6 -> 302.3).
+constexpr long kFewerWavesBlocks = 14;
+
 // Whether ranges of `range` blocks pay by the rows they meet.  A wave goes over
 // the rows of its range one after another, and each costs it a start (and its
 // new token a wait), about a block's time and more at fp8 and in a step that
@@ -285,13 +297,17 @@ std::vector<DecodeLaunch> decode_layout(const mpa_shape* sh, const Batch& b, con
         (long)(d.c1 - d.c0) * sh->num_kv_heads <= short_pairs(sh->dtype))
       d.range_blocks = -1;
     else if (ranges && blocks < (1L << 30)) {  // block counts are 32 bits in the plan
-      const long per_head = std::max(1L, slots / sh->num_kv_heads);
-      const long range = (blocks + per_head - 1) / per_head;
-      if (forced > 0)
+      auto range_over = [&](long waves) {
+        const long per_head = std::max(1L, waves / sh->num_kv_heads);
+        return (blocks + per_head - 1) / per_head;
+      };
+      long range = range_over(slots);
+      if (forced > 0) {
         d.range_blocks = forced;
-      else if (slots > 0 && range >= range_min_blocks(sh->dtype, sh->head_dim) &&
-               ranges_pay(sh, b, seq_lens, d.c0, d.c1, (int)range, split))
-        d.range_blocks = (int)range;
+      } else if (slots > 0 && range >= range_min_blocks(sh->dtype, sh->head_dim)) {
+        if (sh->dtype != MPA_FP8 && range >= kFewerWavesBlocks) range = range_over(slots * 3 / 4);
+        if (ranges_pay(sh, b, seq_lens, d.c0, d.c1, (int)range, split)) d.range_blocks = (int)range;
+      }
     }
     if (d.range_blocks == 0 && *split == 0) *split = choose_split(sh, b, seq_lens);
     long at = 0;
@@ -573,12 +589,13 @@ double shared_makespan(const std::vector<double>& jobs, int copies, int per, std
     cus /= copies;
     copies = 1;
   }
+  const size_t total = jobs.size() * (size_t)copies;
+  if (total <= cus) return jobs.empty() ? 0.0 : *std::max_element(jobs.begin(), jobs.end());
   struct Cu {
     double left[3], at;  // of its jobs, at that time
     int n;
   };
   std::vector<Cu> cu(cus, Cu{{0.0, 0.0, 0.0}, 0.0, 0});
-  const size_t total = jobs.size() * (size_t)copies;
   size_t next = 0;
   for (int r = 0; r < per; ++r)
     for (size_t c = 0; c < cus && next < total; ++c) cu[c].left[cu[c].n++] = jobs[next++ / copies];
@@ -960,13 +977,21 @@ int run_append(const mpa_shape* shape, const void* k_new, const void* v_new, voi
 namespace {
 
 // The rate of a decode launch whose rows are dealt as ranges, over that of
-// row splits (mpa_rates::decode_gbs): 6,420-6,710 GB/s on the agentic, lent,
+// row splits (mpa_rates::decode_gbs): 6,550-7,040 GB/s on the agentic, lent,
 // budget and longctx steps against the 5,880 fitted to row splits.
-constexpr double kRangeSpeed = 1.105;
-// A launch of ranges has one workgroup for every CU.  On three quarters of
-// the CUs a second round runs the last quarter of them by themselves (the
-// 4,096-token budget steps took 1,408-1,421 us in this mode).
-constexpr double kRangeSpeedQ3 = 0.8;
+constexpr double kRangeSpeed = 1.145;
+// The same launch on 1, 2 and 3 quarters of the CUs, over the share of its
+// speed that row splits keep there (mpa_rates::coexec_decode_q1..q3): one round
+// of workgroups on three quarters, three on one (0.476 of the speed on the
+// whole device, 14 steps) and an uneven two on half of them (0.667).
+constexpr double kRangeShare[4] = {1.0, 0.9, 0.8, 1.0};
+// And what side by side the halves lose then, over coexec_slowdown's excess of
+// 1: on 14 steps (agentic, lent, budget and longctx over several seeds, two TP4
+// shares) the picks with 1.06 and 130 us are 1.2 % slower than the best mode
+// in the mean and none slower than one stream; with 1.15, agentic (seed 0) runs
+// on one stream at 3,664 us (3,372 with decode on a quarter) and budget4096 at
+// 1,352 (1,240 on three).
+constexpr double kRangeOverlap = 0.4;
 
 // The step-time model (mpa_predict_step), shared with the mode planner.
 mpa_step_time model_step(const mpa_shape* shape, const StepPlan& plan, const int32_t* seq_lens_host,
@@ -1166,8 +1191,10 @@ int mpa_plan_coexec(const mpa_shape* shape, const int32_t* seq_lens_host, const 
   if (!(r.coexec_fixed_us >= 0.0)) return MPA_ERR_INVALID;
   const StepPlan& plan = step_plan(shape, seq_lens_host, qsl_host);
   const Batch& b = plan.batch;
-  for (const auto& d : plan.decode)
-    if (d.range_blocks > 0) dfrac[3] = r.coexec_decode_q3 * kRangeSpeedQ3;
+  bool ranges = false;
+  for (const auto& d : plan.decode) ranges |= d.range_blocks > 0;
+  for (int k = 1; ranges && k <= 3; ++k) dfrac[k] *= kRangeShare[k];
+  const double slowdown = ranges ? 1.0 + (r.coexec_slowdown - 1.0) * kRangeOverlap : r.coexec_slowdown;
   const mpa_step_time serial = model_step(shape, plan, seq_lens_host, qsl_host, r);
   double t[4];
   t[0] = serial.decode_us + serial.prefill_us;
@@ -1189,7 +1216,7 @@ int mpa_plan_coexec(const mpa_shape* shape, const int32_t* seq_lens_host, const 
                                        slots, 0.0, 0.0) /
                           all_slots;
     const double prefill_k = serial.prefill_us * std::max(1.0, rounds * share / pfrac[k]);
-    t[k] = std::max(serial.decode_us / dfrac[k], prefill_k) * r.coexec_slowdown + r.coexec_fixed_us;
+    t[k] = std::max(serial.decode_us / dfrac[k], prefill_k) * slowdown + r.coexec_fixed_us;
   }
   int best = 0;
   for (int k = 1; k <= 3; ++k)

@@ -105,15 +105,18 @@ def test_crowded_batch(torch_gpu, dtype):  # noqa: F811
 
 
 def test_ranges_give_way_to_row_splits_past_the_fixed_array(torch_gpu):  # noqa: F811
-    """Ranges cut every launch of 256 rows at 384 places, row splits cut these
-    rows rarely: past the no-allocation call's array the step takes those."""
+    """Ranges cut every launch of 256 rows at 287 places, row splits cut each
+    of these rows at most once: past the no-allocation call's array the step
+    takes those."""
     heads = (128, 8, 128)
     few, ws = plan_of(heads, [700] * 1280, "bf16")
-    assert few.num_decode_items > row_parts([700] * 1280, 1024) and ws <= mpa.MPA_SCRATCH_BYTES
-    assert few.num_decode_items == 5 * parts([700] * 256, few.split_tokens // 16)
-    lens = [700] * 1792
+    r = few.split_tokens // 16
+    assert few.num_decode_items == 5 * parts([700] * 256, r) > row_parts([700] * 1280, 1024)
+    assert ws <= mpa.MPA_SCRATCH_BYTES
+    last = -(-208 * 44 // 288)  # the last launch's range
+    assert (7 * parts([700] * 256, r) + parts([700] * 208, last)) * 128 * 130 * 4 > mpa.MPA_SCRATCH_BYTES
+    lens = [700] * 2000
     many, ws = plan_of(heads, lens, "bf16")
-    assert 7 * parts([700] * 256, few.split_tokens // 16) * 128 * 130 * 4 > mpa.MPA_SCRATCH_BYTES
     assert many.num_decode_items == row_parts(lens, many.split_tokens) and ws <= mpa.MPA_SCRATCH_BYTES
 
 

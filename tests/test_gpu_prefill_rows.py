@@ -22,7 +22,8 @@ CASES = [
     ((7, 7, 64), [(127, 0), (129, 3), (300, 250)], 128, 1),            # G 1
     ((12, 4, 64), [(43, 90), (90, 1700)], 128, 4),                     # G 3, KV-split
     ((64, 8, 128), [(1014, 0)], 128, 1),                               # 256 workgroups of 256 rows
-    ((64, 8, 128), [(1270, 0)], 256, 1),                               # 320
+    ((64, 8, 128), [(1270, 0)], 128, 1),                               # 320
+    ((64, 8, 128), [(1494, 0)], 256, 1),                               # 376
     ((64, 8, 128), [(1790, 10)], 256, 1),
     ((64, 8, 64), [(1700, 10)], 128, 1),                               # 432
     ((64, 8, 64), [(1790, 10)], 256, 1),                               # 448
