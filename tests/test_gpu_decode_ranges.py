@@ -235,3 +235,31 @@ def test_coexec_modes_of_ranges(torch_gpu, ranged_step):  # noqa: F811
         assert mpa.coexec_attention(*args, o, lse=l, workspace=ws, scale=d.scale, mode=mode) == mode
         torch.cuda.synchronize()
         assert torch.equal(o.view(torch.int16), o0.view(torch.int16)) and torch.equal(l, l0), mode
+
+
+@pytest.mark.parametrize("dtype, rows, ctx, waves", [("bf16", 100, 3000, 2304), ("bf16", 256, 6000, 2304),
+                                                     ("fp8", 256, 6000, 3072)])
+def test_ranges_are_one_round_on_three_quarters_of_the_device(torch_gpu, dtype, rows, ctx, waves):  # noqa: F811
+    """12 waves of 128-wide heads to a CU: 3072 on the device, 2304 on 192 CUs.  bf16 ranges are one round there; fp8
+    ranges take every slot."""
+    sl = np.full(rows, ctx, np.int32)
+    sh = mpa.make_shape(num_seqs=rows, num_q_heads=32, num_kv_heads=8, head_dim=128, num_blocks=1 << 20,
+                        max_blocks_per_seq=512, total_q_tokens=rows, scale=0.088, dtype=DTYPE[dtype])
+    info = mpa.plan_info(sh, sl, np.arange(rows + 1, dtype=np.int32))
+    want = -(-rows * -(-ctx // 16) // (waves // 8))
+    assert info.split_tokens == 16 * want and info.num_decode_items == parts(sl, want)
+
+
+def test_planner_keeps_partitioned_steps_beside_ranges(torch_gpu):  # noqa: F811
+    """The modes that measured fastest with the decode half in ranges: agentic 3.43 ms on a quarter of the CUs (3.71 on
+    one stream), budget4096 1.32 on three quarters (1.37); lent and longctx on one stream."""
+    from workloads.configs import config_specs
+
+    for cfg, mode in {"agentic": 1, "budget4096": 3, "lent": 0, "longctx": 0, "decode8b": 0}.items():
+        specs, h, _, _ = config_specs(cfg, 0)
+        sl = np.asarray([s.ctx for s in specs], np.int32)
+        qsl = np.concatenate([[0], np.cumsum([s.q_len for s in specs])]).astype(np.int32)
+        sh = mpa.make_shape(num_seqs=len(sl), num_q_heads=h.num_q_heads, num_kv_heads=h.num_kv_heads,
+                            head_dim=h.head_dim, num_blocks=1 << 20, max_blocks_per_seq=1 << 14,
+                            total_q_tokens=int(qsl[-1]), scale=0.088, dtype=mpa.MPA_BF16)
+        assert mpa.plan_coexec(sh, sl, qsl)[0] == mode, cfg
